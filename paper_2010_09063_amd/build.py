@@ -1,13 +1,18 @@
 """Builds libdpstep.so (HIP, gfx950 only) in-tree with hipcc."""
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-SRC = os.path.join(HERE, "csrc", "dp_step.hip")
+CSRC = os.path.join(HERE, "csrc")
+GEMM_GROUPS = 10  # DP_GEMM_GROUPS in csrc/problems.h
+# (source, extra flags) of every object: the step itself, and the tiled contraction's instantiations in groups
+UNITS = [("dp_step.hip", [])] + [("gemm_group.hip", [f"-DDP_GEMM_GROUP={i}"]) for i in range(GEMM_GROUPS)]
 LIB = os.path.join(HERE, "libdpstep.so")
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # packed fp32 VALU forms are kept off for every device function of the library
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",  # (= PACKED_OFF below)
     # fp32 atomic add as one hardware instruction (embedding scatter)
@@ -22,7 +27,6 @@ def check_packed_fp32_flag(hipcc):
     """The flag that keeps packed fp32 VALU forms off must be understood by the DEVICE pass.  hipcc's host pass
     always reports the feature as unknown (x86 has none of that name), which is harmless and is why that line is
     dropped from the build output below; a device-only compile of an empty kernel must not print it."""
-    import tempfile
     with tempfile.TemporaryDirectory() as d:
         src = os.path.join(d, "probe.hip")
         with open(src, "w") as f:
@@ -36,15 +40,24 @@ def check_packed_fp32_flag(hipcc):
 def build_library(verbose=False):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     check_packed_fp32_flag(hipcc)
-    cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB, SRC]
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    lines = r.stdout.splitlines()
-    # the host pass's "unknown feature" lines are dropped; the device pass was checked above
-    out = "\n".join(l for l in lines if "packed-fp32-ops" not in l)
-    if r.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
-    if verbose and out.strip():
-        print(out)
+
+
+    def run(cmd):
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        # the host pass's "unknown feature" lines are dropped; the device pass was checked above
+        out = "\n".join(l for l in r.stdout.splitlines() if "packed-fp32-ops" not in l)
+        if r.returncode != 0:
+            raise RuntimeError("hipcc failed:\n" + out)
+        if verbose and out.strip():
+            print(out, flush=True)
+
+    with tempfile.TemporaryDirectory() as d:
+        objs = [os.path.join(d, f"{i}.o") for i in range(len(UNITS))]
+        jobs = [[hipcc] + HIPCC_FLAGS + extra + ["-c", "-o", o, os.path.join(CSRC, src)]
+                for o, (src, extra) in zip(objs, UNITS)]
+        with ThreadPoolExecutor(min(8, len(jobs))) as pool:
+            list(pool.map(run, jobs))
+        run([hipcc, "--offload-arch=gfx950", "-shared", "-o", LIB] + objs)
     return LIB
 
 

@@ -26,6 +26,7 @@
 #include "kernels_seq.h"
 #include "lstm_wgrad.h"
 #include "operands.h"
+#include "problems.h"
 #include "rows_gemm.h"
 
 static thread_local char g_hip_err[256] = "";
@@ -38,92 +39,6 @@ static thread_local char g_hip_err[256] = "";
       return DP_EHIP;                                                                                \
     }                                                                                                \
   } while (0)
-
-// ---------------------------------------------------------------- epilogues / problems
-
-template <class A_, class B_>
-struct ProbBase {
-  typedef A_ A;
-  typedef B_ B;
-  int M, N, K, k_chunk, tiles_n, tiles, splits, groups;
-  A a;
-  B b;
-};
-
-// out[m*ld + n] = act(acc + bias[n])                                  (dense forward, LSTM input projection)
-template <class A_, class B_>
-struct ProbBiasAct : ProbBase<A_, B_> {
-  static constexpr bool kReduce = false;
-  float *out; const float *bias; int ld, act;
-  DEVI void store(int, int, int m, int n, float v) const { out[(long)m * ld + n] = act_apply(act, v + bias[n]); }
-};
-
-// out[z*zstride + m*ld + n] = acc                                     (batched plain product)
-template <class A_, class B_>
-struct ProbBatchOut : ProbBase<A_, B_> {
-  static constexpr bool kReduce = false;
-  float *out; long zstride; int ld;
-  DEVI void store(int z, int, int m, int n, float v) const { out[z * zstride + (long)m * ld + n] = v; }
-};
-
-// out[m*ld + n] = acc * act'(a_prev[m*ld + n])                        (dense backward-data)
-template <class A_, class B_>
-struct ProbBwdAct : ProbBase<A_, B_> {
-  static constexpr bool kReduce = false;
-  float *out; const float *a_prev; int ld, act;
-  DEVI void store(int, int, int m, int n, float v) const {
-    long o = (long)m * ld + n;
-    out[o] = act ? v * act_deriv_from_out(act, a_prev[o]) : v;
-  }
-};
-
-// conv forward: m = output channel, n = pixel (b, p): out[b, m, p] = act(acc + bias[m])
-template <class A_, class B_>
-struct ProbConvFwd : ProbBase<A_, B_> {
-  static constexpr bool kReduce = false;
-  float *out; const float *bias; int D, P, act; FastDiv dP;
-  DEVI void store(int, int, int m, int n, float v) const {
-    int b = (int)dP.div(n), p = n - b * P;
-    out[((long)b * D + m) * P + p] = act_apply(act, v + bias[m]);
-  }
-};
-
-// conv backward-data: m = input channel, n = input pixel (b, ih*W+iw): out[b, m, hw] = acc * act'(a_prev)
-template <class A_, class B_>
-struct ProbConvBwd : ProbBase<A_, B_> {
-  static constexpr bool kReduce = false;
-  float *out; const float *a_prev; int C, HW, act; FastDiv dHW;
-  DEVI void store(int, int, int m, int n, float v) const {
-    int b = (int)dHW.div(n), r = n - b * HW;
-    long o = ((long)b * C + m) * HW + r;
-    out[o] = act ? v * act_deriv_from_out(act, a_prev[o]) : v;
-  }
-};
-
-// split-K partial of a clipped sum: part[split*stride + m*ldm + n]; if bias_col >= 0 the column
-// n == bias_col goes to bias_off + m instead (conv: bias gradient is the ones-tap column).
-template <class A_, class B_>
-struct ProbPartial : ProbBase<A_, B_> {
-  static constexpr bool kReduce = false;
-  float *part; long stride; int ldm, bias_col; long bias_off;
-  DEVI void store(int, int split, int m, int n, float v) const {
-    long o = (n == bias_col) ? bias_off + m : (long)m * ldm + n;
-    part[split * stride + o] = v;
-  }
-};
-
-// per-example weight-gradient tile, squared and summed: slot[(slot0 + tile)*slot_stride + z]
-template <class A_, class B_>
-struct ProbSqNorm : ProbBase<A_, B_> {
-  static constexpr bool kReduce = true;
-  float *slots; long slot_stride; int slot0;
-  float *gstore; long gstride; // optional: example z's gradient is also written to gstore[z*gstride + m*N + n]
-  DEVI float contrib(int z, int m, int n, float v) const {
-    if (gstore) gstore[z * gstride + (long)m * this->N + n] = v;
-    return v * v;
-  }
-  DEVI void store_tile(int z, int tile, float s) const { slots[(long)(slot0 + tile) * slot_stride + z] = s; }
-};
 
 // ---------------------------------------------------------------- context
 
