@@ -540,22 +540,27 @@ struct SmallGemmArgs {
 typedef float sg_f32x16 __attribute__((ext_vector_type(16)));
 #define SG_LD 33
 
-// 16-byte alignment of every vector the kernel loads: base pointers, the non-unit strides and K must be multiples of
-// 4 floats; an operand whose rows are the contiguous index has a row count that is one too, or rows of memory padded
-// to the next multiple (its k stride covers it), so that the last group of four may be read whole
+// What the kernel can take: one of an operand's two strides is 1.
 static inline bool dense_small_gemm_fits(const SmallGemmArgs &a) {
+  return a.K >= 1 && (a.a_sk == 1 || a.a_sr == 1) && (a.b_sk == 1 || a.b_sr == 1) && !(a.k_scale && a.b_sk == 1);
+}
+// 16-byte loads: base pointers, the non-unit strides and K are multiples of 4 floats; an operand whose rows are the
+// contiguous index has a row count that is one too, or rows of memory padded to the next multiple (its k stride covers
+// it), so that the last group of four may be read whole.  Everything else (a hidden width of 50) is staged with four
+// 4-byte loads in the place of each: the split-K contraction and its partials, which these widths took before, cost the
+// 104-50-10 network 15.6 + 13.6 us at 128 examples.
+static inline bool dense_small_gemm_vec(const SmallGemmArgs &a) {
   auto al = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   const bool a_kc = a.a_sk == 1, b_kc = a.b_sk == 1;
-  if (!al(a.A) || !al(a.B) || a.K < 1 || ((a_kc || b_kc) && (a.K & 3) != 0)) return false;
-  if (a.k_scale && b_kc) return false;
-  if (a_kc ? (a.a_sr & 3) != 0 : (a.a_sr != 1 || (a.a_sk & 3) != 0 || a.a_sk < ((a.M + 3) & ~3))) return false;
-  if (b_kc ? (a.b_sr & 3) != 0 : (a.b_sr != 1 || (a.b_sk & 3) != 0 || a.b_sk < ((a.N + 3) & ~3))) return false;
+  if (!al(a.A) || !al(a.B) || ((a_kc || b_kc) && (a.K & 3) != 0)) return false;
+  if (a_kc ? (a.a_sr & 3) != 0 : ((a.a_sk & 3) != 0 || a.a_sk < ((a.M + 3) & ~3))) return false;
+  if (b_kc ? (a.b_sr & 3) != 0 : ((a.b_sk & 3) != 0 || a.b_sk < ((a.N + 3) & ~3))) return false;
   return true;
 }
 
 // One operand slice: rows r0 .. r0 + 31 (R real rows, row R the constant 1 if ONES), k0 .. k0 + 31, as four 16-byte
 // items per lane.  KC: k is the contiguous index (item = row, four k); otherwise the row is (item = k, four rows).
-template <bool KC>
+template <bool KC, bool VEC>
 __device__ __forceinline__ void sg_fetch(const float *P, long sr, long sk, int r0, int R, int K, int k0, int lane, float4 (&v)[4]) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -563,15 +568,25 @@ __device__ __forceinline__ void sg_fetch(const float *P, long sr, long sk, int r
     if (KC) {
       const int row = r0 + (it >> 3), k = k0 + 4 * (it & 7);
       const bool ok = row < R && k < K;
-      v[q] = *reinterpret_cast<const float4 *>(P + (ok ? (long)row * sr + k : 0));
+      if (VEC) {
+        v[q] = *reinterpret_cast<const float4 *>(P + (ok ? (long)row * sr + k : 0));
+      } else {
+        const float *p = P + (row < R ? (long)row * sr : 0);
+        v[q] = make_float4(p[k < K ? k : 0], p[k + 1 < K ? k + 1 : 0], p[k + 2 < K ? k + 2 : 0], p[k + 3 < K ? k + 3 : 0]);
+      }
     } else {
       const int k = k0 + (it >> 3), row = r0 + 4 * (it & 7);
-      const bool ok = row < R && k < K; // (a group that crosses R reads the row's padding: see dense_small_gemm_fits)
-      v[q] = *reinterpret_cast<const float4 *>(P + (ok ? (long)k * sk + row : 0));
+      const bool ok = row < R && k < K; // (a group that crosses R reads the row's padding: see dense_small_gemm_vec)
+      if (VEC) {
+        v[q] = *reinterpret_cast<const float4 *>(P + (ok ? (long)k * sk + row : 0));
+      } else {
+        const float *p = P + (k < K ? (long)k * sk : 0);
+        v[q] = make_float4(p[row < R ? row : 0], p[row + 1 < R ? row + 1 : 0], p[row + 2 < R ? row + 2 : 0], p[row + 3 < R ? row + 3 : 0]);
+      }
     }
   }
 }
-template <bool KC>
+template <bool KC, bool VEC>
 __device__ __forceinline__ void sg_stash(float *T, int r0, int R, bool ones, int K, int k0, int lane, const float4 (&v)[4]) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -579,9 +594,11 @@ __device__ __forceinline__ void sg_stash(float *T, int r0, int R, bool ones, int
     float e[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
     if (KC) {
       const int rl = it >> 3, kl = 4 * (it & 7), row = r0 + rl;
-      const bool ok = row < R && k0 + kl < K, one = ones && row == R && k0 + kl < K;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) T[(kl + j) * SG_LD + rl] = ok ? e[j] : (one ? 1.f : 0.f);
+      for (int j = 0; j < 4; ++j) {
+        const bool kin = k0 + kl + (VEC ? 0 : j) < K;
+        T[(kl + j) * SG_LD + rl] = kin && row < R ? e[j] : (kin && ones && row == R ? 1.f : 0.f);
+      }
     } else {
       const int kl = it >> 3, rl = 4 * (it & 7), row = r0 + rl;
       const bool kin = k0 + kl < K;
@@ -594,7 +611,7 @@ __device__ __forceinline__ void sg_stash(float *T, int r0, int R, bool ones, int
 // NW waves per workgroup (the K split); LDS: NW areas of 2 x 32 x 33 floats, passed as dynamic shared memory
 // A launch may carry a second product of the same operand layouts (the two clipped sums of a two-layer network):
 // rows ny0 and up of the grid are its tiles.
-template <bool A_KC, bool B_KC, int NW>
+template <bool A_KC, bool B_KC, bool VEC, int NW>
 __global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGemmArgs p0, const SmallGemmArgs p1, int ny0) {
   extern __shared__ float sg_lds[]; // per wave: A slice [k][m], B slice [k][n]; after the K loop: the wave's partial tile
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lk = lane >> 5;
@@ -637,18 +654,18 @@ __global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGe
   };
   int sl = wave;
   if (sl < n_slices) {
-    sg_fetch<A_KC>(a.A, a.a_sr, a.a_sk, m0, a.M, a.K, 32 * sl, lane, va);
-    sg_fetch<B_KC>(a.B, a.b_sr, a.b_sk, n0, a.N, a.K, 32 * sl, lane, vb);
+    sg_fetch<A_KC, VEC>(a.A, a.a_sr, a.a_sk, m0, a.M, a.K, 32 * sl, lane, va);
+    sg_fetch<B_KC, VEC>(a.B, a.b_sr, a.b_sk, n0, a.N, a.K, 32 * sl, lane, vb);
     fetch_scale(32 * sl);
   }
   for (; sl < n_slices; sl += NW) {
     apply_scale();
-    sg_stash<A_KC>(As, m0, a.M, a.a_ones != 0, a.K, 32 * sl, lane, va);
-    sg_stash<B_KC>(Bs, n0, a.N, false, a.K, 32 * sl, lane, vb);
+    sg_stash<A_KC, VEC>(As, m0, a.M, a.a_ones != 0, a.K, 32 * sl, lane, va);
+    sg_stash<B_KC, VEC>(Bs, n0, a.N, false, a.K, 32 * sl, lane, vb);
     __builtin_amdgcn_wave_barrier(); // (the slice is read by other lanes of this wave: LDS operations of a wave complete in order)
     const int nx = min(sl + NW, n_slices - 1); // (past the wave's last slice: one is read again, unused)
-    sg_fetch<A_KC>(a.A, a.a_sr, a.a_sk, m0, a.M, a.K, 32 * nx, lane, va);
-    sg_fetch<B_KC>(a.B, a.b_sr, a.b_sk, n0, a.N, a.K, 32 * nx, lane, vb);
+    sg_fetch<A_KC, VEC>(a.A, a.a_sr, a.a_sk, m0, a.M, a.K, 32 * nx, lane, va);
+    sg_fetch<B_KC, VEC>(a.B, a.b_sr, a.b_sk, n0, a.N, a.K, 32 * nx, lane, vb);
     fetch_scale(32 * nx);
 #pragma unroll
     for (int s2 = 0; s2 < 16; ++s2)
@@ -688,10 +705,12 @@ static inline size_t dense_small_gemm_lds_bytes() { return sizeof(float) * SG_WA
 static inline bool dense_small_gemm_prepare() {
   const int bytes = (int)dense_small_gemm_lds_bytes();
   const hipFuncAttribute at = hipFuncAttributeMaxDynamicSharedMemorySize;
-  return hipFuncSetAttribute((const void *)dense_small_gemm_kernel<true, true, SG_WAVES>, at, bytes) == hipSuccess &&
-         hipFuncSetAttribute((const void *)dense_small_gemm_kernel<true, false, SG_WAVES>, at, bytes) == hipSuccess &&
-         hipFuncSetAttribute((const void *)dense_small_gemm_kernel<false, true, SG_WAVES>, at, bytes) == hipSuccess &&
-         hipFuncSetAttribute((const void *)dense_small_gemm_kernel<false, false, SG_WAVES>, at, bytes) == hipSuccess;
+  bool ok = true;
+#define DP_SG_ATTR(a_, b_, v_) ok = ok && hipFuncSetAttribute((const void *)dense_small_gemm_kernel<a_, b_, v_, SG_WAVES>, at, bytes) == hipSuccess;
+  DP_SG_ATTR(true, true, true) DP_SG_ATTR(true, false, true) DP_SG_ATTR(false, true, true) DP_SG_ATTR(false, false, true)
+  DP_SG_ATTR(true, true, false) DP_SG_ATTR(true, false, false) DP_SG_ATTR(false, true, false) DP_SG_ATTR(false, false, false)
+#undef DP_SG_ATTR
+  return ok;
 }
 
 // b: a second product in the same launch, or null; both must have the same contiguous indices
@@ -702,8 +721,11 @@ static inline void launch_dense_small_gemm(hipStream_t st, const SmallGemmArgs &
   const size_t lds = dense_small_gemm_lds_bytes();
   const bool a_kc = a.a_sk == 1, b_kc = a.b_sk == 1;
   const SmallGemmArgs &a2 = b ? *b : a;
-  if (a_kc && b_kc) hipLaunchKernelGGL((dense_small_gemm_kernel<true, true, SG_WAVES>), grid, block, lds, st, a, a2, ny0);
-  else if (a_kc) hipLaunchKernelGGL((dense_small_gemm_kernel<true, false, SG_WAVES>), grid, block, lds, st, a, a2, ny0);
-  else if (b_kc) hipLaunchKernelGGL((dense_small_gemm_kernel<false, true, SG_WAVES>), grid, block, lds, st, a, a2, ny0);
-  else hipLaunchKernelGGL((dense_small_gemm_kernel<false, false, SG_WAVES>), grid, block, lds, st, a, a2, ny0);
+  const bool vec = dense_small_gemm_vec(a) && (!b || dense_small_gemm_vec(*b));
+#define DP_SG_CASE(a_, b_, v_)                                                                                          \
+  if (a_kc == a_ && b_kc == b_ && vec == v_)                                                                            \
+    hipLaunchKernelGGL((dense_small_gemm_kernel<a_, b_, v_, SG_WAVES>), grid, block, lds, st, a, a2, ny0);
+  DP_SG_CASE(true, true, true) DP_SG_CASE(true, false, true) DP_SG_CASE(false, true, true) DP_SG_CASE(false, false, true)
+  DP_SG_CASE(true, true, false) DP_SG_CASE(true, false, false) DP_SG_CASE(false, true, false) DP_SG_CASE(false, false, false)
+#undef DP_SG_CASE
 }

@@ -22,6 +22,7 @@
 #include "conv_wino.h"
 #include "conv_first.h"
 #include "dense_fused.h"
+#include "emb_pairs.h"
 #include "kernels_misc.h"
 #include "kernels_seq.h"
 #include "lstm_wgrad.h"
@@ -115,10 +116,14 @@ struct dp_ctx {
   int last_batch = -1;
   dp_plan_options opt{}; // route switches, read once at init
   int *bad = nullptr;    // dp_step_validate: number of out-of-range ids / labels
-  uint32_t *xb = nullptr; int *yb = nullptr, *idx = nullptr; // dp_step_loop: the drawn minibatch (allocated on its first call)
+  uint32_t *xb = nullptr; int *yb = nullptr; // dp_step_loop: the drawn minibatch (allocated on its first call)
   bool fused1 = false; // the model is one dense layer small enough for dense1_fused_kernel
   bool fusedcnn = false; float *cnn_part = nullptr; // the small MNIST-shaped CNN in one launch (cnn_small_fused_kernel)
   bool joint2 = false; // fused2 / head2 and both clipped sums in one dense_small_gemm_kernel launch
+  // embedding, mean over the steps, dense classifier: everything per example in bag_net_kernel, the batch sums over
+  // (token, example) pairs in emb_accum_kernel
+  bool bag = false; int bag_shift = 0;
+  float *bag_mean = nullptr, *bag_sdelta = nullptr, *bag_rows = nullptr; uint32_t *pairs = nullptr; uint32_t *pair_off = nullptr;
   bool fused2 = false; // two dense layers: everything between the hidden layer's forward product and the clipped sums in dense2_mid_kernel
   // The embedding layer's counting sort of the batch's tokens depends on the inputs alone: it runs on a stream of the
   // library's own (fork / join by events) beside the forward pass.
@@ -628,13 +633,20 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
     (void)hipGetLastError();
     c->opt.no_small_gemm = 1;
   }
-  // both clipped sums of the two-layer network in one launch of that kernel (widths in whole groups of four floats)
-  c->joint2 = c->fused2 && !c->opt.no_small_gemm && c->L[0].d.in_features % 4 == 0 && c->L[0].d.out_features % 4 == 0;
-  if (c->head2 && !c->opt.no_small_gemm) { // the same for the two dense layers that close a deeper network
+  // The embedding network in two launches.  A table too large for the LDS of its workgroups keeps the sorted lists, and
+  // so does a context whose options name those lists' launches.
+  c->bag = c->L.size() == 3 && c->L[0].d.kind == DP_EMBEDDING && c->L[1].d.kind == DP_SEQ_MEAN && c->L[2].d.kind == DP_DENSE &&
+           c->L[0].d.embed_dim <= BAG_DMAX && c->L[2].d.out_features <= 16 &&
+           emb_accum_wg_shift(c->L[0].d.vocab, c->L[0].d.embed_dim) >= 0 && !c->opt.no_fused_dense &&
+           !c->opt.no_single_bucket && !c->opt.no_side_stream;
+  if (c->bag) c->bag_shift = emb_accum_wg_shift(c->L[0].d.vocab, c->L[0].d.embed_dim);
+  // both clipped sums of a two-layer network, or of the two dense layers that close a deeper one, in one launch of that kernel
+  c->joint2 = c->fused2 && !c->opt.no_small_gemm;
+  if (c->head2 && !c->opt.no_small_gemm) { // (a deeper network's last layers: widths in whole groups of four floats)
     const dp_layer_desc &h = c->L[c->L.size() - 2].d;
     c->joint2 = h.in_features % 4 == 0 && h.out_features % 4 == 0;
   }
-  if (rc == DP_OK && !c->L.empty() && c->L[0].d.kind == DP_EMBEDDING && !c->opt.no_side_stream) {
+  if (rc == DP_OK && !c->L.empty() && c->L[0].d.kind == DP_EMBEDDING && !c->bag && !c->opt.no_side_stream) {
     if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) != hipSuccess) {
@@ -650,19 +662,21 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
   for (auto &l : c->L) {
     if (rc != DP_OK) break;
     const bool emb = l.d.kind == DP_EMBEDDING;
-    rc = dev_alloc(c, &l.a, mb * l.out_size); // embedding: the gathered rows x[B, T, D]
-    if (rc == DP_OK) rc = dev_alloc(c, &l.g, mb * std::max<long>(l.out_size, &l == &c->L.back() ? 16 : 0)); // (the loss gradient: rows of up to 16 floats)
+    if (!c->bag) { // (bag_net_kernel keeps them in one workgroup)
+      rc = dev_alloc(c, &l.a, mb * l.out_size); // embedding: the gathered rows x[B, T, D]
+      if (rc == DP_OK) rc = dev_alloc(c, &l.g, mb * std::max<long>(l.out_size, &l == &c->L.back() ? 16 : 0)); // (the loss gradient: rows of up to 16 floats)
+    }
     if (rc == DP_OK && l.d.kind == DP_MAXPOOL2D) rc = dev_alloc(c, &l.arg, mb * l.out_size);
     if (rc == DP_OK && l.p_count > 0) {
       l.max_split = 1;
-      if (!emb) {
+      if (!emb && !c->bag) {
         long ms = DP_MAX_PART_FLOATS / l.p_count;
         l.max_split = (int)(ms < 8 ? 8 : (ms > DP_MAX_SPLIT ? DP_MAX_SPLIT : ms));
       }
       l.pstride = (l.p_count + 3) & ~3l;
       rc = dev_alloc(c, &l.part, (size_t)l.max_split * l.pstride);
     }
-    if (rc == DP_OK && l.d.kind == DP_DENSE) {
+    if (rc == DP_OK && l.d.kind == DP_DENSE && !c->bag) {
       // a small output with a long K would leave most CUs idle and expose every load's latency: split K
       GemmShape sh = pick_tile(max_batch, l.d.out_features, 1, c->opt.gemm_plain_tiles == 0);
       long tiles = (long)sh.tiles_m * sh.tiles_n;
@@ -739,7 +753,7 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
       o.n_total = (long)o.D * (o.C * o.KK + 1);
       rc = dev_alloc(c, &l.gst, (size_t)mb * o.n_total);
     }
-    if (rc == DP_OK && emb) {
+    if (rc == DP_OK && emb && !c->bag) {
       const size_t V = l.d.vocab;
       rc = dev_alloc(c, &l.e_count, V + 1);
       if (rc == DP_OK) rc = dev_alloc(c, &l.e_start, V + 1);
@@ -767,6 +781,14 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
   if (rc == DP_OK) rc = dev_alloc(c, &c->s, mb);
   if (rc == DP_OK) rc = dev_alloc(c, &c->ones, mb);
   if (rc == DP_OK) rc = dev_alloc(c, &c->bad, 1);
+  if (rc == DP_OK && c->bag) {
+    const size_t T = c->m.seq_len, D = c->L[0].d.embed_dim;
+    rc = dev_alloc(c, &c->bag_mean, mb * D);
+    if (rc == DP_OK) rc = dev_alloc(c, &c->bag_sdelta, mb * 16);
+    if (rc == DP_OK) rc = dev_alloc(c, &c->bag_rows, mb * D);
+    if (rc == DP_OK) rc = dev_alloc(c, &c->pairs, mb * T);
+    if (rc == DP_OK) rc = dev_alloc(c, &c->pair_off, mb << c->bag_shift);
+  }
   if (rc == DP_OK && c->fusedcnn) rc = dev_alloc(c, &c->cnn_part, (size_t)256 * ((cnnf::NPARAM + 3) & ~3));
   if (rc == DP_OK) {
     std::vector<float> one(mb, 1.f);
@@ -888,6 +910,35 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
     });
     FinalizeSeg &sg = fa.seg[fa.nseg++];
     sg.p_off = 0; sg.n = l.p_count; sg.part = l.part; sg.stride = dense1_part_stride(a.d_in, a.N); sg.nsplit = tiles;
+  } else if (B > 0 && c->bag) {
+    // embedding, mean, classifier: one launch per example, one for the batch sums
+    Layer &le = c->L[0], &ld = c->L[2];
+    BagArgs a{};
+    a.tok = (const int *)x; a.E = params; a.W = params + ld.p_off; a.bias = a.W + (long)ld.d.in_features * ld.d.out_features;
+    a.y = (const int *)y; a.mean = c->bag_mean; a.sdelta = c->bag_sdelta; a.rows = c->bag_rows; a.pairs = c->pairs;
+    a.off = c->pair_off; a.off_ld = c->maxB; a.wg_shift = c->bag_shift; a.norms = priv ? c->norms : nullptr; a.s = priv ? c->s : nullptr;
+    a.T = le.outC; a.D = le.d.embed_dim; a.N = ld.d.out_features; a.C = C;
+    const bool vec = (a.D & 3) == 0 && aligned16(a.E);
+    Ln("bag_net", dim3(B), dim3(256), [&](hipStream_t st) {
+#define DP_BAG_CASE(kpt_) \
+      if (vec) hipLaunchKernelGGL((bag_net_kernel<kpt_, true>), dim3(B), dim3(256), 0, st, a); \
+      else hipLaunchKernelGGL((bag_net_kernel<kpt_, false>), dim3(B), dim3(256), 0, st, a);
+      if (a.T <= 256) { DP_BAG_CASE(1) } else if (a.T <= 512) { DP_BAG_CASE(2) } else { DP_BAG_CASE(4) }
+#undef DP_BAG_CASE
+    });
+    EmbAccumArgs q{};
+    q.pairs = c->pairs; q.off = c->pair_off; q.off_ld = c->maxB; q.rows = c->bag_rows; q.out = le.part;
+    q.B = B; q.T = a.T; q.D = a.D; q.V = le.d.vocab; q.wg_shift = c->bag_shift;
+    for (q.lpm = 1; q.lpm < 64 && q.lpm < a.D;) q.lpm <<= 1;
+    q.mean = c->bag_mean; q.sdelta = c->bag_sdelta; q.out_w = ld.part; q.N = a.N;
+    dim3 grid((1u << q.wg_shift) + 1), block(EMB_ACC_THREADS);
+    Ln("emb_pair_sum", grid, block, [&](hipStream_t st) {
+      hipLaunchKernelGGL(emb_accum_kernel<false>, grid, block, emb_accum_lds_bytes(q.V, q.D, q.wg_shift), st, q);
+    });
+    for (Layer *l : {&le, &ld}) {
+      FinalizeSeg &sg = fa.seg[fa.nseg++];
+      sg.p_off = l->p_off; sg.n = l->p_count; sg.part = l->part; sg.stride = l->pstride; sg.nsplit = 1;
+    }
   } else if (B > 0) {
     // The embedding layer's token lists for its clipped sum (a counting sort of the batch by token id) and its zeroed
     // partial: inputs of emb_reduce_kernel that depend on x alone.
@@ -997,7 +1048,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
           g.bias = W + (long)l.d.in_features * l.d.out_features; g.act = l.d.act;
           g.C = l.a; g.c_sm = l.d.out_features; g.c_sn = 1; g.C_ones = nullptr;
           g.M = B; g.N = l.d.out_features; g.K = l.d.in_features; g.a_ones = 0;
-          if (dense_small_gemm_fits(g)) {
+          if (f2 ? dense_small_gemm_fits(g) : dense_small_gemm_vec(g)) {
             Ln(LL("dense_fwd"), dim3(1), dim3(256), [&](hipStream_t st) { launch_dense_small_gemm(st, g); });
             break;
           }
@@ -1241,7 +1292,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
         g1.B = l1.g; g1.b_sr = 1; g1.b_sk = 16;
         g1.C = l1.part; g1.c_sm = l1.d.out_features; g1.c_sn = 1; g1.C_ones = l1.part + (long)l1.d.in_features * l1.d.out_features;
         g1.M = l1.d.in_features; g1.N = l1.d.out_features; g1.K = B; g1.act = DP_ACT_NONE;
-        joint = dense_small_gemm_fits(g0) && dense_small_gemm_fits(g1);
+        joint = dense_small_gemm_vec(g0) && dense_small_gemm_vec(g1);
         if (joint) a.d2_ld = 16;
       }
       if (priv) {
@@ -1820,13 +1871,17 @@ __global__ void sample_indices_kernel(uint32_t k0, uint32_t k1, long n, int batc
   idx[k] = (int)(((uint64_t)r[k & 3] * (uint64_t)n) >> 32);
 }
 
-// one workgroup per drawn example: its input row (fp32 features or int32 token ids: 4-byte words) and its label
-__global__ void gather_rows_kernel(const uint32_t *__restrict__ data_x, const int *__restrict__ data_y,
-                                   const int *__restrict__ idx, long row_words, uint32_t *__restrict__ xb,
-                                   int *__restrict__ yb) {
-  const long src = (long)idx[blockIdx.x] * row_words, dst = (long)blockIdx.x * row_words;
+// One workgroup per drawn example: its index (as above; one Philox block per thread costs less than a launch of its
+// own), its input row (fp32 features or int32 token ids: 4-byte words) and its label.
+__global__ void draw_rows_kernel(const uint32_t *__restrict__ data_x, const int *__restrict__ data_y, uint32_t k0,
+                                 uint32_t k1, long n, long row_words, uint32_t *__restrict__ xb, int *__restrict__ yb) {
+  uint32_t r[4];
+  philox4x32_10((uint32_t)(blockIdx.x >> 2), 0u, 1u, 0u, k0, k1, r);
+  const uint32_t w = blockIdx.x & 2 ? (blockIdx.x & 1 ? r[3] : r[2]) : (blockIdx.x & 1 ? r[1] : r[0]);
+  const long idx = (long)(((uint64_t)w * (uint64_t)n) >> 32);
+  const long src = idx * row_words, dst = (long)blockIdx.x * row_words;
   for (long i = threadIdx.x; i < row_words; i += blockDim.x) xb[dst + i] = data_x[src + i];
-  if (threadIdx.x == 0) yb[blockIdx.x] = data_y[idx[blockIdx.x]];
+  if (threadIdx.x == 0) yb[blockIdx.x] = data_y[idx];
 }
 
 extern "C" int dp_step_sample_indices(uint64_t seed, int64_t n_examples, int batch, int32_t *indices, void *hip_stream) {
@@ -1853,17 +1908,14 @@ extern "C" int dp_step_loop(dp_ctx *c, float *params, const void *data_x, const 
   if (!c->xb) { // first call on this context: room for one drawn minibatch
     int rc = dev_alloc(c, &c->xb, (size_t)c->maxB * row_words);
     if (rc == DP_OK) rc = dev_alloc(c, &c->yb, c->maxB);
-    if (rc == DP_OK) rc = dev_alloc(c, &c->idx, c->maxB);
     if (rc != DP_OK) { c->xb = nullptr; return rc; }
   }
   Launcher Ln{c};
   for (int t = 0; t < steps; ++t) {
     const uint64_t seed = seed0 + (uint64_t)t;
     Ln("sample_minibatch", dim3(1), dim3(256), [&](hipStream_t st) {
-      hipLaunchKernelGGL(sample_indices_kernel, grid1d(batch, 256), dim3(256), 0, st, (uint32_t)seed, (uint32_t)(seed >> 32),
-                         (long)n_examples, batch, c->idx);
-      hipLaunchKernelGGL(gather_rows_kernel, dim3(batch), dim3(256), 0, st, (const uint32_t *)data_x, (const int *)data_y,
-                         (const int *)c->idx, row_words, c->xb, c->yb);
+      hipLaunchKernelGGL(draw_rows_kernel, dim3(batch), dim3(256), 0, st, (const uint32_t *)data_x, (const int *)data_y,
+                         (uint32_t)seed, (uint32_t)(seed >> 32), (long)n_examples, row_words, c->xb, c->yb);
     });
     int rc = run_step(c, params, c->xb, c->yb, batch, true, C, sigma, seed, nullptr, params, lr / (float)batch);
     if (rc != DP_OK) return rc;
@@ -1887,6 +1939,7 @@ extern "C" int dp_step_describe_plan(const dp_ctx *c, char *buf, size_t cap) {
       if (c->fused2) { norm = "fused"; if (i == 1) { fwd = bwd = "fused"; sum = c->joint2 ? "joint" : "fused"; } }
       if (c->head2 && i + 2 >= c->L.size()) { norm = "head"; if (i + 1 == c->L.size()) { fwd = bwd = "head"; if (c->joint2) sum = "joint"; } }
       if (c->fusedcnn) fwd = bwd = norm = sum = "fused-net";
+      if (c->bag) { fwd = bwd = norm = "fused"; sum = "pairs"; }
       break;
     case DP_CONV2D:
       fwd = l.u_f ? (l.wino_f == 2 ? "mf64" : "mf32") : (l.first_fwd ? "first" : (l.dir_fwd ? "direct" : "generic"));
@@ -1901,7 +1954,10 @@ extern "C" int dp_step_describe_plan(const dp_ctx *c, char *buf, size_t cap) {
       sum = l.gst ? "weighted" : ((l.wino_wgu || l.wino_wg) ? "mf" : (l.dir_wg ? (l.wg_ws ? "ws" : "direct") : "generic"));
       if (c->fusedcnn) fwd = bwd = norm = sum = "fused-net";
       break;
-    case DP_EMBEDDING: fwd = "gather"; norm = "sorted-segments"; sum = "scatter"; break;
+    case DP_EMBEDDING:
+      fwd = "gather"; norm = "sorted-segments"; sum = "scatter";
+      if (c->bag) { fwd = norm = "fused"; sum = "pairs"; }
+      break;
     case DP_LSTM_LAST:
     case DP_LSTM_SEQ: fwd = "recurrence"; bwd = "recurrence"; norm = l.gst ? "generic+store" : "generic"; sum = l.gst ? "weighted" : "generic"; break;
     default: break;

@@ -1,0 +1,49 @@
+"""Parity of kernels and dispatch branches at the sizes where they can go wrong: edges of tiles, remainders, the
+smallest and the largest of their ranges.  Same oracle and bars as tests/test_gpu_parity.py."""
+import numpy as np
+import pytest
+
+import dp_workloads as W
+from tests.test_gpu_parity import _check_all_regimes
+
+pytestmark = pytest.mark.gpu
+
+
+def _tokens(batch, seq, vocab, rng, kind):
+    if kind == "same":  # one token throughout: every step of an example adds up to one row
+        return np.full((batch, seq), vocab - 1, dtype=np.int32)
+    if kind == "uniform":  # as many distinct tokens as there can be
+        return rng.integers(0, vocab, size=(batch, seq)).astype(np.int32)
+    return W.zipf_tokens(rng, vocab, 1.1, (batch, seq))
+
+
+@pytest.mark.parametrize("vocab,dim,seq,classes,batch,kind", [
+    (1, 1, 1, 2, 1, "same"),              # the smallest of everything
+    (300, 3, 255, 2, 70, "zipf"),         # scalar rows; one key per thread, one short of the sort's size
+    (256, 127, 256, 15, 9, "uniform"),    # a row per workgroup; the widest scalar rows
+    (257, 128, 257, 16, 9, "same"),       # the widest rows and the most classes; two keys per thread
+    (2000, 20, 1024, 4, 70, "uniform"),   # four keys per thread; more pairs than a workgroup's list holds at a time
+    (5000, 8, 40, 3, 1100, "zipf"),       # more examples than a pass takes; tokens of several chunks
+    (70000, 36, 12, 2, 33, "uniform"),    # a table too large for 256 workgroups' LDS
+])
+def test_embedding_mean_classifier_network(vocab, dim, seq, classes, batch, kind):
+    from paper_2010_09063_amd import DpStep
+    m = W.model(W.token_input(seq), [W.embedding(vocab, dim), W.seq_mean(), W.dense(dim, classes)], classes)
+    rng = np.random.default_rng(seq)
+    x = _tokens(batch, seq, vocab, rng, kind)
+    y = rng.integers(0, classes, size=batch).astype(np.int32)
+    theta = W.init_params(m, rng, bias_scale=0.2) * np.float32(4)
+    st = DpStep(m, batch)
+    assert st.dp_step_describe_plan()[0]["sum"] == "pairs"
+    _check_all_regimes(m, x, y, theta, f"embedding V{vocab} D{dim} T{seq} N{classes} B{batch} {kind}", stepper=st)
+
+
+@pytest.mark.parametrize("d_in,hidden,classes,batch", [
+    (1, 1, 2, 1), (5, 31, 3, 33), (33, 32, 2, 31), (257, 129, 15, 65), (104, 50, 10, 1025), (1023, 639, 7, 96)])
+def test_two_layer_networks_of_widths_off_the_vector_size(d_in, hidden, classes, batch):
+    """Widths that are no multiples of four floats: one short of, at and past a 32-wide tile or slice."""
+    m = W.model(W.image_input(d_in), [W.dense(d_in, hidden, act="tanh"), W.dense(hidden, classes)], classes)
+    rng = np.random.default_rng(hidden)
+    x, y = W.make_inputs(m, batch, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.3)
+    _check_all_regimes(m, x, y, theta, f"dense {d_in}->{hidden}->{classes}/B{batch}")
