@@ -34,17 +34,17 @@ __device__ __forceinline__ uint32_t emb_pair_key(uint32_t v, int i, int wg_shift
 // of owner w at off[w * off_ld]); sq (one value per thread) receives this thread's share of the sum of squared counts.
 // head, start [EMB_WG_MAX + 1], wsum: LDS scratch.
 template <int KPT>
-__device__ __forceinline__ void emb_write_pairs(const uint32_t *key, uint16_t *head, uint16_t *start, int *wsum, int T, int tid,
+__device__ __forceinline__ int emb_write_pairs(const uint32_t *key, uint16_t *head, uint16_t *start, int *wsum, int T, int tid,
                                                 int wg_shift, uint32_t *__restrict__ pairs, uint32_t *__restrict__ off,
                                                 long off_ld, int &sq) {
   const int lane = tid & 63, wave = tid >> 6;
   uint64_t mine[KPT];
 #pragma unroll
   for (int m = 0; m < KPT; ++m) {
-    const int p = (m << 8) + tid;
+    const int p = (m << 8) + (tid & 255); // (threads past the first 256 have no part in this)
     const bool h = p < T && (p == 0 || (key[p] >> 10) != (key[p - 1] >> 10));
     mine[m] = __ballot(h);
-    if (lane == 0) wsum[m * 4 + wave] = __popcll(mine[m]);
+    if (lane == 0 && wave < 4) wsum[m * 4 + wave] = __popcll(mine[m]);
   }
   __syncthreads();
   int total = 0;
@@ -55,18 +55,18 @@ __device__ __forceinline__ void emb_write_pairs(const uint32_t *key, uint16_t *h
     int base = 0;
 #pragma unroll
     for (int q = 0; q < KPT * 4; ++q) base += q < m * 4 + wave ? wsum[q] : 0;
-    if ((mine[m] >> lane) & 1) head[base + __popcll(mine[m] & ((1ull << lane) - 1))] = (uint16_t)((m << 8) + tid);
+    if (wave < 4 && ((mine[m] >> lane) & 1)) head[base + __popcll(mine[m] & ((1ull << lane) - 1))] = (uint16_t)((m << 8) + tid);
   }
   __syncthreads();
   sq = 0;
-  for (int r = tid; r < total; r += 256) {
+  for (int r = tid; r < total; r += blockDim.x) {
     const int p = head[r], q = r + 1 < total ? head[r + 1] : T, c = q - p;
     pairs[r] = ((key[p] >> 10) & ((1u << (21 - wg_shift)) - 1)) << EMB_PAIR_SHIFT | (uint32_t)c;
     sq += c * c;
   }
   // first pair of every owner: the number of pairs whose owner is smaller
   const int n_wg = 1 << wg_shift;
-  for (int w = tid; w <= n_wg; w += 256) {
+  for (int w = tid; w <= n_wg; w += blockDim.x) {
     int lo = 0, hi = total;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
@@ -75,7 +75,8 @@ __device__ __forceinline__ void emb_write_pairs(const uint32_t *key, uint16_t *h
     start[w] = (uint16_t)lo;
   }
   __syncthreads();
-  for (int w = tid; w < n_wg; w += 256) off[w * off_ld] = (uint32_t)start[w] | (uint32_t)start[w + 1] << 16;
+  for (int w = tid; w < n_wg; w += blockDim.x) off[w * off_ld] = (uint32_t)start[w] | (uint32_t)start[w + 1] << 16;
+  return total;
 }
 
 // ---------------------------------------------------------------- embedding, mean over the steps, dense classifier
@@ -214,7 +215,7 @@ __global__ __launch_bounds__(256) void bag_net_kernel(const BagArgs a) {
   for (int m = 0; m < KPT; ++m) key[(m << 8) + tid] = kr[m];
   __syncthreads();
   int sq;
-  emb_write_pairs<KPT>(key, head, start, wsum, T, tid, a.wg_shift, a.pairs + (long)b * T, a.off + b, a.off_ld, sq);
+  (void)emb_write_pairs<KPT>(key, head, start, wsum, T, tid, a.wg_shift, a.pairs + (long)b * T, a.off + b, a.off_ld, sq);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
   if (lane == 0) cred[wave] = sq;
@@ -237,6 +238,90 @@ __global__ __launch_bounds__(256) void bag_net_kernel(const BagArgs a) {
   if (tid < 16) a.sdelta[(long)b * 16 + tid] = s * delta[tid];
 }
 
+// ---------------------------------------------------------------- embedding below other layers (the LSTM)
+//
+// Per example: the steps' gradients dx[b, t, :] summed over the steps of each distinct token into rows[b * T + pair], the
+// pairs, and the squared norm of those rows (slot[b], null: not wanted).  Two workgroups of 512 threads share a CU; a group of 32
+// lanes walks through every sixteenth token with eight steps' loads in flight (the most frequent token of an example
+// has some tens of steps, most have one or two).  Bound by HBM: B T D floats read, about half of them written.
+struct EmbRowsArgs {
+  const int *tok; const float *dx; // [B][T], [B][T][D]
+  float *rows, *slot;
+  uint32_t *pairs, *off; long off_ld;
+  int T, D, wg_shift;
+};
+#define EMB_ROWS_THREADS 512
+
+template <int KPT, bool VEC>
+__global__ __launch_bounds__(EMB_ROWS_THREADS) void emb_rows_kernel(const EmbRowsArgs a) {
+  constexpr int W_ = VEC ? 4 : 1;
+  __shared__ uint32_t key[KPT * 256];
+  __shared__ uint16_t head[KPT * 256], start[EMB_WG_MAX + 1];
+  __shared__ int wsum[KPT * 4];
+  __shared__ float red[EMB_ROWS_THREADS / 64];
+  const int b = blockIdx.x, tid = threadIdx.x, T = a.T, D = a.D;
+  const int *tok = a.tok + (long)b * T;
+  uint32_t kr[KPT];
+#pragma unroll
+  for (int m = 0; m < KPT; ++m) {
+    const int i = (m << 8) + (tid & 255);
+    kr[m] = i < T ? emb_pair_key((uint32_t)tok[i], i, a.wg_shift) : 0xFFFFFFFFu;
+  }
+  // (both halves of the workgroup sort the same keys; the barriers inside count every thread)
+  emb_sort_keys<KPT>(kr, key, tid & 255);
+#pragma unroll
+  for (int m = 0; m < KPT; ++m) key[(m << 8) + (tid & 255)] = kr[m];
+  __syncthreads();
+  int sq;
+  const int total = emb_write_pairs<KPT>(key, head, start, wsum, T, tid, a.wg_shift, a.pairs + (long)b * T, a.off + b, a.off_ld, sq);
+  const int sub = tid & 31, grp = tid >> 5;
+  const float *dx = a.dx + (long)b * T * D;
+  float *rows = a.rows + (long)b * T * D;
+  float n2 = 0.f;
+  for (int u = grp; u < total; u += EMB_ROWS_THREADS / 32) {
+    const int p0 = head[u], p1 = u + 1 < total ? head[u + 1] : T;
+    for (int e0 = 0; e0 < D; e0 += 32 * W_) {
+      const int e = e0 + sub * W_;
+      const bool on = e < D;
+      float acc[W_] = {};
+      for (int p = p0; p < p1; p += 8) {
+        float v[8][W_];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float *r = dx + (long)(key[min(p + j, p1 - 1)] & 1023u) * D + (on ? e : 0);
+          if constexpr (VEC) {
+            const float4 q = *reinterpret_cast<const float4 *>(r);
+            v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
+          } else {
+            v[j][0] = *r;
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+          for (int w = 0; w < W_; ++w) acc[w] += p + j < p1 ? v[j][w] : 0.f;
+      }
+      if (on) {
+        if constexpr (VEC) *reinterpret_cast<float4 *>(rows + (long)u * D + e) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        else rows[(long)u * D + e] = acc[0];
+#pragma unroll
+        for (int w = 0; w < W_; ++w) n2 = fmaf(acc[w], acc[w], n2);
+      }
+    }
+  }
+  if (a.slot == nullptr) return;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o, 64);
+  if ((tid & 63) == 0) red[tid >> 6] = n2;
+  __syncthreads();
+  if (tid == 0) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < EMB_ROWS_THREADS / 64; ++w) t += red[w];
+    a.slot[b] = t;
+  }
+}
+
 // ---------------------------------------------------------------- the batch sum over the pairs
 
 #define EMB_ACC_THREADS 1024
@@ -251,10 +336,17 @@ struct EmbAccumArgs {
   float *out;                // [V][D], every row written
   int B, T, D, V, wg_shift;  // 1 << wg_shift workgroups share the tokens
   int lpm;                   // lanes per pair, a power of two
-  // one more workgroup: sum_b mean[b] (x) sdelta[b] and sum_b sdelta[b] of the classifier (N = 0: none)
-  const float *mean, *sdelta; float *out_w; int N;
+  // one more workgroup: sum_b in[b] (x) s delta[b] and sum_b s delta[b] of a classifier of N classes: its input rows
+  // [B][Dc], its loss gradient in rows of 16, and the factors that are not in it yet (null: it carries them)
+  const float *mean, *sdelta, *dscale; float *out_w; int N, Dc;
 };
 
+static inline int emb_accum_lanes(int D) { // lanes per pair
+  const int n = (D & 3) == 0 ? D / 4 : D;
+  int l = 1;
+  while (l < 64 && l < n) l <<= 1;
+  return l;
+}
 static inline size_t emb_accum_lds_bytes(long V, int D, int s) {
   const size_t rows = (size_t)((V + (1l << s) - 1) >> s);
   const size_t bytes = 4 * (rows * D + 3 * rows + 2);
@@ -272,7 +364,9 @@ static inline int emb_accum_wg_shift(long V, int D) {
 // in registers.  Only the few tokens with more than one chunk meet in an LDS float atomic: with one such atomic per pair
 // and coordinate, which is the obvious way, the kernel spent 15 of its 18 us on them.  The order of a token's pairs
 // depends on the order in which the integer atomics retire.
-template <bool PER_PAIR>
+// VEC: D is a multiple of 4 and a lane holds four coordinates (at D = 100 half as many lanes per row, all of a chunk's
+// rows in flight: 66 -> 25 us on the LSTM network at 512 examples).
+template <bool PER_PAIR, bool VEC>
 __global__ __launch_bounds__(EMB_ACC_THREADS) void emb_accum_kernel(const EmbAccumArgs a) {
   extern __shared__ float acc[];
   __shared__ uint2 list[EMB_ACC_CAP];
@@ -281,7 +375,7 @@ __global__ __launch_bounds__(EMB_ACC_THREADS) void emb_accum_kernel(const EmbAcc
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n_wg = 1 << a.wg_shift, wg = blockIdx.x, D = a.D, T = a.T;
   if (wg == n_wg) { // the classifier's sums: thread (output o, group of examples g)
-    const int n_out = (D + 1) * a.N;
+    const int Dc = a.Dc, n_out = (Dc + 1) * a.N;
     for (int o0 = 0; o0 < n_out; o0 += EMB_ACC_THREADS) {
       const int ch = min(EMB_ACC_THREADS, n_out - o0), G = EMB_ACC_THREADS / ch;
       const int o = o0 + tid % ch, g = tid / ch, e = o / a.N, n = o - e * a.N;
@@ -291,11 +385,12 @@ __global__ __launch_bounds__(EMB_ACC_THREADS) void emb_accum_kernel(const EmbAcc
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
           const long bb = min(b + u * G, a.B - 1);
-          m[u] = a.mean[bb * D + min(e, D - 1)];
+          m[u] = a.mean[bb * Dc + min(e, Dc - 1)];
           d[u] = a.sdelta[bb * 16 + n];
+          if (a.dscale != nullptr) d[u] *= a.dscale[bb];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v += b + u * G < a.B ? (e < D ? m[u] * d[u] : d[u]) : 0.f;
+        for (int u = 0; u < 8; ++u) v += b + u * G < a.B ? (e < Dc ? m[u] * d[u] : d[u]) : 0.f;
       }
       acc[tid] = v;
       __syncthreads();
@@ -381,23 +476,36 @@ __global__ __launch_bounds__(EMB_ACC_THREADS) void emb_accum_kernel(const EmbAcc
         if (item0[mid] <= it) lo = mid; else hi = mid;
       }
       const int p0 = first[lo] + (it - item0[lo]) * EMB_ACC_CHUNK, np = min(EMB_ACC_CHUNK, first[lo] + cnt[lo] - p0);
-      for (int e0 = 0; e0 < D; e0 += lpm) {
-        const int e = e0 + sub, ec = min(e, D - 1);
-        float sum = 0.f;
-        for (int j0 = 0; j0 < np; j0 += 8) { // eight rows in flight
-          float v[8], f[8];
+      constexpr int W_ = VEC ? 4 : 1, IN_FLIGHT = VEC ? EMB_ACC_CHUNK : EMB_ACC_CHUNK / 2;
+      for (int e0 = 0; e0 < D; e0 += lpm * W_) {
+        const int e = e0 + sub * W_, ec = e < D ? e : 0;
+        float sum[W_] = {};
+        for (int j0 = 0; j0 < np; j0 += IN_FLIGHT) {
+          float v[IN_FLIGHT][W_], f[IN_FLIGHT];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
+          for (int j = 0; j < IN_FLIGHT; ++j) {
             const uint2 en = list[order[p0 + min(j0 + j, np - 1)]];
             f[j] = PER_PAIR ? a.scale[en.y] : (float)(en.x & EMB_PAIR_COUNT);
-            v[j] = a.rows[(PER_PAIR ? (long)en.y * T + (en.x & EMB_PAIR_COUNT) : (long)en.y) * D + ec];
+            const float *r = a.rows + (PER_PAIR ? (long)en.y * T + (en.x & EMB_PAIR_COUNT) : (long)en.y) * D + ec;
+            if constexpr (VEC) {
+              const float4 q = *reinterpret_cast<const float4 *>(r);
+              v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
+            } else {
+              v[j][0] = *r;
+            }
           }
 #pragma unroll
-          for (int j = 0; j < 8; ++j) sum += j0 + j < np ? f[j] * v[j] : 0.f;
+          for (int j = 0; j < IN_FLIGHT; ++j)
+#pragma unroll
+            for (int w = 0; w < W_; ++w) sum[w] += j0 + j < np ? f[j] * v[j][w] : 0.f;
         }
         if (e < D) {
-          if (cnt[lo] <= EMB_ACC_CHUNK) acc[lo * D + e] += sum;
-          else unsafeAtomicAdd(&acc[lo * D + e], sum);
+          const bool whole = cnt[lo] <= EMB_ACC_CHUNK;
+#pragma unroll
+          for (int w = 0; w < W_; ++w) {
+            if (whole) acc[lo * D + e + w] += sum[w];
+            else unsafeAtomicAdd(&acc[lo * D + e + w], sum[w]);
+          }
         }
       }
     }

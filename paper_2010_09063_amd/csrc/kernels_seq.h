@@ -70,6 +70,55 @@ __global__ __launch_bounds__(256) void seq_mean_fwd_kernel(const float *__restri
   }
 }
 
+// The classifier of a sequence network (a dense layer of at most 16 classes on a vector per example): logits, loss
+// gradient (rows of 16, zero beyond the classes), the layer's squared norm (slot, null: not wanted) and the gradient of
+// its input, one wave per example.  Lane (class n = lane / 4, quarter of the input) for the logits.  Split-K
+// contraction, loss kernel and backward contraction were three launches of 11 + 5 + 6 us at 128 examples.
+__global__ __launch_bounds__(256) void class_head_kernel(const float *__restrict__ in, const float *__restrict__ W,
+                                                         const float *__restrict__ bias, const int *__restrict__ y,
+                                                         float *__restrict__ delta, float *__restrict__ gin,
+                                                         float *__restrict__ slot, int B, int D, int N) {
+  const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (b >= B) return;
+  const float *a = in + (long)b * D;
+  const int n = lane >> 2, q = lane & 3, nc = min(n, N - 1);
+  float z = 0.f, sa = 0.f;
+  for (int e0 = 0; e0 < D; e0 += 16) { // (four input values per lane in flight)
+    float v[4], w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int e = e0 + 4 * j + q, ec = min(e, D - 1);
+      v[j] = a[ec];
+      w[j] = W[(long)ec * N + nc];
+      if (e >= D) v[j] = 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { z = fmaf(v[j], w[j], z); sa = fmaf(v[j], v[j], sa); }
+  }
+  z += __shfl_xor(z, 1, 64); z += __shfl_xor(z, 2, 64);
+  sa += __shfl_xor(sa, 1, 64); sa += __shfl_xor(sa, 2, 64);
+  z = n < N ? z + bias[nc] : -INFINITY;
+  float mx = z;
+#pragma unroll
+  for (int o = 4; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+  const float ex = n < N ? expf(z - mx) : 0.f;
+  float se = ex;
+#pragma unroll
+  for (int o = 4; o < 64; o <<= 1) se += __shfl_xor(se, o, 64);
+  const float d = n < N ? ex * (1.f / se) - (n == y[b] ? 1.f : 0.f) : 0.f;
+  float sd = d * d;
+#pragma unroll
+  for (int o = 4; o < 64; o <<= 1) sd += __shfl_xor(sd, o, 64);
+  if (q == 0) delta[(long)b * 16 + n] = d;
+  if (slot != nullptr && lane == 0) slot[b] = (sa + 1.f) * sd;
+  for (int e0 = 0; e0 < D; e0 += 64) {
+    const int e = e0 + lane;
+    float g = 0.f;
+    for (int m = 0; m < N; ++m) g = fmaf(W[(long)min(e, D - 1) * N + m], __shfl(d, 4 * m, 64), g);
+    if (e < D) gin[(long)b * D + e] = g;
+  }
+}
+
 // ... and its gradient: every step receives g[b, e] / T.  One thread per (b, t, e).
 __global__ void seq_mean_bwd_kernel(const float *__restrict__ g, float *__restrict__ gin, long n, int T, int D) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -102,7 +151,9 @@ __device__ __forceinline__ float quad_bcast(float v) { // every lane of the quad
 }
 
 // Forward.  gates: in  x_t W_ih + b for every (b, t); out activated i, f, g, o.
-// hs, cs: [B, T, H] hidden and cell states; hlast [B, H] = h_T (null: not wanted).  H <= 128, HP >= H.
+// hs, cs: [B, T, H] hidden and cell states; hlast [B, H] = h_T, or the mean of every h_t (mean != 0: the sequence mean
+// that follows the layer in the Appendix B network costs one addition a step here and was a launch of 33 us at 128
+// examples).  H <= 128, HP >= H.
 // Thread (u = tid / 4, q = tid % 4) belongs to hidden unit u and holds, for all four gates
 // of that unit, the quarter q of the rows of W_hh (k in [q*QL, q*QL + QL)).  A step is then: quarter product (QL
 // broadcast words of h from LDS instead of all H), sum over the quad with two DPP exchanges per gate, lane q
@@ -113,7 +164,7 @@ __device__ __forceinline__ float quad_bcast(float v) { // every lane of the quad
 template <int HP>
 __global__ __launch_bounds__(LSTM_THREADS) void lstm_fwd_kernel(float *__restrict__ gates, const float *__restrict__ Whh,
                                                                       float *__restrict__ hs, float *__restrict__ cs,
-                                                                      float *__restrict__ hlast, int B, int T, int H) {
+                                                                      float *__restrict__ hlast, int mean, int B, int T, int H) {
   constexpr int QL = (HP + 3) / 4;        // rows of W_hh per quarter
   constexpr int QLP = (QL + 3) & ~3;      // the quarter's stride in LDS (16-byte aligned)
   __shared__ __attribute__((aligned(16))) float h_s[2][4 * QLP];
@@ -132,7 +183,7 @@ __global__ __launch_bounds__(LSTM_THREADS) void lstm_fwd_kernel(float *__restric
       w[g][i] = (unit_ok && k < H) ? Whh[(long)k * G + g * H + ul] : 0.f;
     }
   for (int i = tid; i < 2 * 4 * QLP; i += LSTM_THREADS) (&h_s[0][0])[i] = 0.f;
-  float c_reg = 0.f;
+  float c_reg = 0.f, h_sum = 0.f;
   const unsigned colb = 4u * (q * H + ul), ub = 4u * ul;
   const int hpos = (ul / QL) * QLP + ul % QL; // where unit u's h sits in a buffer
   float *const grow0 = gates + (long)b * T * G;
@@ -177,7 +228,8 @@ __global__ __launch_bounds__(LSTM_THREADS) void lstm_fwd_kernel(float *__restric
       hout[hpos] = h;
       lane_at(hrow0 + (long)t * H, ux) = h;
       lane_at(crow0 + (long)t * H, ux) = c_reg;
-      if (hlast != nullptr && t == T - 1) lane_at(hlast + (long)b * H, ux) = h;
+      h_sum += h;
+      if (t == T - 1) lane_at(hlast + (long)b * H, ux) = mean ? h_sum / (float)T : h;
     }
     __syncthreads();
   };
@@ -193,8 +245,8 @@ __global__ __launch_bounds__(LSTM_THREADS) void lstm_fwd_kernel(float *__restric
 // Back-propagation through time.  gates: in activated gates, out d(loss)/d(gate pre-activations).
 // One workgroup per example; thread (k = tid % 128, q = tid / 128) owns W_hh[k][qH .. qH + H), the columns of
 // gate q, and computes that gate's share of dL/dh_{t-1}[k].
-// SEQ = false: the loss sees h_T only, dh_out is [B, H].  SEQ = true: the layer's output is every h_t,
-// dh_out is [B, T, H] and step t adds its own share to what the later steps send back.
+// dh_out is [B, H].  SEQ = false: the gradient of h_T, which is all that the loss sees.  SEQ = true: the gradient of the
+// mean over every h_t: each step adds its share dh_out / T to what the later steps send back.
 template <int HP, bool SEQ>
 __global__ __launch_bounds__(LSTM_THREADS, (HP <= 100 ? 4 : 2)) void lstm_bwd_kernel(float *__restrict__ gates, const float *__restrict__ cs,
                                                                  const float *__restrict__ Whh,
@@ -215,7 +267,7 @@ __global__ __launch_bounds__(LSTM_THREADS, (HP <= 100 ? 4 : 2)) void lstm_bwd_ke
   const unsigned urb = 4u * ur;
   float *const grow0 = gates + (long)b * T * G;
   const float *const crow0 = cs + (long)b * T * H;
-  const float *const drow0 = SEQ ? dh_out + (long)b * T * H : dh_out + (long)b * H;
+  const float *const drow0 = dh_out + (long)b * H;
   // Operands of the step being processed, held by the cell-update threads only.  They are declared without a
   // value and loaded and used inside the same branch: an initial value, a load under one branch used under
   // another, or a loaded value copied into a second variable would each be waited for at once, not at the use.
@@ -226,7 +278,8 @@ __global__ __launch_bounds__(LSTM_THREADS, (HP <= 100 ? 4 : 2)) void lstm_bwd_ke
     gi = lane_ld(g, urb); gf = lane_ld(g + H, urb); gg = lane_ld(g + 2 * H, urb); go = lane_ld(g + 3 * H, urb);
     ct = lane_ld(crow0 + (long)(T - 1) * H, urb);
     cp = lane_ld(crow0 + (long)max(T - 2, 0) * H, urb); // c_{t-1}; unused at t = 0
-    dh_own = SEQ ? lane_ld(drow0 + (long)(T - 1) * H, urb) : lane_ld(drow0, urb);
+    dh_own = lane_ld(drow0, urb);
+    if (SEQ) dh_own /= (float)T;
   }
   __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the weight loads end here, not at their first use inside the loop
   __syncthreads();
@@ -256,7 +309,6 @@ __global__ __launch_bounds__(LSTM_THREADS, (HP <= 100 ? 4 : 2)) void lstm_bwd_ke
       gi = lane_ld(gn, urx); gf = lane_ld(gn + H, urx); gg = lane_ld(gn + 2 * H, urx); go = lane_ld(gn + 3 * H, urx);
       ct = lane_ld(crow0 + (long)tn * H, urx); // (loaded again rather than copied from cp: see above)
       cp = lane_ld(crow0 + (long)max(tn - 1, 0) * H, urx);
-      if (SEQ) dh_own = lane_ld(drow0 + (long)tn * H, urx);
     }
     __syncthreads();
     if (t > 0) {
