@@ -527,7 +527,7 @@ static inline int launch_dense2_mid(hipStream_t st, Dense2Args a, int max_tiles)
 // LDS operations of one wave complete in order, so one area per wave needs no double buffer.
 struct SmallGemmArgs {
   const float *A; long a_sr, a_sk; // element (m, k) = A[m * a_sr + k * a_sk]; one of the two strides is 1
-  const float *B; long b_sr, b_sk; // element (n, k) = B[n * b_sr + k * b_sk]; one of the two strides is 1
+  const float *B; long b_sr, b_sk; // element (n, k) = B[n * b_sr + k * b_sk]; b_sr = 1
   const float *bias;               // [N] or null
   float *C; long c_sm, c_sn;       // C[m * c_sm + n * c_sn]
   float *C_ones;                   // row M of the output when a_ones (the bias gradient), indexed by n
@@ -535,6 +535,8 @@ struct SmallGemmArgs {
   int a_ones;                      // 1: A has one more row, m = M, that is constant 1 (then the grid covers M + 1 rows)
   const float *k_scale;            // [K] or null: B's element (n, k) is multiplied by k_scale[k] (the clip factors of a
                                    // clipped sum whose delta is not scaled yet); B's rows must be the contiguous index
+  int final; FinalWrite fin; long j0; // final: the output is the parameter vector's coordinates from j0 on, row after row
+                                      // (c_sm = N, the row of ones last), and goes through the final write
 };
 
 typedef float sg_f32x16 __attribute__((ext_vector_type(16)));
@@ -542,7 +544,7 @@ typedef float sg_f32x16 __attribute__((ext_vector_type(16)));
 
 // What the kernel can take: one of an operand's two strides is 1.
 static inline bool dense_small_gemm_fits(const SmallGemmArgs &a) {
-  return a.K >= 1 && (a.a_sk == 1 || a.a_sr == 1) && (a.b_sk == 1 || a.b_sr == 1) && !(a.k_scale && a.b_sk == 1);
+  return a.K >= 1 && (a.a_sk == 1 || a.a_sr == 1) && a.b_sr == 1;
 }
 // 16-byte loads: base pointers, the non-unit strides and K are multiples of 4 floats; an operand whose rows are the
 // contiguous index has a row count that is one too, or rows of memory padded to the next multiple (its k stride covers
@@ -551,10 +553,10 @@ static inline bool dense_small_gemm_fits(const SmallGemmArgs &a) {
 // 104-50-10 network 15.6 + 13.6 us at 128 examples.
 static inline bool dense_small_gemm_vec(const SmallGemmArgs &a) {
   auto al = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  const bool a_kc = a.a_sk == 1, b_kc = a.b_sk == 1;
-  if (!al(a.A) || !al(a.B) || ((a_kc || b_kc) && (a.K & 3) != 0)) return false;
+  const bool a_kc = a.a_sk == 1;
+  if (!al(a.A) || !al(a.B) || (a_kc && (a.K & 3) != 0)) return false;
   if (a_kc ? (a.a_sr & 3) != 0 : ((a.a_sk & 3) != 0 || a.a_sk < ((a.M + 3) & ~3))) return false;
-  if (b_kc ? (a.b_sr & 3) != 0 : ((a.b_sk & 3) != 0 || a.b_sk < ((a.N + 3) & ~3))) return false;
+  if ((a.b_sk & 3) != 0 || a.b_sk < ((a.N + 3) & ~3)) return false;
   return true;
 }
 
@@ -611,7 +613,7 @@ __device__ __forceinline__ void sg_stash(float *T, int r0, int R, bool ones, int
 // NW waves per workgroup (the K split); LDS: NW areas of 2 x 32 x 33 floats, passed as dynamic shared memory
 // A launch may carry a second product of the same operand layouts (the two clipped sums of a two-layer network):
 // rows ny0 and up of the grid are its tiles.
-template <bool A_KC, bool B_KC, bool VEC, int NW>
+template <bool A_KC, bool VEC, int NW>
 __global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGemmArgs p0, const SmallGemmArgs p1, int ny0) {
   extern __shared__ float sg_lds[]; // per wave: A slice [k][m], B slice [k][n]; after the K loop: the wave's partial tile
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lk = lane >> 5;
@@ -641,13 +643,13 @@ __global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGe
   float4 va[4], vb[4];
   float sb[4] = {1.f, 1.f, 1.f, 1.f}; // k_scale of vb's four items (an item of a row-contiguous operand has one k)
   auto fetch_scale = [&](int k0) {
-    if (!B_KC && a.k_scale) {
+    if (a.k_scale) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) sb[q] = a.k_scale[min(k0 + ((lane + 64 * q) >> 3), a.K - 1)];
     }
   };
   auto apply_scale = [&]() {
-    if (!B_KC && a.k_scale) {
+    if (a.k_scale) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) { vb[q].x *= sb[q]; vb[q].y *= sb[q]; vb[q].z *= sb[q]; vb[q].w *= sb[q]; }
     }
@@ -655,17 +657,17 @@ __global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGe
   int sl = wave;
   if (sl < n_slices) {
     sg_fetch<A_KC, VEC>(a.A, a.a_sr, a.a_sk, m0, a.M, a.K, 32 * sl, lane, va);
-    sg_fetch<B_KC, VEC>(a.B, a.b_sr, a.b_sk, n0, a.N, a.K, 32 * sl, lane, vb);
+    sg_fetch<false, VEC>(a.B, a.b_sr, a.b_sk, n0, a.N, a.K, 32 * sl, lane, vb);
     fetch_scale(32 * sl);
   }
   for (; sl < n_slices; sl += NW) {
     apply_scale();
     sg_stash<A_KC, VEC>(As, m0, a.M, a.a_ones != 0, a.K, 32 * sl, lane, va);
-    sg_stash<B_KC, VEC>(Bs, n0, a.N, false, a.K, 32 * sl, lane, vb);
+    sg_stash<false, VEC>(Bs, n0, a.N, false, a.K, 32 * sl, lane, vb);
     __builtin_amdgcn_wave_barrier(); // (the slice is read by other lanes of this wave: LDS operations of a wave complete in order)
     const int nx = min(sl + NW, n_slices - 1); // (past the wave's last slice: one is read again, unused)
     sg_fetch<A_KC, VEC>(a.A, a.a_sr, a.a_sk, m0, a.M, a.K, 32 * nx, lane, va);
-    sg_fetch<B_KC, VEC>(a.B, a.b_sr, a.b_sk, n0, a.N, a.K, 32 * nx, lane, vb);
+    sg_fetch<false, VEC>(a.B, a.b_sr, a.b_sk, n0, a.N, a.K, 32 * nx, lane, vb);
     fetch_scale(32 * nx);
 #pragma unroll
     for (int s2 = 0; s2 < 16; ++s2)
@@ -693,7 +695,8 @@ __global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGe
       float r = v[0];
       if (a.bias) r += a.bias[n];
       r = act_apply(a.act, r);
-      if (m < a.M) a.C[(long)m * a.c_sm + (long)n * a.c_sn] = r;
+      if (a.final) final_write(a.fin, a.j0 + (long)m * a.N + n, r);
+      else if (m < a.M) a.C[(long)m * a.c_sm + (long)n * a.c_sn] = r;
       else a.C_ones[n] = r;
     }
   }
@@ -706,9 +709,8 @@ static inline bool dense_small_gemm_prepare() {
   const int bytes = (int)dense_small_gemm_lds_bytes();
   const hipFuncAttribute at = hipFuncAttributeMaxDynamicSharedMemorySize;
   bool ok = true;
-#define DP_SG_ATTR(a_, b_, v_) ok = ok && hipFuncSetAttribute((const void *)dense_small_gemm_kernel<a_, b_, v_, SG_WAVES>, at, bytes) == hipSuccess;
-  DP_SG_ATTR(true, true, true) DP_SG_ATTR(true, false, true) DP_SG_ATTR(false, true, true) DP_SG_ATTR(false, false, true)
-  DP_SG_ATTR(true, true, false) DP_SG_ATTR(true, false, false) DP_SG_ATTR(false, true, false) DP_SG_ATTR(false, false, false)
+#define DP_SG_ATTR(a_, v_) ok = ok && hipFuncSetAttribute((const void *)dense_small_gemm_kernel<a_, v_, SG_WAVES>, at, bytes) == hipSuccess;
+  DP_SG_ATTR(true, true) DP_SG_ATTR(false, true) DP_SG_ATTR(true, false) DP_SG_ATTR(false, false)
 #undef DP_SG_ATTR
   return ok;
 }
@@ -719,13 +721,11 @@ static inline void launch_dense_small_gemm(hipStream_t st, const SmallGemmArgs &
   const int ny0 = (a.N + 31) / 32, ny1 = b ? (b->N + 31) / 32 : 0;
   dim3 grid((std::max(Mtot, Mtot2) + 31) / 32, ny0 + ny1), block(64 * SG_WAVES);
   const size_t lds = dense_small_gemm_lds_bytes();
-  const bool a_kc = a.a_sk == 1, b_kc = a.b_sk == 1;
+  const bool a_kc = a.a_sk == 1;
   const SmallGemmArgs &a2 = b ? *b : a;
   const bool vec = dense_small_gemm_vec(a) && (!b || dense_small_gemm_vec(*b));
-#define DP_SG_CASE(a_, b_, v_)                                                                                          \
-  if (a_kc == a_ && b_kc == b_ && vec == v_)                                                                            \
-    hipLaunchKernelGGL((dense_small_gemm_kernel<a_, b_, v_, SG_WAVES>), grid, block, lds, st, a, a2, ny0);
-  DP_SG_CASE(true, true, true) DP_SG_CASE(true, false, true) DP_SG_CASE(false, true, true) DP_SG_CASE(false, false, true)
-  DP_SG_CASE(true, true, false) DP_SG_CASE(true, false, false) DP_SG_CASE(false, true, false) DP_SG_CASE(false, false, false)
+#define DP_SG_CASE(a_, v_)                                                                                              \
+  if (a_kc == a_ && vec == v_) hipLaunchKernelGGL((dense_small_gemm_kernel<a_, v_, SG_WAVES>), grid, block, lds, st, a, a2, ny0);
+  DP_SG_CASE(true, true) DP_SG_CASE(false, true) DP_SG_CASE(true, false) DP_SG_CASE(false, false)
 #undef DP_SG_CASE
 }

@@ -29,6 +29,9 @@
 #include "operands.h"
 #include "problems.h"
 #include "rows_gemm.h"
+#include "split_conv.h"
+#include "split_rows.h"
+#include "split_wgrad.h"
 
 static thread_local char g_hip_err[256] = "";
 
@@ -72,6 +75,10 @@ struct Layer {
   // forward / backward-data by the F(2x2, 3x3) minimal-filtering kernel: output-channel blocks per workgroup (0: not
   // used), transformed weights [16][cpad][mpad]
   int wino_f = 0, wino_b = 0;
+  bool split_f = false, split_b = false; // forward / backward-data in direct form on the bf16 matrix units, three pieces per operand
+  void *frag_f = nullptr, *frag_b = nullptr;
+  bool split_wg = false;   // weight gradient on the bf16 matrix units: batch sums, where no other family's apply
+  bool split_norm = false; // ... and the norm pass
   bool wino_wg = false; // batch sum of the weight gradient in the F(3x3, 2x2) form on 8x8 planes (any multiple of 64 output channels)
   bool u_f_planned = false; // pad-1 3x3 stride-1 layer with even planes: the minimal-filtering family applies
   bool wino_wgu = false;    // per-example and batch weight gradient in that form on 16- and 32-wide planes (32 / 64 output channels)
@@ -84,6 +91,7 @@ struct Layer {
   // lstm
   bool lstm_wg = false; // per-example weight gradient by lstm_wgrad_kernel (16x16 MFMA blocks, one example per two workgroups)
   float *gates = nullptr, *cs = nullptr, *hs = nullptr;
+  void *frag_dx = nullptr; // split W_ih^T of the input gradient
   int T = 0, Din = 0, H = 0;
 };
 
@@ -98,7 +106,7 @@ static const char *layer_label(Layer &l, int li, const char *name) {
 }
 static const char *const kLayerLabels[] = {"dense_fwd", "dense_fwd_epilogue", "dense_norm", "dense_bwd_data", "dense_clipped_sum",
                                            "conv_weight_layout", "conv_fwd", "conv_wgrad_norm", "conv_bwd_data", "conv_clipped_sum",
-                                           "maxpool_fwd", "maxpool_bwd", "lstm_xproj", "lstm_fwd", "lstm_bwd", "lstm_wgrad_norm",
+                                           "maxpool_fwd", "maxpool_bwd", "lstm_weights", "lstm_xproj", "lstm_fwd", "lstm_bwd", "lstm_wgrad_norm",
                                            "lstm_dx", "lstm_clipped_sum", "emb_norm", "emb_gather", "emb_bucket", "emb_scatter", "fill_zero",
                                            "seq_mean_fwd", "seq_mean_bwd", "avgpool_fwd", "avgpool_bwd", "conv_weighted_sum", "lstm_weighted_sum"};
 
@@ -122,7 +130,9 @@ struct dp_ctx {
   bool joint2 = false; // fused2 / head2 and both clipped sums in one dense_small_gemm_kernel launch
   // embedding, mean over the steps, dense classifier: everything per example in bag_net_kernel, the batch sums over
   // (token, example) pairs in emb_accum_kernel
-  bool bag = false; int bag_shift = 0;
+  bool bag = false; int emb_shift = 0;
+  bool emb_pairs = false; float *pair_rows = nullptr; // an embedding below other layers: its norm and clipped sum over pairs as well
+  bool class_head = false; // a sequence network's classifier (at most 16 classes) in class_head_kernel
   float *bag_mean = nullptr, *bag_sdelta = nullptr, *bag_rows = nullptr; uint32_t *pairs = nullptr; uint32_t *pair_off = nullptr;
   bool fused2 = false; // two dense layers: everything between the hidden layer's forward product and the clipped sums in dense2_mid_kernel
   // The embedding layer's counting sort of the batch's tokens depends on the inputs alone: it runs on a stream of the
@@ -278,6 +288,28 @@ static void plan_direct_conv(Layer &l, int maxB, const dp_plan_options &opt) {
     l.wino_f = pick(g.C, g.D);
     l.wino_b = pick(g.D, g.C);
   }
+  // The direct form on the bf16 matrix units, for pad-1 planes of the widths the kernel is built for and at least a whole
+  // chunk of sixteen input channels: where the minimal-filtering form does not apply, or would run with 32 output
+  // channels per workgroup because the launch is small (48 to 192 channels at 61 examples: 31 -> 28 us on 32-wide planes,
+  // 30 -> 25 on 16-wide, 37 -> 23 on 8-wide; 128 -> 256 and 256 -> 10 channels on 4x4 planes at 256: 50 -> 23, 67 -> 23).  With
+  // 64 channels per workgroup, or the weights resident, that form does 16 of 36 multiplies and stays ahead (64 -> 64 on
+  // 16x16 at 1024: 100 against 108 us; 32 -> 32 on 32x32: 106 against 150).  The options that name the other families
+  // keep them.
+  if (l.dir_fwd && l.dir_bwd && g.PAD == 1 && g.H == g.OH && g.W == g.OW && split_conv_fits(g.H, g.W) &&
+      !opt.no_minimal_filtering && !opt.minimal_filtering_all) {
+    auto resident = [&](int Cin, int M) {
+      return Cin == 32 && M <= 64 && ((g.W == 32 && g.H % 4 == 0) || (g.W == 16 && g.H % 8 == 0)) && !opt.no_resident_weights;
+    };
+    l.split_f = g.C >= 16 && (l.wino_f == 0 || (l.wino_f == 1 && !resident(g.C, g.D)));
+    l.split_b = g.D >= 16 && (l.wino_b == 0 || (l.wino_b == 1 && !resident(g.D, g.C)));
+    if (l.split_f) l.wino_f = 0;
+    if (l.split_b) l.wino_b = 0;
+  }
+  // Weight gradients on the bf16 matrix units, for the planes that kernel is built for: everything that the
+  // minimal-filtering and Gram routes leave (channel counts that are no multiples of their blocks, more than 64 output
+  // channels on wide planes, batch sums on 4x4 planes) except the flattened first layer.
+  l.split_wg = g.PAD == 1 && g.H == g.OH && g.W == g.OW && split_wgrad_fits(g.H, g.W) && !opt.no_minimal_filtering &&
+               !opt.minimal_filtering_all && !opt.no_minimal_filtering_wgrad && !opt.no_specialised_waves && !opt.specialised_waves_all;
   // per-example norm from Gram matrices: P^2 (9C + D) multiply-adds instead of 9 C D P, for the two plane sizes
   // the kernel is built for (pad 1, so the input plane equals the output plane)
   if (g.PAD == 1 && g.H == g.OH && g.W == g.OW && ((g.OH == 8 && g.OW == 8) || (g.OH == 4 && g.OW == 4)) &&
@@ -285,6 +317,8 @@ static void plan_direct_conv(Layer &l, int maxB, const dp_plan_options &opt) {
     l.gram = true;
   // weight gradient
   const bool flat = g.C * 9 <= 32 && g.D <= 32;
+  if (flat) l.split_wg = false;
+  l.split_norm = l.split_wg && !l.gram && !l.wino_wgu;
   if ((g.C >= 16 || flat) && (g.OW & 3) == 0 && (g.W & 3) == 0) {
     int db = g.D <= 32 ? 1 : (g.D <= 64 ? 2 : 4);
     int pch_max = flat ? 256 : (db <= 2 ? 128 : 64);
@@ -635,18 +669,24 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
   }
   // The embedding network in two launches.  A table too large for the LDS of its workgroups keeps the sorted lists, and
   // so does a context whose options name those lists' launches.
-  c->bag = c->L.size() == 3 && c->L[0].d.kind == DP_EMBEDDING && c->L[1].d.kind == DP_SEQ_MEAN && c->L[2].d.kind == DP_DENSE &&
-           c->L[0].d.embed_dim <= BAG_DMAX && c->L[2].d.out_features <= 16 &&
-           emb_accum_wg_shift(c->L[0].d.vocab, c->L[0].d.embed_dim) >= 0 && !c->opt.no_fused_dense &&
-           !c->opt.no_single_bucket && !c->opt.no_side_stream;
-  if (c->bag) c->bag_shift = emb_accum_wg_shift(c->L[0].d.vocab, c->L[0].d.embed_dim);
+  c->emb_pairs = c->L[0].d.kind == DP_EMBEDDING && !c->opt.no_single_bucket && !c->opt.no_side_stream;
+  if (c->emb_pairs) {
+    c->emb_shift = emb_accum_wg_shift(c->L[0].d.vocab, c->L[0].d.embed_dim);
+    c->emb_pairs = c->emb_shift >= 0;
+  }
+  {
+    const size_t n = c->L.size();
+    c->class_head = c->emb_pairs && n >= 3 && c->L[n - 1].d.kind == DP_DENSE && c->L[n - 1].d.out_features <= 16 &&
+                    (c->L[n - 2].d.kind == DP_LSTM_LAST || c->L[n - 2].d.kind == DP_SEQ_MEAN) && !c->opt.no_fused_dense;
+    c->bag = c->class_head && n == 3 && c->L[1].d.kind == DP_SEQ_MEAN && c->L[0].d.embed_dim <= BAG_DMAX;
+  }
   // both clipped sums of a two-layer network, or of the two dense layers that close a deeper one, in one launch of that kernel
   c->joint2 = c->fused2 && !c->opt.no_small_gemm;
   if (c->head2 && !c->opt.no_small_gemm) { // (a deeper network's last layers: widths in whole groups of four floats)
     const dp_layer_desc &h = c->L[c->L.size() - 2].d;
     c->joint2 = h.in_features % 4 == 0 && h.out_features % 4 == 0;
   }
-  if (rc == DP_OK && !c->L.empty() && c->L[0].d.kind == DP_EMBEDDING && !c->bag && !c->opt.no_side_stream) {
+  if (rc == DP_OK && !c->L.empty() && c->L[0].d.kind == DP_EMBEDDING && !c->emb_pairs && !c->opt.no_side_stream) {
     if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) != hipSuccess) {
@@ -674,7 +714,7 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
         l.max_split = (int)(ms < 8 ? 8 : (ms > DP_MAX_SPLIT ? DP_MAX_SPLIT : ms));
       }
       l.pstride = (l.p_count + 3) & ~3l;
-      rc = dev_alloc(c, &l.part, (size_t)l.max_split * l.pstride);
+      if (!c->bag) rc = dev_alloc(c, &l.part, (size_t)l.max_split * l.pstride);
     }
     if (rc == DP_OK && l.d.kind == DP_DENSE && !c->bag) {
       // a small output with a long K would leave most CUs idle and expose every load's latency: split K
@@ -698,6 +738,8 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
       if (rc == DP_OK && (hipMemsetAsync(l.wt_f, 0, nf * sizeof(float), c->stream) != hipSuccess ||
                           hipMemsetAsync(l.wt_b, 0, nb * sizeof(float), c->stream) != hipSuccess)) rc = DP_EHIP;
     }
+    if (rc == DP_OK && l.split_f) rc = dev_alloc(c, (char **)&l.frag_f, split_conv_frag_bytes(l.geom.D, l.geom.C));
+    if (rc == DP_OK && l.split_b && &l != &c->L.front()) rc = dev_alloc(c, (char **)&l.frag_b, split_conv_frag_bytes(l.geom.C, l.geom.D));
     if (rc == DP_OK && l.wino_f) {
       l.uf_cpad = ceil_div(l.geom.C, WINO_CC) * WINO_CC; l.uf_mpad = ceil_div(l.geom.D, 32 * l.wino_f) * 32 * l.wino_f;
       const size_t n = (size_t)16 * l.uf_cpad * l.uf_mpad;
@@ -719,6 +761,13 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
     // Large planes: the norm pass writes each example's gradient (8 bytes of traffic per coordinate, written and
     // read once) and the clipped sum becomes a weighted sum of those rows; repeating the contraction instead costs
     // 2 P flops per coordinate, which is more from P = 256 pixels on.
+    if (rc == DP_OK && l.d.kind == DP_CONV2D && l.split_norm && l.geom.P >= 256 && (size_t)mb * l.p_count <= ((size_t)1 << 30) &&
+        !c->opt.no_stored_gradients) {
+      l.gorder = GradOrder{};
+      l.gorder.C = l.geom.C; l.gorder.D = l.geom.D; l.gorder.KK = 9; l.gorder.flat = 4;
+      l.gorder.n_total = l.p_count;
+      rc = dev_alloc(c, &l.gst, (size_t)mb * l.p_count);
+    } else
     if (rc == DP_OK && l.d.kind == DP_CONV2D && l.dir_wg && !l.gram && !l.wg_ws && l.geom.D <= DP_WG_DSLICE &&
         l.geom.P >= 256 && (size_t)mb * l.p_count <= ((size_t)1 << 30) && !c->opt.no_stored_gradients) {
       // the order in which conv_s1_wgrad_kernel<3, 3, wg_db, wg_flat, false> holds the gradient in its accumulators
@@ -745,7 +794,7 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
     }
     // the same route for convolutions on the generic contraction (other strides / filter sizes): its per-example
     // tile is [D][C*KK + 1], the last column being the bias gradient
-    if (rc == DP_OK && l.d.kind == DP_CONV2D && !l.dir_wg && !l.gram && l.geom.P >= 128 &&
+    if (rc == DP_OK && l.d.kind == DP_CONV2D && !l.dir_wg && !l.gram && !l.split_norm && l.geom.P >= 128 &&
         (size_t)mb * l.p_count <= ((size_t)1 << 30) && !c->opt.no_stored_gradients) {
       GradOrder &o = l.gorder;
       o = GradOrder{};
@@ -753,7 +802,7 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
       o.n_total = (long)o.D * (o.C * o.KK + 1);
       rc = dev_alloc(c, &l.gst, (size_t)mb * o.n_total);
     }
-    if (rc == DP_OK && emb && !c->bag) {
+    if (rc == DP_OK && emb && !c->emb_pairs) {
       const size_t V = l.d.vocab;
       rc = dev_alloc(c, &l.e_count, V + 1);
       if (rc == DP_OK) rc = dev_alloc(c, &l.e_start, V + 1);
@@ -762,8 +811,11 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
       if (rc == DP_OK) rc = dev_alloc(c, &l.e_list, (size_t)mb * l.outC);
     }
     if (rc == DP_OK && (l.d.kind == DP_LSTM_LAST || l.d.kind == DP_LSTM_SEQ)) {
-      rc = dev_alloc(c, &l.gates, mb * l.T * 4 * l.H);
-      if (rc == DP_OK) rc = dev_alloc(c, &l.cs, mb * l.T * l.H);
+      rc = dev_alloc(c, &l.gates, mb * l.T * 4 * l.H + SPLIT_ROWS_SLACK);
+      if (rc == DP_OK && !c->opt.no_rows_gemm) {
+        rc = dev_alloc(c, (char **)&l.frag_dx, split_rows_frag_bytes(4 * l.H, l.Din));
+      }
+      if (rc == DP_OK) rc = dev_alloc(c, &l.cs, mb * l.T * std::max(l.H, l.Din)); // (also the embedding's pair rows)
       if (l.d.kind == DP_LSTM_SEQ) l.hs = l.a; // the hidden states are the layer's output
       else if (rc == DP_OK) rc = dev_alloc(c, &l.hs, mb * l.T * l.H);
       // long sequences: the norm contraction writes each example's gradient ([Din + H + 1][4H], which is the layer's
@@ -781,13 +833,19 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
   if (rc == DP_OK) rc = dev_alloc(c, &c->s, mb);
   if (rc == DP_OK) rc = dev_alloc(c, &c->ones, mb);
   if (rc == DP_OK) rc = dev_alloc(c, &c->bad, 1);
-  if (rc == DP_OK && c->bag) {
+  if (rc == DP_OK && c->emb_pairs) {
     const size_t T = c->m.seq_len, D = c->L[0].d.embed_dim;
-    rc = dev_alloc(c, &c->bag_mean, mb * D);
-    if (rc == DP_OK) rc = dev_alloc(c, &c->bag_sdelta, mb * 16);
-    if (rc == DP_OK) rc = dev_alloc(c, &c->bag_rows, mb * D);
+    if (c->bag) {
+      rc = dev_alloc(c, &c->bag_mean, mb * D);
+      if (rc == DP_OK) rc = dev_alloc(c, &c->bag_sdelta, mb * 16);
+      if (rc == DP_OK) rc = dev_alloc(c, &c->bag_rows, mb * D);
+    } else if (c->L.size() > 1 && (c->L[1].d.kind == DP_LSTM_LAST || c->L[1].d.kind == DP_LSTM_SEQ)) {
+      c->pair_rows = c->L[1].cs; // (the cell states are done with when the rows are summed)
+    } else {
+      rc = dev_alloc(c, &c->pair_rows, mb * T * D);
+    }
     if (rc == DP_OK) rc = dev_alloc(c, &c->pairs, mb * T);
-    if (rc == DP_OK) rc = dev_alloc(c, &c->pair_off, mb << c->bag_shift);
+    if (rc == DP_OK) rc = dev_alloc(c, &c->pair_off, mb << c->emb_shift);
   }
   if (rc == DP_OK && c->fusedcnn) rc = dev_alloc(c, &c->cnn_part, (size_t)256 * ((cnnf::NPARAM + 3) & ~3));
   if (rc == DP_OK) {
@@ -833,12 +891,14 @@ extern "C" const char *dp_step_strerror(int code) {
 
 static inline dim3 grid1d(long n, int block) { return dim3((unsigned)((n + block - 1) / block)); }
 
+// (a layer that returns every hidden state is always followed by the mean over them, (&l)[1], which the recurrence kernels
+// take along)
 template <int HP>
 static void launch_lstm_fwd(const Launcher &Ln, Layer &l, const float *Whh, int B, const char *label) {
   dim3 grid(B), block(LSTM_THREADS);
   Ln(label, grid, block, [&](hipStream_t st) {
     hipLaunchKernelGGL(lstm_fwd_kernel<HP>, grid, block, 0, st, l.gates, Whh, l.hs, l.cs,
-                       l.d.kind == DP_LSTM_SEQ ? (float *)nullptr : l.a, B, l.T, l.H);
+                       l.d.kind == DP_LSTM_SEQ ? (&l)[1].a : l.a, l.d.kind == DP_LSTM_SEQ ? 1 : 0, B, l.T, l.H);
   });
 }
 template <int HP>
@@ -846,7 +906,7 @@ static void launch_lstm_bwd(const Launcher &Ln, Layer &l, const float *Whh, int 
   dim3 grid(B), block(LSTM_THREADS);
   Ln(label, grid, block, [&](hipStream_t st) {
     if (l.d.kind == DP_LSTM_SEQ)
-      hipLaunchKernelGGL((lstm_bwd_kernel<HP, true>), grid, block, 0, st, l.gates, (const float *)l.cs, Whh, (const float *)l.g, B, l.T, l.H);
+      hipLaunchKernelGGL((lstm_bwd_kernel<HP, true>), grid, block, 0, st, l.gates, (const float *)l.cs, Whh, (const float *)(&l)[1].g, B, l.T, l.H);
     else
       hipLaunchKernelGGL((lstm_bwd_kernel<HP, false>), grid, block, 0, st, l.gates, (const float *)l.cs, Whh, (const float *)l.g, B, l.T, l.H);
   });
@@ -869,9 +929,13 @@ static inline void vec_dispatch(bool cond, F &&body) {
   if (cond) body(std::true_type{});
   else body(std::false_type{});
 }
+// draw_n > 0: x, y are a dataset of that many examples and the kernels of the step draw the minibatch themselves (key: seed)
 static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t *y, int B, bool priv, float C,
-                    float sigma, uint64_t seed, float *out, float *theta_update = nullptr, float update_step = 0.f) {
+                    float sigma, uint64_t seed, float *out, float *theta_update = nullptr, float update_step = 0.f,
+                    long draw_n = 0) {
   Launcher Ln{c};
+  const FinalWrite fin = {out, theta_update, update_step, (priv && sigma > 0.f) ? sigma * C : 0.f, (uint32_t)seed, (uint32_t)(seed >> 32)};
+  bool written = false; // the last kernel of the step took the final write along
   const int nL = (int)c->L.size();
   const long slot_stride = c->maxB;
   int slot_next = 0;
@@ -916,8 +980,9 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
     BagArgs a{};
     a.tok = (const int *)x; a.E = params; a.W = params + ld.p_off; a.bias = a.W + (long)ld.d.in_features * ld.d.out_features;
     a.y = (const int *)y; a.mean = c->bag_mean; a.sdelta = c->bag_sdelta; a.rows = c->bag_rows; a.pairs = c->pairs;
-    a.off = c->pair_off; a.off_ld = c->maxB; a.wg_shift = c->bag_shift; a.norms = priv ? c->norms : nullptr; a.s = priv ? c->s : nullptr;
+    a.off = c->pair_off; a.off_ld = c->maxB; a.wg_shift = c->emb_shift; a.norms = priv ? c->norms : nullptr; a.s = priv ? c->s : nullptr;
     a.T = le.outC; a.D = le.d.embed_dim; a.N = ld.d.out_features; a.C = C;
+    a.draw_n = draw_n; a.draw_k0 = fin.k0; a.draw_k1 = fin.k1;
     const bool vec = (a.D & 3) == 0 && aligned16(a.E);
     Ln("bag_net", dim3(B), dim3(256), [&](hipStream_t st) {
 #define DP_BAG_CASE(kpt_) \
@@ -927,18 +992,18 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
 #undef DP_BAG_CASE
     });
     EmbAccumArgs q{};
-    q.pairs = c->pairs; q.off = c->pair_off; q.off_ld = c->maxB; q.rows = c->bag_rows; q.out = le.part;
-    q.B = B; q.T = a.T; q.D = a.D; q.V = le.d.vocab; q.wg_shift = c->bag_shift;
-    for (q.lpm = 1; q.lpm < 64 && q.lpm < a.D;) q.lpm <<= 1;
-    q.mean = c->bag_mean; q.sdelta = c->bag_sdelta; q.out_w = ld.part; q.N = a.N;
-    dim3 grid((1u << q.wg_shift) + 1), block(EMB_ACC_THREADS);
+    q.pairs = c->pairs; q.off = c->pair_off; q.off_ld = c->maxB; q.rows = c->bag_rows;
+    q.B = B; q.T = a.T; q.D = a.D; q.V = le.d.vocab; q.wg_shift = c->emb_shift;
+    q.lpm = emb_accum_lanes(a.D);
+    q.mean = c->bag_mean; q.sdelta = c->bag_sdelta; q.N = a.N; q.Dc = a.D;
+    q.fin = fin; q.w_off = ld.p_off;
+    written = true;
+    dim3 grid(emb_accum_grid(q.wg_shift, q.Dc, q.N)), block(EMB_ACC_THREADS);
     Ln("emb_pair_sum", grid, block, [&](hipStream_t st) {
-      hipLaunchKernelGGL(emb_accum_kernel<false>, grid, block, emb_accum_lds_bytes(q.V, q.D, q.wg_shift), st, q);
+      const size_t lds = emb_accum_lds_bytes(q.V, q.D, q.wg_shift);
+      if ((q.D & 3) == 0) hipLaunchKernelGGL((emb_accum_kernel<false, true, true>), grid, block, lds, st, q);
+      else hipLaunchKernelGGL((emb_accum_kernel<false, false, true>), grid, block, lds, st, q);
     });
-    for (Layer *l : {&le, &ld}) {
-      FinalizeSeg &sg = fa.seg[fa.nseg++];
-      sg.p_off = l->p_off; sg.n = l->p_count; sg.part = l->part; sg.stride = l->pstride; sg.nsplit = 1;
-    }
   } else if (B > 0) {
     // The embedding layer's token lists for its clipped sum (a counting sort of the batch by token id) and its zeroed
     // partial: inputs of emb_reduce_kernel that depend on x alone.
@@ -1007,8 +1072,8 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
         const ConvGeom &g = l.geom;
         if (l.dir_fwd || l.dir_bwd) {
           // only the layouts a direct kernel of this step reads (the minimal-filtering kernels have their own)
-          float *need_f = (l.dir_fwd && !l.u_f && !l.first_fwd) ? l.wt_f : nullptr;
-          float *need_b = (l.dir_bwd && !l.u_b && i > 0) ? l.wt_b : nullptr;
+          float *need_f = (l.dir_fwd && !l.u_f && !l.frag_f && !l.first_fwd) ? l.wt_f : nullptr;
+          float *need_b = (l.dir_bwd && !l.u_b && !l.frag_b && i > 0) ? l.wt_b : nullptr;
           if (need_f || need_b) {
             auto &e = la.l[la.n++];
             e.w_off = l.p_off; e.wt_f = need_f; e.wt_b = need_b; e.D = g.D; e.C = g.C;
@@ -1025,6 +1090,22 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
         if (la.n == CONV_LAYOUT_MAX || wa.n == 16) flush();
       }
       flush();
+      SplitConvWeights sw{};
+      auto flush_split = [&]() {
+        if (sw.n > 0) Ln("conv_weight_split", dim3(1), dim3(64), [&](hipStream_t st) { split_conv_weights(st, params, sw); });
+        sw.n = 0;
+      };
+      for (int i = 0; i < nL; ++i) {
+        Layer &l = c->L[i];
+        for (int flip = 0; flip < 2; ++flip) {
+          void *frag = flip ? l.frag_b : l.frag_f;
+          if (!frag) continue;
+          auto &e = sw.l[sw.n++];
+          e.w_off = l.p_off; e.frag = frag; e.D = l.geom.D; e.C = l.geom.C; e.flip = flip;
+          if (sw.n == SPLIT_CONV_MAX) flush_split();
+        }
+      }
+      flush_split();
     }
     // ------------------------------------------------------------ forward
     const float *in = (const float *)x;
@@ -1035,7 +1116,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
     SmallGemmArgs joint_g[2] = {};
     bool joint = false;
     for (int i = 0; i < nL; ++i) {
-      if ((f2 && i == 1) || (h2 && i == nL - 1)) break; // the logits are computed by the kernel that follows the hidden layer
+      if ((f2 && i == 1) || ((h2 || c->class_head) && i == nL - 1)) break; // the logits are computed by the kernel that follows the hidden layer
       Layer &l = c->L[i];
       const float *W = params + l.p_off;
       switch (l.d.kind) {
@@ -1093,6 +1174,21 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
                             OpKMajor<true, false>::can_vec(W, l.d.out_features, 0, l.d.out_features), run);
       } break;
       case DP_CONV2D: {
+        if (l.frag_f) {
+          const ConvGeom &g = l.geom;
+          SplitConvArgs a{};
+          a.x = in; a.frag = l.frag_f; a.bias = W + (long)g.D * g.CKK; a.out = l.a;
+          a.B = B; a.Cin = g.C; a.M = g.D; a.H = g.H; a.W = g.W; a.act = l.d.act;
+          // a 2x2 / stride-2 pool right after the layer: its windows lie inside a wave
+          if (i + 1 < nL && (c->L[i + 1].d.kind == DP_MAXPOOL2D || c->L[i + 1].d.kind == DP_AVGPOOL2D) &&
+              c->L[i + 1].d.kh == 2 && c->L[i + 1].d.kw == 2 && c->L[i + 1].d.stride == 2 && !no_pool_fusion) {
+            a.pool = c->L[i + 1].d.kind == DP_MAXPOOL2D ? 1 : 2;
+            a.pool_out = c->L[i + 1].a; a.pool_arg = c->L[i + 1].arg;
+            fused_pool = i + 1;
+          }
+          Ln(LL("conv_fwd"), dim3(1), dim3(256), [&](hipStream_t st) { split_conv_launch(st, a); });
+          break;
+        }
         if (l.u_f) {
           const ConvGeom &g = l.geom;
           ConvWinoArgs a{};
@@ -1185,6 +1281,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
         }
       } break;
       case DP_SEQ_MEAN: {
+        if (c->L[i - 1].d.kind == DP_LSTM_SEQ) break; // taken by the recurrence
         dim3 grid(B), block(256);
         Ln(LL("seq_mean_fwd"), grid, block, [&](hipStream_t st) {
           hipLaunchKernelGGL(seq_mean_fwd_kernel, grid, block, 0, st, in, l.a, l.T, l.Din);
@@ -1304,6 +1401,17 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
     }
     // ------------------------------------------------------------ loss gradient
     if (f2 || h2) {
+    } else if (c->class_head) {
+      Layer &l = c->L[nL - 1], &p = c->L[nL - 2];
+      const float *Wl = params + l.p_off;
+      float *slot = priv ? c->slots + (long)slot_next * slot_stride : nullptr;
+      if (priv) slot_next += 1;
+      dim3 grid(ceil_div(B, 4)), block(256);
+      Ln("class_head", grid, block, [&](hipStream_t st) {
+        hipLaunchKernelGGL(class_head_kernel, grid, block, 0, st, (const float *)p.a, Wl,
+                           Wl + (long)l.d.in_features * l.d.out_features, (const int *)y, l.g, p.g, slot, B,
+                           l.d.in_features, l.d.out_features);
+      });
     } else if (fused_head) {
       // the last dense layer's bias, the loss gradient and that layer's norm (the first slot of the backward
       // pass) in one launch, one wave per example
@@ -1330,7 +1438,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
       });
     }
     // ------------------------------------------------------------ backward: data gradients and per-example norms
-    for (int i = f2 ? -1 : (h2 ? nL - 2 : nL - 1); i >= 0; --i) {
+    for (int i = f2 ? -1 : ((h2 || c->class_head) ? nL - 2 : nL - 1); i >= 0; --i) {
       Layer &l = c->L[i];
       const float *W = params + l.p_off;
       const float *lin = i > 0 ? c->L[i - 1].a : (const float *)x;
@@ -1409,6 +1517,12 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
             DP_CFW_CASE(true, true, 16) DP_CFW_CASE(true, false, 16) DP_CFW_CASE(false, true, 16) DP_CFW_CASE(false, false, 16)
 #undef DP_CFW_CASE
           });
+        } else if (priv && l.split_norm) {
+          SplitWgArgs a{};
+          a.x = lin; a.dy = l.g; a.B = B; a.C = g.C; a.D = g.D; a.H = g.H; a.W = g.W;
+          a.slots = c->slots; a.slot_stride = slot_stride; a.slot0 = slot_next;
+          a.gstore = l.gst; a.gstride = l.gorder.n_total;
+          Ln(LL("conv_wgrad_norm"), dim3(1), dim3(256), [&](hipStream_t st) { slot_next += split_wgrad_norm(st, a); });
         } else if (priv && l.dir_wg && aligned16(lin)) {
           // one round of resident workgroups, each walking through its run of examples: the next
           // example's tiles are fetched while the current one is multiplied and reduced
@@ -1438,7 +1552,12 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
           };
           vec_dispatch(OpRowMajor<true>::can_vec(l.g, g.P, (long)g.D * g.P, g.P), run);
         }
-        if (prev && l.u_b) {
+        if (prev && l.frag_b) {
+          SplitConvArgs a{};
+          a.x = l.g; a.frag = l.frag_b; a.a_prev = prev->a; a.out = prev->g;
+          a.B = B; a.Cin = g.D; a.M = g.C; a.H = g.H; a.W = g.W; a.act = prev_act;
+          Ln(LL("conv_bwd_data"), dim3(1), dim3(256), [&](hipStream_t st) { split_conv_launch(st, a); });
+        } else if (prev && l.u_b) {
           ConvWinoArgs a{};
           a.x = l.g; a.u = l.u_b; a.bias = nullptr; a.a_prev = prev->a; a.out = prev->g;
           a.B = B; a.Cin = g.D; a.Cpad = l.ub_cpad; a.H = g.H; a.W = g.W; a.M = g.C; a.Mpad = l.ub_mpad; a.act = prev_act;
@@ -1562,20 +1681,14 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
           vec_dispatch(OpLstmIn<true>::can_vec(lin, l.hs, l.Din, l.H) &&
                               OpKMajor<true, false>::can_vec(l.gates, G, (long)l.T * G, G), run);
         }
-        // (measured on the 512 x 256-step configuration: 148 us this way against 133 us on the generic contraction --
-        // one column block per wave leaves one LDS read per multiply and one wave of eight idle -- so the route stays
-        // off; the kernel is kept for the projection, where it is 119 against 178 us)
-        if (false && rows_gemm_fits(G, l.Din, 1, 4) && aligned16(l.gates) && !c->opt.no_rows_gemm) {
-          // dx = dgates W_ih^T with W_ih^T held in registers by persistent workgroups
-          RowsGemmArgs a{};
-          a.A = l.gates; a.W = W; a.w_sk = 1; a.w_sn = G; a.bias = nullptr; a.C = prev->g;
+        if (l.frag_dx) { // dx = dgates W_ih^T: gradient w.r.t. the embedding outputs
+          const SplitWeights w = {W, 1, G, G, l.Din, l.frag_dx};
+          Ln(LL("lstm_weights"), dim3(1), dim3(64), [&](hipStream_t st) { split_rows_prepare(st, &w, 1); });
+          SplitRowsArgs a{};
+          a.A = l.gates; a.lda = G; a.frag = l.frag_dx; a.bias = nullptr; a.C = prev->g; a.ldc = l.Din;
           a.M = (long)B * l.T; a.K = G; a.N = l.Din;
-          const long tiles = (a.M + 63) / 64;
-          dim3 grid((unsigned)std::min<long>(tiles, 256)), block(RG_THREADS);
-          Ln(LL("lstm_dx"), grid, block, [&](hipStream_t st) {
-            hipLaunchKernelGGL((rows_gemm_kernel<1, 4, 4>), grid, block, rows_gemm_lds_bytes(4), st, a);
-          });
-        } else { // dx = dgates W_ih^T: gradient w.r.t. the embedding outputs
+          Ln(LL("lstm_dx"), dim3(1), dim3(256), [&](hipStream_t st) { split_rows_launch(st, a); });
+        } else {
           auto run = [&](auto vt) {
             constexpr bool V = decltype(vt)::value;
             typedef ProbBwdAct<OpRowMajor<V>, OpRowMajor<V>> Pb;
@@ -1590,6 +1703,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
         }
       } break;
       case DP_SEQ_MEAN: {
+        if (prev->d.kind == DP_LSTM_SEQ) break; // taken by the recurrence
         const long n = (long)B * l.in_size;
         dim3 grid = grid1d(n, 256), block(256);
         Ln(LL("seq_mean_bwd"), grid, block, [&](hipStream_t st) {
@@ -1597,6 +1711,22 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
         });
       } break;
       case DP_EMBEDDING: {
+        if (c->emb_pairs) {
+          EmbRowsArgs a{};
+          a.tok = (const int *)x; a.dx = l.g; a.rows = c->pair_rows; a.pairs = c->pairs; a.off = c->pair_off; a.off_ld = c->maxB;
+          a.T = l.outC; a.D = l.d.embed_dim; a.wg_shift = c->emb_shift;
+          if (priv) { a.slot = c->slots + (long)slot_next * slot_stride; slot_next += 1; }
+          dim3 grid(B), block(EMB_ROWS_THREADS);
+          const bool vec = (a.D & 3) == 0; // (dx and the rows are this library's own allocations)
+          Ln(LL("emb_norm"), grid, block, [&](hipStream_t st) {
+#define DP_ROWS_CASE(kpt_) \
+            if (vec) hipLaunchKernelGGL((emb_rows_kernel<kpt_, true>), grid, block, 0, st, a); \
+            else hipLaunchKernelGGL((emb_rows_kernel<kpt_, false>), grid, block, 0, st, a);
+            if (a.T <= 256) { DP_ROWS_CASE(1) } else if (a.T <= 512) { DP_ROWS_CASE(2) } else { DP_ROWS_CASE(4) }
+#undef DP_ROWS_CASE
+          });
+          break;
+        }
         if (priv) {
           dim3 grid(B), block(256);
           float *slot = c->slots + (long)slot_next * slot_stride;
@@ -1632,8 +1762,13 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
       int nsplit = 1;
       switch (l.d.kind) {
       case DP_DENSE: {
+        if (c->class_head) break; // (the last layer: its sums were taken by the embedding's launch)
         if (joint && i >= nL - 2) {
           if (i == nL - 2) {
+            if (f2) { // (nothing else is summed: the two products are the parameter vector)
+              for (int q = 0; q < 2; ++q) { joint_g[q].final = 1; joint_g[q].fin = fin; joint_g[q].j0 = c->L[q].p_off; }
+              written = true;
+            }
             if (h2) joint_g[0].k_scale = joint_g[1].k_scale = sc; // (the head kernel could not scale: the clip factors came later)
             Ln(LL("dense_clipped_sum"), dim3(1), dim3(256), [&](hipStream_t st) { launch_dense_small_gemm(st, joint_g[0], &joint_g[1]); });
           }
@@ -1671,7 +1806,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
       } break;
       case DP_CONV2D: {
         const ConvGeom &g = l.geom;
-        if (priv && l.gst && (!l.dir_wg || aligned16(lin))) {
+        if (priv && l.gst && (l.split_norm || !l.dir_wg || aligned16(lin))) {
           // the norm pass of this step stored every example's gradient: weighted sum of the rows
           const long gstride = l.gorder.n_total;
           int want = (int)std::min<long>(l.max_split, std::max<long>(1, 4096 / ceil_div(gstride, 256)));
@@ -1701,6 +1836,13 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
             else if (db == 1) hipLaunchKernelGGL((conv_wino_wgrad_unit_kernel<16, 2, 1, false>), grid, block, 0, st, a);
             else hipLaunchKernelGGL((conv_wino_wgrad_unit_kernel<16, 2, 2, false>), grid, block, 0, st, a);
           });
+          break;
+        }
+        if (l.split_wg) {
+          SplitWgArgs a{};
+          a.x = lin; a.dy = l.g; a.B = B; a.C = g.C; a.D = g.D; a.H = g.H; a.W = g.W;
+          a.scale = sc; a.part = l.part; a.part_stride = l.pstride;
+          Ln(LL("conv_clipped_sum"), dim3(1), dim3(256), [&](hipStream_t st) { nsplit = split_wgrad_sum(st, a, l.max_split); });
           break;
         }
         if (l.dir_wg && aligned16(lin)) {
@@ -1757,6 +1899,25 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
       case DP_EMBEDDING: {
         const long rows = (long)B * l.outC;
         const int V = l.d.vocab;
+        if (c->emb_pairs) {
+          EmbAccumArgs q{};
+          q.pairs = c->pairs; q.off = c->pair_off; q.off_ld = c->maxB; q.rows = c->pair_rows; q.scale = sc; q.out = l.part;
+          q.B = B; q.T = l.outC; q.D = l.d.embed_dim; q.V = V; q.wg_shift = c->emb_shift;
+          q.lpm = emb_accum_lanes(q.D);
+          dim3 grid(1u << q.wg_shift), block(EMB_ACC_THREADS);
+          if (c->class_head) {
+            const Layer &ld = c->L[nL - 1];
+            q.mean = c->L[nL - 2].a; q.sdelta = ld.g; q.dscale = sc; q.out_w = ld.part; q.N = ld.d.out_features; q.Dc = ld.d.in_features;
+            grid.x = emb_accum_grid(q.wg_shift, q.Dc, q.N);
+          }
+          Ln(LL("emb_scatter"), grid, block, [&](hipStream_t st) {
+            const size_t lds = emb_accum_lds_bytes(q.V, q.D, q.wg_shift);
+            if ((q.D & 3) == 0) hipLaunchKernelGGL((emb_accum_kernel<true, true, false>), grid, block, lds, st, q);
+            else hipLaunchKernelGGL((emb_accum_kernel<true, false, false>), grid, block, lds, st, q);
+          });
+          nsplit = 1;
+          break;
+        }
         if (emb_early) (void)hipStreamWaitEvent(c->stream, c->ev_join, 0); // the token lists were built beside the forward pass
         else emb_prepare(l, i, Ln);
         {
@@ -1783,9 +1944,9 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
     }
   }
   // ------------------------------------------------------------ final write with fused noise
-  {
-    const float noise_std = (priv && sigma > 0.f) ? sigma * C : 0.f;
-    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+  if (!written) {
+    const float noise_std = fin.noise_std;
+    const uint32_t k0 = fin.k0, k1 = fin.k1;
     Ln("finalize_noise", dim3(1), dim3(256), [&](hipStream_t st) {
       launch_finalize(st, fa, out, c->P, noise_std, k0, k1, theta_update, update_step);
     });
@@ -1861,24 +2022,18 @@ extern "C" int dp_step_last_norms(dp_ctx *c, float *norms_out) {
 
 // ---------------------------------------------------------------- minibatch draw and the training loop
 
-// DPSGD item 1: index k of the minibatch = (word k%4 of the Philox block with counter (k/4, 0, 1, 0)) * n >> 32 --
-// uniform over [0, n), with replacement; the third counter word keeps these blocks apart from the noise stream's.
+// (the minibatch draw: draw_index)
 __global__ void sample_indices_kernel(uint32_t k0, uint32_t k1, long n, int batch, int *__restrict__ idx) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= batch) return;
-  uint32_t r[4];
-  philox4x32_10((uint32_t)(k >> 2), 0u, 1u, 0u, k0, k1, r);
-  idx[k] = (int)(((uint64_t)r[k & 3] * (uint64_t)n) >> 32);
+  idx[k] = (int)draw_index(k, n, k0, k1);
 }
 
-// One workgroup per drawn example: its index (as above; one Philox block per thread costs less than a launch of its
+// One workgroup per drawn example: its index (one Philox block per thread costs less than a launch of its
 // own), its input row (fp32 features or int32 token ids: 4-byte words) and its label.
 __global__ void draw_rows_kernel(const uint32_t *__restrict__ data_x, const int *__restrict__ data_y, uint32_t k0,
                                  uint32_t k1, long n, long row_words, uint32_t *__restrict__ xb, int *__restrict__ yb) {
-  uint32_t r[4];
-  philox4x32_10((uint32_t)(blockIdx.x >> 2), 0u, 1u, 0u, k0, k1, r);
-  const uint32_t w = blockIdx.x & 2 ? (blockIdx.x & 1 ? r[3] : r[2]) : (blockIdx.x & 1 ? r[1] : r[0]);
-  const long idx = (long)(((uint64_t)w * (uint64_t)n) >> 32);
+  const long idx = draw_index(blockIdx.x, n, k0, k1);
   const long src = idx * row_words, dst = (long)blockIdx.x * row_words;
   for (long i = threadIdx.x; i < row_words; i += blockDim.x) xb[dst + i] = data_x[src + i];
   if (threadIdx.x == 0) yb[blockIdx.x] = data_y[idx];
@@ -1905,7 +2060,8 @@ extern "C" int dp_step_loop(dp_ctx *c, float *params, const void *data_x, const 
   if (!(C > 0.f) || !(sigma >= 0.f) || std::isnan(C) || std::isinf(sigma) || std::isnan(lr) || std::isinf(lr)) return DP_EINVAL;
   if (std::isinf(C) && sigma > 0.f) return DP_EINVAL;
   const long row_words = c->m.seq_len > 0 ? c->m.seq_len : (long)c->m.in_c * c->m.in_h * c->m.in_w;
-  if (!c->xb) { // first call on this context: room for one drawn minibatch
+  const bool in_step = c->bag; // the step's kernels draw the examples themselves
+  if (!c->xb && !in_step) { // first call on this context: room for one drawn minibatch
     int rc = dev_alloc(c, &c->xb, (size_t)c->maxB * row_words);
     if (rc == DP_OK) rc = dev_alloc(c, &c->yb, c->maxB);
     if (rc != DP_OK) { c->xb = nullptr; return rc; }
@@ -1913,6 +2069,11 @@ extern "C" int dp_step_loop(dp_ctx *c, float *params, const void *data_x, const 
   Launcher Ln{c};
   for (int t = 0; t < steps; ++t) {
     const uint64_t seed = seed0 + (uint64_t)t;
+    if (in_step) {
+      int rc = run_step(c, params, data_x, data_y, batch, true, C, sigma, seed, nullptr, params, lr / (float)batch, (long)n_examples);
+      if (rc != DP_OK) return rc;
+      continue;
+    }
     Ln("sample_minibatch", dim3(1), dim3(256), [&](hipStream_t st) {
       hipLaunchKernelGGL(draw_rows_kernel, dim3(batch), dim3(256), 0, st, (const uint32_t *)data_x, (const int *)data_y,
                          (uint32_t)seed, (uint32_t)(seed >> 32), (long)n_examples, row_words, c->xb, c->yb);
@@ -1939,23 +2100,24 @@ extern "C" int dp_step_describe_plan(const dp_ctx *c, char *buf, size_t cap) {
       if (c->fused2) { norm = "fused"; if (i == 1) { fwd = bwd = "fused"; sum = c->joint2 ? "joint" : "fused"; } }
       if (c->head2 && i + 2 >= c->L.size()) { norm = "head"; if (i + 1 == c->L.size()) { fwd = bwd = "head"; if (c->joint2) sum = "joint"; } }
       if (c->fusedcnn) fwd = bwd = norm = sum = "fused-net";
-      if (c->bag) { fwd = bwd = norm = "fused"; sum = "pairs"; }
+      if (c->class_head && i + 1 == c->L.size()) { fwd = bwd = norm = "fused"; sum = "pairs"; }
       break;
     case DP_CONV2D:
-      fwd = l.u_f ? (l.wino_f == 2 ? "mf64" : "mf32") : (l.first_fwd ? "first" : (l.dir_fwd ? "direct" : "generic"));
-      if (l.u_f && i + 1 < c->L.size() && !c->opt.no_pool_fusion) { // the pool after the layer is taken in its epilogue
+      fwd = l.frag_f ? "split" : l.u_f ? (l.wino_f == 2 ? "mf64" : "mf32") : (l.first_fwd ? "first" : (l.dir_fwd ? "direct" : "generic"));
+      if ((l.u_f || l.frag_f) && i + 1 < c->L.size() && !c->opt.no_pool_fusion) { // the pool after the layer is taken in its epilogue
         const dp_layer_desc &n = c->L[i + 1].d;
         if ((n.kind == DP_MAXPOOL2D || n.kind == DP_AVGPOOL2D) && n.kh == 2 && n.kw == 2 && n.stride == 2)
           fwd += n.kind == DP_MAXPOOL2D ? "+maxpool" : "+avgpool";
       }
-      bwd = i == 0 ? "-" : (l.u_b ? (l.wino_b == 2 ? "mf64" : "mf32") : (l.dir_bwd ? "direct" : (l.cols ? "columns" : "generic")));
-      norm = l.gram ? "gram" : ((l.wino_norm && l.gst) ? "mf+store" : (l.dir_wg ? (l.gst ? "direct+store" : (l.wg_ws ? "ws" : "direct"))
+      bwd = i == 0 ? "-" : (l.frag_b ? "split" : l.u_b ? (l.wino_b == 2 ? "mf64" : "mf32") : (l.dir_bwd ? "direct" : (l.cols ? "columns" : "generic")));
+      norm = l.gram ? "gram" : l.split_norm ? (l.gst ? "split+store" : "split") : ((l.wino_norm && l.gst) ? "mf+store" : (l.dir_wg ? (l.gst ? "direct+store" : (l.wg_ws ? "ws" : "direct"))
                                                                                 : (l.gst ? "generic+store" : "generic")));
-      sum = l.gst ? "weighted" : ((l.wino_wgu || l.wino_wg) ? "mf" : (l.dir_wg ? (l.wg_ws ? "ws" : "direct") : "generic"));
+      sum = l.gst ? "weighted" : ((l.wino_wgu || l.wino_wg) ? "mf" : l.split_wg ? "split" : (l.dir_wg ? (l.wg_ws ? "ws" : "direct") : "generic"));
       if (c->fusedcnn) fwd = bwd = norm = sum = "fused-net";
       break;
     case DP_EMBEDDING:
       fwd = "gather"; norm = "sorted-segments"; sum = "scatter";
+      if (c->emb_pairs) norm = sum = "pairs";
       if (c->bag) { fwd = norm = "fused"; sum = "pairs"; }
       break;
     case DP_LSTM_LAST:

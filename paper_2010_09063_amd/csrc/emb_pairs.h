@@ -87,7 +87,7 @@ __device__ __forceinline__ int emb_write_pairs(const uint32_t *key, uint16_t *he
 // the number of steps with the token, so its squared norm is |W delta / T|^2 times the sum of the squared counts.
 // Bound by latency (T + 4 row loads, a 256-key sort in registers, six barriers), so several workgroups share a CU.
 struct BagArgs {
-  const int *tok;
+  const int *tok; // [B][T], or the whole dataset where the minibatch is drawn here (draw_n > 0 examples; key draw_k0, draw_k1)
   const float *E, *W, *bias; // [V][D], [D][N], [N]
   const int *y;
   float *mean;     // [B][D]
@@ -98,7 +98,17 @@ struct BagArgs {
   float *norms, *s; // [B] or null (then nothing is clipped)
   int T, D, N, wg_shift;
   float C;
+  long draw_n; uint32_t draw_k0, draw_k1;
 };
+
+// DPSGD item 1: index k of the minibatch = (word k % 4 of the Philox block with counter (k / 4, 0, 1, 0)) * n >> 32 --
+// uniform over [0, n), with replacement; the third counter word keeps these blocks apart from the noise stream's.
+__device__ __forceinline__ long draw_index(int k, long n, uint32_t k0, uint32_t k1) {
+  uint32_t r[4];
+  philox4x32_10((uint32_t)(k >> 2), 0u, 1u, 0u, k0, k1, r);
+  const uint32_t w = k & 2 ? (k & 1 ? r[3] : r[2]) : (k & 1 ? r[1] : r[0]);
+  return (long)(((uint64_t)w * (uint64_t)n) >> 32);
+}
 
 #define BAG_DMAX 128
 
@@ -114,7 +124,8 @@ __global__ __launch_bounds__(256) void bag_net_kernel(const BagArgs a) {
   __shared__ int cred[4];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int T = a.T, D = a.D, N = a.N;
-  const int *tok = a.tok + (long)b * T;
+  const long src = a.draw_n > 0 ? draw_index(b, a.draw_n, a.draw_k0, a.draw_k1) : b;
+  const int *tok = a.tok + src * T;
   uint32_t kr[KPT];
 #pragma unroll
   for (int m = 0; m < KPT; ++m) {
@@ -193,7 +204,7 @@ __global__ __launch_bounds__(256) void bag_net_kernel(const BagArgs a) {
     float se = ex;
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) se += __shfl_xor(se, o, 16);
-    const float dn = n < N ? ex * (1.f / se) - (n == a.y[b] ? 1.f : 0.f) : 0.f;
+    const float dn = n < N ? ex * (1.f / se) - (n == a.y[src] ? 1.f : 0.f) : 0.f;
     d2 = dn * dn;
 #pragma unroll
     for (int o = 8; o > 0; o >>= 1) d2 += __shfl_xor(d2, o, 16);
@@ -326,6 +337,7 @@ __global__ __launch_bounds__(EMB_ROWS_THREADS) void emb_rows_kernel(const EmbRow
 
 #define EMB_ACC_THREADS 1024
 #define EMB_ACC_CAP 2048        // pairs a workgroup holds at a time
+#define EMB_ACC_CLS 32          // outputs of the classifier per workgroup (with all 202 of the LSTM network's in one, it took 60 us)
 #define EMB_ACC_CHUNK 16        // pairs of one token that a group of lanes adds up at a time
 #define EMB_ACC_LDS (38 * 1024) // per workgroup: the rows of its tokens and three counters for each
 
@@ -333,14 +345,16 @@ struct EmbAccumArgs {
   const uint32_t *pairs, *off; long off_ld; // [B][T], [1 << wg_shift][off_ld]
   // rows: not PER_PAIR: rows[b] times the pair's count (one row per example); PER_PAIR: rows[b * T + pair] times scale[b]
   const float *rows, *scale;
-  float *out;                // [V][D], every row written
+  float *out;                // [V][D], every row written (FINAL: not used)
+  FinalWrite fin; long w_off; // FINAL: the network is complete with this launch, the table at coordinate 0, the classifier at w_off
   int B, T, D, V, wg_shift;  // 1 << wg_shift workgroups share the tokens
   int lpm;                   // lanes per pair, a power of two
-  // one more workgroup: sum_b in[b] (x) s delta[b] and sum_b s delta[b] of a classifier of N classes: its input rows
+  // further workgroups (emb_accum_grid): sum_b in[b] (x) s delta[b] and sum_b s delta[b] of a classifier of N classes: its input rows
   // [B][Dc], its loss gradient in rows of 16, and the factors that are not in it yet (null: it carries them)
   const float *mean, *sdelta, *dscale; float *out_w; int N, Dc;
 };
 
+static inline int emb_accum_grid(int wg_shift, int Dc, int N) { return (1 << wg_shift) + ((Dc + 1) * N + EMB_ACC_CLS - 1) / EMB_ACC_CLS; }
 static inline int emb_accum_lanes(int D) { // lanes per pair
   const int n = (D & 3) == 0 ? D / 4 : D;
   int l = 1;
@@ -366,7 +380,7 @@ static inline int emb_accum_wg_shift(long V, int D) {
 // depends on the order in which the integer atomics retire.
 // VEC: D is a multiple of 4 and a lane holds four coordinates (at D = 100 half as many lanes per row, all of a chunk's
 // rows in flight: 66 -> 25 us on the LSTM network at 512 examples).
-template <bool PER_PAIR, bool VEC>
+template <bool PER_PAIR, bool VEC, bool FINAL>
 __global__ __launch_bounds__(EMB_ACC_THREADS) void emb_accum_kernel(const EmbAccumArgs a) {
   extern __shared__ float acc[];
   __shared__ uint2 list[EMB_ACC_CAP];
@@ -374,31 +388,29 @@ __global__ __launch_bounds__(EMB_ACC_THREADS) void emb_accum_kernel(const EmbAcc
   __shared__ int wtot[EMB_ACC_THREADS / 64], items;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n_wg = 1 << a.wg_shift, wg = blockIdx.x, D = a.D, T = a.T;
-  if (wg == n_wg) { // the classifier's sums: thread (output o, group of examples g)
-    const int Dc = a.Dc, n_out = (Dc + 1) * a.N;
-    for (int o0 = 0; o0 < n_out; o0 += EMB_ACC_THREADS) {
-      const int ch = min(EMB_ACC_THREADS, n_out - o0), G = EMB_ACC_THREADS / ch;
-      const int o = o0 + tid % ch, g = tid / ch, e = o / a.N, n = o - e * a.N;
-      float v = 0.f;
-      for (int b = g; b < a.B && g < G; b += 8 * G) { // eight examples in flight
-        float m[8], d[8];
+  if (wg >= n_wg) { // the classifier's sums, EMB_ACC_CLS outputs per workgroup: thread (output o, group of examples g)
+    const int Dc = a.Dc, n_out = (Dc + 1) * a.N, o0 = (wg - n_wg) * EMB_ACC_CLS;
+    const int ch = min(EMB_ACC_CLS, n_out - o0), G = EMB_ACC_THREADS / ch;
+    const int o = o0 + tid % ch, g = tid / ch, e = o / a.N, n = o - e * a.N;
+    float v = 0.f;
+    for (int b = g; b < a.B && g < G; b += 8 * G) { // eight examples in flight
+      float m[8], d[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const long bb = min(b + u * G, a.B - 1);
-          m[u] = a.mean[bb * Dc + min(e, Dc - 1)];
-          d[u] = a.sdelta[bb * 16 + n];
-          if (a.dscale != nullptr) d[u] *= a.dscale[bb];
-        }
+      for (int u = 0; u < 8; ++u) {
+        const long bb = min(b + u * G, a.B - 1);
+        m[u] = a.mean[bb * Dc + min(e, Dc - 1)];
+        d[u] = a.sdelta[bb * 16 + n];
+        if (a.dscale != nullptr) d[u] *= a.dscale[bb];
+      }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v += b + u * G < a.B ? (e < Dc ? m[u] * d[u] : d[u]) : 0.f;
-      }
-      acc[tid] = v;
-      __syncthreads();
-      if (tid < ch) {
-        for (int q = 1; q < G; ++q) v += acc[q * ch + tid];
-        a.out_w[o] = v;
-      }
-      __syncthreads();
+      for (int u = 0; u < 8; ++u) v += b + u * G < a.B ? (e < Dc ? m[u] * d[u] : d[u]) : 0.f;
+    }
+    acc[tid] = v;
+    __syncthreads();
+    if (tid < ch) {
+      for (int q = 1; q < G; ++q) v += acc[q * ch + tid];
+      if (FINAL) final_write(a.fin, a.w_off + o, v);
+      else a.out_w[o] = v;
     }
     return;
   }
@@ -515,6 +527,8 @@ __global__ __launch_bounds__(EMB_ACC_THREADS) void emb_accum_kernel(const EmbAcc
   for (int i = tid; i < n_rows * D; i += EMB_ACC_THREADS) {
     const int r = i / D;
     const long v = ((long)r << a.wg_shift) + wg;
-    if (v < a.V) a.out[v * D + (i - r * D)] = acc[i];
+    if (v >= a.V) continue;
+    if (FINAL) final_write(a.fin, v * D + (i - r * D), acc[i]);
+    else a.out[v * D + (i - r * D)] = acc[i];
   }
 }

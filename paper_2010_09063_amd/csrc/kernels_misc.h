@@ -273,7 +273,8 @@ struct GradOrder {
   int NBW, WN, NW;    // tap slots per wave group, wave groups along the taps, wave groups per channel block
   int flat;           // 1: one wave group whose lane column is the flattened (channel, tap) index;
                       // 2: the rows are in the parameter layout already;
-                      // 3: rows are [D][C*KK + 1], the bias gradient being the last column
+                      // 3: rows are [D][C*KK + 1], the bias gradient being the last column;
+                      // 4: rows are [D][KK][C], then the bias gradient
   long n_w;           // flat 0 / 1: stored words before the bias
   long n_total;       // words per stored row
 };
@@ -290,6 +291,9 @@ __global__ __launch_bounds__(256) void weighted_sum_kernel(const float *__restri
     const long m = n / (ckk + 1);
     const int col = (int)(n - m * (ckk + 1));
     p = col < ckk ? m * ckk + col : (long)o.D * ckk + m;
+  } else if (o.flat == 4) {
+    const long w = (long)o.D * o.KK * o.C, t = n / o.C, d = t / o.KK;
+    p = n < w ? (d * o.C + (n - t * o.C)) * o.KK + (t - d * o.KK) : n;
   } else if (n >= o.n_w) {
     p = (long)o.D * o.C * o.KK + (n - o.n_w);
   } else {
@@ -452,6 +456,32 @@ __device__ __forceinline__ void normal4(uint64_t blk, uint32_t k0, uint32_t k1, 
   z[0] = r0 * c; z[1] = r0 * s;
   sincospif(2.f * u[3], &s, &c);
   z[2] = r1 * c; z[3] = r1 * s;
+}
+
+// coordinate j's normal alone: the same operations on its half of the block
+__device__ __forceinline__ float normal1(uint64_t j, uint32_t k0, uint32_t k1) {
+  uint32_t r[4];
+  philox4x32_10((uint32_t)(j >> 2), (uint32_t)(j >> 34), 0u, 0u, k0, k1, r);
+  const uint32_t ra = j & 2 ? r[2] : r[0], rb = j & 2 ? r[3] : r[1];
+  const float ua = ((float)(ra >> 9) + 0.5f) * (1.0f / 8388608.0f), ub = ((float)(rb >> 9) + 0.5f) * (1.0f / 8388608.0f);
+  const float rr = sqrtf(-2.f * logf(ua));
+  float s, c;
+  sincospif(2.f * ub, &s, &c);
+  return rr * (j & 1 ? s : c);
+}
+
+// The final write of one coordinate by a kernel whose sums are complete (theta, out and step as in finalize_kernel).  A
+// block's Philox words are drawn for each of its coordinates, but a launch and a round trip of the sums through memory
+// go away: 4 to 6 us of steps that take 24 to 35.
+struct FinalWrite {
+  float *out, *theta;
+  float step, noise_std;
+  uint32_t k0, k1;
+};
+__device__ __forceinline__ void final_write(const FinalWrite &f, long j, float v) {
+  if (f.noise_std > 0.f) v = fmaf(f.noise_std, normal1((uint64_t)j, f.k0, f.k1), v);
+  if (f.out) f.out[j] = v;
+  if (f.theta) f.theta[j] -= f.step * v;
 }
 
 // Final write (DPSGD item 3): out[j] = sum over split-K partials of the clipped sum + sigma*C*z_j.

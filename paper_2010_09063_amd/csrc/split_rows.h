@@ -1,0 +1,26 @@
+// C[M x N] = A[M x K] W (+ bias): one row per (example, step), a weight matrix that every row shares -- the gradient of the
+// LSTM's input -- on the bf16 matrix units (split_bf16.h).  Kernels in split_rows.hip.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+
+struct SplitRowsArgs {
+  const float *A; long lda;  // rows of A; reads run up to SPLIT_ROWS_SLACK floats past the end of the last row
+  const void *frag;          // the split weights (split_rows_prepare)
+  const float *bias;         // [N] or null
+  float *C; long ldc;
+  long M;
+  int K, N;
+};
+struct SplitWeights { // element (k, n) = W[k * sk + n * sn]
+  const float *W; long sk, sn;
+  int K, N;
+  void *frag;
+};
+
+#define SPLIT_ROWS_SLACK 16
+static inline size_t split_rows_frag_bytes(int K, int N) { return (size_t)((K + 15) / 16) * ((N + 31) / 32) * 3 * 1024; }
+
+// splits up to two weight matrices in one launch
+void split_rows_prepare(hipStream_t st, const SplitWeights *w, int n);
+void split_rows_launch(hipStream_t st, const SplitRowsArgs &a);

@@ -1,0 +1,316 @@
+#include "split_wgrad.h"
+
+#include <algorithm>
+
+#include "split_bf16.h"
+
+// G[d, c, tap] = sum over the pixels of dy[d, p] x[c, p + tap]: M = output channel, N = input channel, K = pixel, nine
+// accumulators of 32 x 32 per wave.  The matrix instruction wants eight consecutive k of a row in one 16-byte register
+// group, and the two operands are shifted against each other by the tap, so "consecutive" pixels of a row are taken
+// S = W / 8 apart: group s of a row is x = s, s + S, ..., s + 7 S.  Shifted by kx - 1 that is the group
+// phi = s + kx of the haloed row (haloed columns phi, phi + S, ...), so a row of the input is staged as its S + 2
+// groups phi, each split once, and every tap is a read at a constant offset, all of it aligned.  On 4-wide planes a
+// group is two rows.  A thread stages whole rows: it loads a row with 16-byte loads and picks the groups out of its
+// registers.  One k step is two groups: rows 2 rho and 2 rho + 1, one per half of the wave.
+//
+// A workgroup of four waves owns a block of 32 input channels and 32 DBW output channels; the 4 / DBW waves of a block of
+// output channels share the k steps of a band of rows and add up at the end.  54 matrix instructions of 32 cycles per
+// k step against 30 LDS reads; staging costs about 300 vector instructions per thread and band, which the second
+// workgroup of the CU covers.
+template <int W_>
+struct SplitWgGeom {
+  static constexpr int W = W_;
+  static constexpr int S = W_ / 8 > 0 ? W_ / 8 : 1;      // groups per row (4-wide: per pair of rows)
+  static constexpr int PHI = W_ == 4 ? 3 : S + 2;        // groups per haloed row
+  static constexpr int TR = W_ == 32 ? 2 : (W_ == 16 ? 4 : (W_ == 8 ? 8 : 16)); // rows of a band (4-wide: four images)
+  static constexpr int XR = W_ == 4 ? 4 * 5 : TR + 2;    // staged input rows (4-wide: per image the five pairs of rows)
+  static constexpr int YR = W_ == 4 ? 4 * 2 : TR;        // staged dy rows (4-wide: pairs)
+  static constexpr int KSTEPS = W_ == 4 ? 4 : TR / 2 * S;
+  static constexpr int XBYTES = XR * PHI * 3 * 512, YBYTES = YR * S * 3 * 512; // dy: per block of 32 output channels
+};
+
+template <int W_, int DBW, bool NORM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1 : 2, W_ == 4 ? 1 : 2))) void split_wgrad_kernel(const SplitWgArgs a) {
+  typedef SplitWgGeom<W_> G;
+  constexpr int S = G::S, KW = 4 / DBW;
+  constexpr bool APART = W_ == 4 && NORM; // every wave has an example of its own: nothing to add up
+  static_assert(!APART || DBW == 1, "4-wide norms: one block of output channels per workgroup");
+  constexpr int STAGE = G::XBYTES + DBW * G::YBYTES, EXCH = 3 * 16 * 64 * 4; // per wave: three taps' registers
+  __shared__ __attribute__((aligned(16))) char lds[STAGE > 4 * EXCH ? STAGE : 4 * EXCH];
+  __shared__ float red[256];
+  char *const xs = lds, *const ys = lds + G::XBYTES;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lk = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kp = wave % KW, db = wave / KW;
+  const int C = a.C, D = a.D, H = a.H, HW = H * W_;
+  const int c0 = blockIdx.x * 32, d0 = blockIdx.z * 32 * DBW;
+  const bool bias_wg = blockIdx.x == 0;
+  constexpr int EX_BAND = W_ == 4 ? 4 : 1;
+  const int ex0 = NORM ? (int)blockIdx.y * EX_BAND : (int)blockIdx.y * a.ex_per_block;
+  const int ex1 = NORM ? min(a.B, ex0 + EX_BAND) : min(a.B, ex0 + a.ex_per_block);
+  const int bands = W_ == 4 ? 1 : H / G::TR;
+
+  sb_f32x16 acc[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+  float bsum[DBW][APART ? 4 : 1] = {}; // sums of dy over what this thread stages (output channel tid % 32), for the bias
+
+  auto put = [&](char *dst, const float (&v)[8]) {
+    SbFrag f;
+    sb_split8(v, f);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<sb_u32x4 *>(dst + p * 512) = f.p[p];
+  };
+  auto row_load = [&](const float *p, float (&v)[W_]) {
+#pragma unroll
+    for (int q = 0; q < W_ / 4; ++q) {
+      const sb_f32x4u t = *reinterpret_cast<const sb_f32x4u *>(p + 4 * q);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[4 * q + j] = t[j];
+    }
+  };
+  for (int e = ex0; e < ex1; e += EX_BAND) {
+    for (int band = 0; band < bands; ++band) {
+      __syncthreads(); // the last band's operands have been read
+      // ---- input rows: item (row, channel), channels along the lanes
+#pragma unroll
+      for (int q = 0; q < (G::XR * 32 + 255) / 256; ++q) {
+        const int it = tid + 256 * q, c = it & 31, r = it >> 5;
+        if (G::XR * 32 % 256 != 0 && r >= G::XR) break; // (a whole wave or half of one)
+        char *dst = xs + (r * G::PHI * 3 * 32 + c) * 16;
+        if constexpr (W_ == 4) {
+          const int im = r / 5, y = r - im * 5 - 1; // rows y and y + 1 of the pair
+          const bool ok = c0 + c < C && e + im < ex1;
+          const float *p = a.x + ((long)(ok ? e + im : 0) * C + (ok ? c0 + c : 0)) * HW;
+          float u[4], v[4];
+          row_load(p + max(y, 0) * 4, u);
+          row_load(p + min(y + 1, 3) * 4, v);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) { u[j] = ok && y >= 0 ? u[j] : 0.f; v[j] = ok && y < 3 ? v[j] : 0.f; }
+#pragma unroll
+          for (int phi = 0; phi < 3; ++phi) {
+            float g[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const int x = phi - 1 + j;
+              g[j] = x >= 0 && x < 4 ? u[x < 0 ? 0 : (x > 3 ? 3 : x)] : 0.f;
+              g[4 + j] = x >= 0 && x < 4 ? v[x < 0 ? 0 : (x > 3 ? 3 : x)] : 0.f;
+            }
+            put(dst + phi * 3 * 512, g);
+          }
+        } else {
+          const int y = band * G::TR + r - 1;
+          const bool ok = c0 + c < C && y >= 0 && y < H;
+          float u[W_];
+          row_load(a.x + ((long)e * C + (ok ? c0 + c : 0)) * HW + (ok ? y * W_ : 0), u);
+#pragma unroll
+          for (int j = 0; j < W_; ++j) u[j] = ok ? u[j] : 0.f;
+#pragma unroll
+          for (int phi = 0; phi < G::PHI; ++phi) {
+            float g[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const int x = phi - 1 + S * j;
+              g[j] = x >= 0 && x < W_ ? u[x < 0 ? 0 : (x >= W_ ? W_ - 1 : x)] : 0.f;
+            }
+            put(dst + phi * 3 * 512, g);
+          }
+        }
+      }
+      // ---- dy rows: item (block of output channels, row, channel)
+#pragma unroll
+      for (int q = 0; q < (DBW * G::YR * 32 + 255) / 256; ++q) {
+        const int it = tid + 256 * q, d = it & 31, rr = it >> 5, b = rr / G::YR, r = rr - b * G::YR;
+        if (DBW * G::YR * 32 % 256 != 0 && b >= DBW) break;
+        char *dst = ys + b * G::YBYTES + (r * S * 3 * 32 + d) * 16;
+        const int im = W_ == 4 ? r >> 1 : 0;
+        const bool ok = d0 + 32 * b + d < D && e + im < ex1;
+        const float f = ok ? (NORM ? 1.f : a.scale[e + im]) : 0.f;
+        constexpr int N = W_ == 4 ? 8 : W_;
+        const float *p = a.dy + ((long)(ok ? e + im : 0) * D + (ok ? d0 + 32 * b + d : 0)) * HW + (W_ == 4 ? (r & 1) * 8 : (band * G::TR + r) * W_);
+        float u[N];
+#pragma unroll
+        for (int t = 0; t < N / 4; ++t) {
+          const sb_f32x4u v = *reinterpret_cast<const sb_f32x4u *>(p + 4 * t);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) u[4 * t + j] = ok ? (NORM ? v[j] : v[j] * f) : 0.f;
+        }
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < N; ++j) sum += u[j];
+#pragma unroll
+        for (int bb = 0; bb < DBW; ++bb)
+#pragma unroll
+          for (int m = 0; m < (APART ? 4 : 1); ++m) bsum[bb][m] += (DBW == 1 || bb == b) && (!APART || m == im) ? sum : 0.f;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+          float g[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) g[j] = W_ == 4 ? u[j] : u[s + S * j];
+          put(dst + s * 3 * 512, g);
+        }
+      }
+      __syncthreads();
+      // ---- this wave's k steps
+#pragma unroll
+      for (int q = 0; q < G::KSTEPS / KW; ++q) {
+        const int k = kp + q * KW;
+        const int rho = k / S, s = k - rho * S;
+        SbFrag yf[1];
+        const char *yp = ys + db * G::YBYTES + (((2 * rho + lk) * S + s) * 3 * 32 + li) * 16;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) yf[0].p[p] = *reinterpret_cast<const sb_u32x4 *>(yp + p * 512);
+        // (4-wide: k step = image; the half lk starts at row 2 lk, so its pair for tap row ky is 2 lk + ky of the five)
+        const char *xp = xs + (((W_ == 4 ? rho * 5 + 2 * lk : 2 * rho + lk) * G::PHI + (W_ == 4 ? 0 : s)) * 3 * 32 + li) * 16;
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) {
+          SbFrag xf[3];
+#pragma unroll
+          for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+              xf[kx].p[p] = *reinterpret_cast<const sb_u32x4 *>(xp + ((ky * G::PHI + kx) * 3 + p) * 512);
+          sb_mfma(yf, xf, *reinterpret_cast<sb_f32x16 (*)[1][3]>(&acc[3 * ky]));
+        }
+      }
+    }
+  }
+
+  // ---- the waves of a block of output channels add up, three taps at a time, each finishing 16 / KW registers
+  constexpr int RN = APART ? 16 : 16 / KW;
+  const int r0 = APART ? 0 : kp * RN;
+  float fin[9][RN];
+  if constexpr (APART || KW == 1) {
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int r = 0; r < RN; ++r) fin[t][r] = acc[t][r];
+  } else {
+#pragma unroll
+    for (int t3 = 0; t3 < 9; t3 += 3) {
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) *reinterpret_cast<float *>(lds + wave * EXCH + ((t * 16 + r) * 64 + lane) * 4) = acc[t3 + t][r];
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int r = 0; r < RN; ++r) {
+          float v = 0.f;
+#pragma unroll
+          for (int w = 0; w < KW; ++w)
+            v += *reinterpret_cast<const float *>(lds + (db * KW + w) * EXCH + ((t * 16 + r0 + r) * 64 + lane) * 4);
+          fin[t3 + t][r] = v;
+        }
+    }
+  }
+  // ---- bias: eight threads staged a channel's rows
+  float bias[DBW][APART ? 4 : 1];
+#pragma unroll
+  for (int b = 0; b < DBW; ++b)
+#pragma unroll
+    for (int m = 0; m < (APART ? 4 : 1); ++m) {
+      __syncthreads();
+      red[tid] = bsum[b][m];
+      __syncthreads();
+      float v = 0.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v += red[(tid & 31) + 32 * q];
+      bias[b][m] = v;
+    }
+  const int c = c0 + li, dw = d0 + 32 * db;
+  if constexpr (NORM) {
+    const int e = APART ? ex0 + wave : ex0;
+    const bool mine = e < ex1;
+    float n2 = 0.f;
+    float *gs = a.gstore != nullptr && mine ? a.gstore + (long)e * a.gstride : nullptr;
+#pragma unroll
+    for (int r = 0; r < RN; ++r) {
+      // accumulator register r of a lane: row 8 (r / 4) + 4 lk + r % 4, column li
+      const int d = dw + 8 * ((r0 + r) >> 2) + 4 * lk + ((r0 + r) & 3);
+#pragma unroll
+      for (int t = 0; t < 9; ++t) {
+        const float v = fin[t][r];
+        n2 = fmaf(v, v, n2); // (zero beyond both channel counts: nothing else was staged)
+        if (gs != nullptr && d < D && c < C) gs[((long)d * 9 + t) * C + c] = v;
+      }
+    }
+    if (bias_wg) {
+      if constexpr (APART) {
+        const float v = wave == 0 ? bias[0][0] : wave == 1 ? bias[0][1] : wave == 2 ? bias[0][2] : bias[0][3];
+        if (lane < 32) n2 = fmaf(v, v, n2);
+        if (gs != nullptr && lane < 32 && dw + lane < D) gs[(long)D * 9 * C + dw + lane] = v;
+      } else {
+#pragma unroll
+        for (int b = 0; b < DBW; ++b) {
+          if (tid < 32) n2 = fmaf(bias[b][0], bias[b][0], n2);
+          if (gs != nullptr && tid < 32 && d0 + 32 * b + tid < D) gs[(long)D * 9 * C + d0 + 32 * b + tid] = bias[b][0];
+        }
+      }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o, 64);
+    const long slot = (long)(a.slot0 + (int)(blockIdx.x * gridDim.z + blockIdx.z)) * a.slot_stride;
+    if constexpr (APART) {
+      if (lane == 0 && mine) a.slots[slot + e] = n2;
+    } else {
+      __syncthreads();
+      if (lane == 0) red[wave] = n2;
+      __syncthreads();
+      if (tid == 0 && mine) a.slots[slot + e] = (red[0] + red[1]) + (red[2] + red[3]);
+    }
+  } else {
+    float *pp = a.part + (long)blockIdx.y * a.part_stride;
+#pragma unroll
+    for (int r = 0; r < RN; ++r) {
+      const int d = dw + 8 * ((r0 + r) >> 2) + 4 * lk + ((r0 + r) & 3);
+      if (d < D && c < C) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) pp[((long)d * C + c) * 9 + t] = fin[t][r];
+      }
+    }
+    if (bias_wg) {
+#pragma unroll
+      for (int b = 0; b < DBW; ++b)
+        if (tid < 32 && d0 + 32 * b + tid < D) pp[(long)D * C * 9 + d0 + 32 * b + tid] = bias[b][0];
+    }
+  }
+}
+
+template <int W_, int DBW, bool NORM>
+static int launch_one(hipStream_t st, const SplitWgArgs &a, int groups) {
+  dim3 grid((a.C + 31) / 32, groups, (a.D + 32 * DBW - 1) / (32 * DBW));
+  hipLaunchKernelGGL((split_wgrad_kernel<W_, DBW, NORM>), grid, dim3(256), 0, st, a);
+  return (int)(grid.x * grid.z);
+}
+
+int split_wgrad_norm(hipStream_t st, const SplitWgArgs &a) {
+  const int cb = (a.C + 31) / 32, dbl = (a.D + 31) / 32;
+  // two blocks of output channels per workgroup share its input rows; where that wastes none and leaves the chip two
+  // workgroups per CU
+  const bool two = dbl % 2 == 0 && (long)a.B * cb * (dbl / 2) >= 512;
+  if (a.W == 4) return launch_one<4, 1, true>(st, a, (a.B + 3) / 4);
+  if (a.W == 8) return two ? launch_one<8, 2, true>(st, a, a.B) : launch_one<8, 1, true>(st, a, a.B);
+  if (a.W == 16) return two ? launch_one<16, 2, true>(st, a, a.B) : launch_one<16, 1, true>(st, a, a.B);
+  return two ? launch_one<32, 2, true>(st, a, a.B) : launch_one<32, 1, true>(st, a, a.B);
+}
+
+int split_wgrad_sum(hipStream_t st, SplitWgArgs a, int max_split) {
+  const int cb = (a.C + 31) / 32, dbl = (a.D + 31) / 32;
+  const bool two = dbl % 2 == 0;
+  const int blocks = cb * (two ? dbl / 2 : dbl);
+  // about one round of two workgroups per CU; a partial row costs its write and a read by the final write
+  const int want = std::max(1, std::min(max_split, (512 + blocks - 1) / blocks));
+  int eps = (a.B + want - 1) / want;
+  if (a.W == 4) eps = (eps + 3) / 4 * 4;
+  a.ex_per_block = eps;
+  const int groups = (a.B + eps - 1) / eps;
+  if (a.W == 4) two ? launch_one<4, 2, false>(st, a, groups) : launch_one<4, 1, false>(st, a, groups);
+  else if (a.W == 8) two ? launch_one<8, 2, false>(st, a, groups) : launch_one<8, 1, false>(st, a, groups);
+  else if (a.W == 16) two ? launch_one<16, 2, false>(st, a, groups) : launch_one<16, 1, false>(st, a, groups);
+  else two ? launch_one<32, 2, false>(st, a, groups) : launch_one<32, 1, false>(st, a, groups);
+  return groups;
+}

@@ -47,3 +47,33 @@ def test_two_layer_networks_of_widths_off_the_vector_size(d_in, hidden, classes,
     x, y = W.make_inputs(m, batch, rng, x_dist="normal")
     theta = W.init_params(m, rng, bias_scale=0.3)
     _check_all_regimes(m, x, y, theta, f"dense {d_in}->{hidden}->{classes}/B{batch}")
+
+
+@pytest.mark.parametrize("cin,widths,plane,act,pool,batch", [
+    (3, (16, 48), (32, 32), "tanh", "max", 3),      # one and two blocks of output channels, the second half empty
+    (3, (48, 100, 20), (4, 32), "relu", "avg", 5),  # the fewest rows of a 32-wide plane; ragged blocks on both sides
+    (16, (96, 33), (16, 16), "tanh", "max", 4),     # three blocks; one channel past a block
+    (17, (20, 70), (4, 16), "relu", "avg", 3),      # a chunk of sixteen input channels and one more
+    (16, (40, 130), (8, 8), "tanh", "avg", 9),      # norms of both kinds on 8x8 planes
+    (24, (64, 16), (4, 8), "relu", "max", 7),       # two images of a tile, a ragged last tile
+    (32, (64, 10), (4, 4), "relu", "avg", 13),      # four images of a tile; batch sums over a ragged last run
+    (16, (160, 32), (8, 4), "tanh", "max", 1),
+])
+def test_convolutions_on_the_bf16_matrix_units(cin, widths, plane, act, pool, batch):
+    from paper_2010_09063_amd import DpStep
+    h, w = plane
+    layers, c = [], cin
+    for d in widths:
+        layers.append(W.conv2d(c, d, 3, stride=1, pad=1, act=act))
+        c = d
+    layers += [W.maxpool2d(2, 2) if pool == "max" else W.avgpool2d(2, 2), W.dense(c * (h // 2) * (w // 2), 3)]
+    m = W.model(W.image_input(cin, h, w), layers, 3)
+    rng = np.random.default_rng(h * w + cin)
+    x, y = W.make_inputs(m, batch, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.3)
+    st = DpStep(m, batch)
+    plan = st.dp_step_describe_plan()
+    assert any(v.startswith("split") for l in range(len(widths)) for v in plan[l].values()), plan
+    _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} {act} {pool} B{batch}", stepper=st)
+    st = DpStep(m, batch, no_stored_gradients=1)
+    _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} recomputed", stepper=st)
