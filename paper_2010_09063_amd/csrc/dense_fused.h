@@ -614,24 +614,9 @@ __device__ __forceinline__ void sg_stash(float *T, int r0, int R, bool ones, int
 // A launch may carry a second product of the same operand layouts (the two clipped sums of a two-layer network):
 // rows ny0 and up of the grid are its tiles.
 template <bool A_KC, bool VEC, int NW>
-__global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGemmArgs p0, const SmallGemmArgs p1, int ny0) {
-  extern __shared__ float sg_lds[]; // per wave: A slice [k][m], B slice [k][n]; after the K loop: the wave's partial tile
+__device__ __forceinline__ void sg_tile(const SmallGemmArgs &a, float *sg_lds, int tm, int tn) {
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lk = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool second = (int)blockIdx.y >= ny0;
-  const SmallGemmArgs &a = second ? p1 : p0;
-  int tm = blockIdx.x, tn = (int)blockIdx.y - (second ? ny0 : 0);
-  if (!second) {
-    // Workgroups go to the eight XCDs in turn, each with an L2 of its own: XCD x takes a run of consecutive tiles of
-    // the list "panels of eight tile columns, row by row inside a panel", a compact block of the output, so that it
-    // reads a few row strips of A and column strips of B instead of all of one operand.
-    const int gx = gridDim.x, T = gx * ny0, L = blockIdx.x + gx * blockIdx.y;
-    const int xcd = L & 7, i = L >> 3, qn = T >> 3, rn = T & 7;
-    const int t = xcd * qn + min(xcd, rn) + i;
-    const int p = t / (gx * 8), rem = t - p * (gx * 8), w = min(8, ny0 - 8 * p);
-    tm = rem / w;
-    tn = 8 * p + (rem - tm * w);
-  }
   const int m0 = tm * 32, n0 = tn * 32;
   const int Mtot = a.M + (a.a_ones ? 1 : 0);
   if (m0 >= Mtot) return; // (the grid is as wide as the larger of the two products; uniform, before any barrier)
@@ -688,10 +673,9 @@ __global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGe
       float v[NW];
 #pragma unroll
       for (int w = 0; w < NW; ++w) v[w] = rp[w * (2 * 32 * SG_LD)];
-#pragma unroll
-      for (int h = 1; h < NW; h *= 2) // a fixed tree: (0+1) + (2+3) ...
-#pragma unroll
-        for (int w = 0; w + h < NW; w += 2 * h) v[w] += v[w + h];
+      // a fixed tree: (0+1) + (2+3) ... (written out: as a loop over the distance it is not unrolled, and v is in scratch)
+      static_assert(NW == 8, "the sum of the partial tiles is written out for eight waves");
+      v[0] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
       float r = v[0];
       if (a.bias) r += a.bias[n];
       r = act_apply(a.act, r);
@@ -700,6 +684,27 @@ __global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGe
       else a.C_ones[n] = r;
     }
   }
+}
+
+template <bool A_KC, bool VEC, int NW>
+__global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGemmArgs p0, const SmallGemmArgs p1, int ny0) {
+  extern __shared__ float sg_lds[]; // per wave: A slice [k][m], B slice [k][n]; after the K loop: the wave's partial tile
+  const bool second = (int)blockIdx.y >= ny0;
+  int tm = blockIdx.x, tn = (int)blockIdx.y - (second ? ny0 : 0);
+  if (!second) {
+    // Workgroups go to the eight XCDs in turn, each with an L2 of its own: XCD x takes a run of consecutive tiles of
+    // the list "panels of eight tile columns, row by row inside a panel", a compact block of the output, so that it
+    // reads a few row strips of A and column strips of B instead of all of one operand.
+    const int gx = gridDim.x, T = gx * ny0, L = blockIdx.x + gx * blockIdx.y;
+    const int xcd = L & 7, i = L >> 3, qn = T >> 3, rn = T & 7;
+    const int t = xcd * qn + min(xcd, rn) + i;
+    const int p = t / (gx * 8), rem = t - p * (gx * 8), w = min(8, ny0 - 8 * p);
+    tm = rem / w;
+    tn = 8 * p + (rem - tm * w);
+  }
+  // (the tile is compiled for each product: selected by a flag, the arguments pass through scratch memory)
+  if (second) sg_tile<A_KC, VEC, NW>(p1, sg_lds, tm, tn);
+  else sg_tile<A_KC, VEC, NW>(p0, sg_lds, tm, tn);
 }
 
 #define SG_WAVES 8
