@@ -28,7 +28,6 @@
 #include "lstm_wgrad.h"
 #include "operands.h"
 #include "problems.h"
-#include "rows_gemm.h"
 #include "split_conv.h"
 #include "split_rows.h"
 #include "split_wgrad.h"
@@ -91,7 +90,7 @@ struct Layer {
   // lstm
   bool lstm_wg = false; // per-example weight gradient by lstm_wgrad_kernel (16x16 MFMA blocks, one example per two workgroups)
   float *gates = nullptr, *cs = nullptr, *hs = nullptr;
-  void *frag_dx = nullptr; // split W_ih^T of the input gradient
+  void *frag_x = nullptr, *frag_dx = nullptr; // split W_ih of the input projection, split W_ih^T of the input gradient
   int T = 0, Din = 0, H = 0;
 };
 
@@ -703,7 +702,7 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
     if (rc != DP_OK) break;
     const bool emb = l.d.kind == DP_EMBEDDING;
     if (!c->bag) { // (bag_net_kernel keeps them in one workgroup)
-      rc = dev_alloc(c, &l.a, mb * l.out_size); // embedding: the gathered rows x[B, T, D]
+      rc = dev_alloc(c, &l.a, mb * l.out_size + (emb ? SPLIT_ROWS_SLACK : 0)); // embedding: the gathered rows x[B, T, D]
       if (rc == DP_OK) rc = dev_alloc(c, &l.g, mb * std::max<long>(l.out_size, &l == &c->L.back() ? 16 : 0)); // (the loss gradient: rows of up to 16 floats)
     }
     if (rc == DP_OK && l.d.kind == DP_MAXPOOL2D) rc = dev_alloc(c, &l.arg, mb * l.out_size);
@@ -812,9 +811,15 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
     }
     if (rc == DP_OK && (l.d.kind == DP_LSTM_LAST || l.d.kind == DP_LSTM_SEQ)) {
       rc = dev_alloc(c, &l.gates, mb * l.T * 4 * l.H + SPLIT_ROWS_SLACK);
-      if (rc == DP_OK && !c->opt.no_rows_gemm) {
-        rc = dev_alloc(c, (char **)&l.frag_dx, split_rows_frag_bytes(4 * l.H, l.Din));
-      }
+      // the input projection and the input gradient with the weights in registers; wider ones on the tiled contraction
+      auto in_registers = [&](int K, int N) {
+        if (!split_rows_fits(K, N) || c->opt.no_rows_gemm) return false;
+        if (K <= SPLIT_ROWS_K1 || split_rows_enable()) return true;
+        (void)hipGetLastError(); // its LDS size refused
+        return false;
+      };
+      if (rc == DP_OK && in_registers(l.Din, 4 * l.H)) rc = dev_alloc(c, (char **)&l.frag_x, split_rows_frag_bytes(l.Din, 4 * l.H));
+      if (rc == DP_OK && in_registers(4 * l.H, l.Din)) rc = dev_alloc(c, (char **)&l.frag_dx, split_rows_frag_bytes(4 * l.H, l.Din));
       if (rc == DP_OK) rc = dev_alloc(c, &l.cs, mb * l.T * std::max(l.H, l.Din)); // (also the embedding's pair rows)
       if (l.d.kind == DP_LSTM_SEQ) l.hs = l.a; // the hidden states are the layer's output
       else if (rc == DP_OK) rc = dev_alloc(c, &l.hs, mb * l.T * l.H);
@@ -1306,16 +1311,18 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
       case DP_LSTM_LAST:
       case DP_LSTM_SEQ: {
         const int G = 4 * l.H;
-        if (rows_gemm_fits(l.Din, G, 4, 1) && aligned16(in) && !c->opt.no_rows_gemm) {
-          // gates = x W_ih + b with W_ih held in registers by persistent workgroups
-          RowsGemmArgs a{};
-          a.A = in; a.W = W; a.w_sk = G; a.w_sn = 1; a.bias = W + (long)l.Din * G + (long)l.H * G; a.C = l.gates;
+        if (l.frag_x || l.frag_dx) {
+          SplitWeights w[2];
+          int nw = 0;
+          if (l.frag_x) w[nw++] = {W, G, 1, l.Din, G, l.frag_x};
+          if (l.frag_dx) w[nw++] = {W, 1, G, G, l.Din, l.frag_dx};
+          Ln(LL("lstm_weights"), dim3(1), dim3(64), [&](hipStream_t st) { split_rows_prepare(st, w, nw); });
+        }
+        if (l.frag_x) { // gates = x W_ih + b
+          SplitRowsArgs a{};
+          a.A = in; a.lda = l.Din; a.frag = l.frag_x; a.bias = W + (long)l.Din * G + (long)l.H * G; a.C = l.gates; a.ldc = G;
           a.M = (long)B * l.T; a.K = l.Din; a.N = G;
-          const long tiles = (a.M + 31) / 32;
-          dim3 grid((unsigned)std::min<long>(tiles, 256)), block(RG_THREADS);
-          Ln(LL("lstm_xproj"), grid, block, [&](hipStream_t st) {
-            hipLaunchKernelGGL((rows_gemm_kernel<4, 1, 2>), grid, block, rows_gemm_lds_bytes(2), st, a);
-          });
+          Ln(LL("lstm_xproj"), dim3(1), dim3(SPLIT_ROWS_THREADS), [&](hipStream_t st) { split_rows_launch(st, a); });
         } else {
         auto run = [&](auto vt) {
           constexpr bool V = decltype(vt)::value;
@@ -1682,12 +1689,10 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
                               OpKMajor<true, false>::can_vec(l.gates, G, (long)l.T * G, G), run);
         }
         if (l.frag_dx) { // dx = dgates W_ih^T: gradient w.r.t. the embedding outputs
-          const SplitWeights w = {W, 1, G, G, l.Din, l.frag_dx};
-          Ln(LL("lstm_weights"), dim3(1), dim3(64), [&](hipStream_t st) { split_rows_prepare(st, &w, 1); });
           SplitRowsArgs a{};
           a.A = l.gates; a.lda = G; a.frag = l.frag_dx; a.bias = nullptr; a.C = prev->g; a.ldc = l.Din;
           a.M = (long)B * l.T; a.K = G; a.N = l.Din;
-          Ln(LL("lstm_dx"), dim3(1), dim3(256), [&](hipStream_t st) { split_rows_launch(st, a); });
+          Ln(LL("lstm_dx"), dim3(1), dim3(SPLIT_ROWS_THREADS), [&](hipStream_t st) { split_rows_launch(st, a); });
         } else {
           auto run = [&](auto vt) {
             constexpr bool V = decltype(vt)::value;

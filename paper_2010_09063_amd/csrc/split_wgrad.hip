@@ -70,8 +70,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
       for (int j = 0; j < 4; ++j) v[4 * q + j] = t[j];
     }
   };
-  for (int e = ex0; e < ex1; e += EX_BAND) {
-    for (int band = 0; band < bands; ++band) {
+  auto multiply = [&]() { // this wave's k steps of the staged band
+#pragma unroll
+    for (int q = 0; q < G::KSTEPS / KW; ++q) {
+      const int k = kp + q * KW;
+      const int rho = k / S, s = k - rho * S;
+      SbFrag yf[1];
+      const char *yp = ys + db * G::YBYTES + (((2 * rho + lk) * S + s) * 3 * 32 + li) * 16;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) yf[0].p[p] = *reinterpret_cast<const sb_u32x4 *>(yp + p * 512);
+      // (4-wide: k step = image; the half lk starts at row 2 lk, so its pair for tap row ky is 2 lk + ky of the five)
+      const char *xp = xs + (((W_ == 4 ? rho * 5 + 2 * lk : 2 * rho + lk) * G::PHI + (W_ == 4 ? 0 : s)) * 3 * 32 + li) * 16;
+#pragma unroll
+      for (int ky = 0; ky < 3; ++ky) {
+        SbFrag xf[3];
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+          for (int p = 0; p < 3; ++p)
+            xf[kx].p[p] = *reinterpret_cast<const sb_u32x4 *>(xp + ((ky * G::PHI + kx) * 3 + p) * 512);
+        sb_mfma(yf, xf, *reinterpret_cast<sb_f32x16 (*)[1][3]>(&acc[3 * ky]));
+      }
+    }
+  };
+  if constexpr (W_ == 4) {
+    for (int e = ex0; e < ex1; e += EX_BAND) {
       __syncthreads(); // the last band's operands have been read
       // ---- input rows: item (row, channel), channels along the lanes
 #pragma unroll
@@ -79,43 +102,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
         const int it = tid + 256 * q, c = it & 31, r = it >> 5;
         if (G::XR * 32 % 256 != 0 && r >= G::XR) break; // (a whole wave or half of one)
         char *dst = xs + (r * G::PHI * 3 * 32 + c) * 16;
-        if constexpr (W_ == 4) {
-          const int im = r / 5, y = r - im * 5 - 1; // rows y and y + 1 of the pair
-          const bool ok = c0 + c < C && e + im < ex1;
-          const float *p = a.x + ((long)(ok ? e + im : 0) * C + (ok ? c0 + c : 0)) * HW;
-          float u[4], v[4];
-          row_load(p + max(y, 0) * 4, u);
-          row_load(p + min(y + 1, 3) * 4, v);
+        const int im = r / 5, y = r - im * 5 - 1; // rows y and y + 1 of the pair
+        const bool ok = c0 + c < C && e + im < ex1;
+        const float *p = a.x + ((long)(ok ? e + im : 0) * C + (ok ? c0 + c : 0)) * HW;
+        float u[4], v[4];
+        row_load(p + max(y, 0) * 4, u);
+        row_load(p + min(y + 1, 3) * 4, v);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) { u[j] = ok && y >= 0 ? u[j] : 0.f; v[j] = ok && y < 3 ? v[j] : 0.f; }
+        for (int j = 0; j < 4; ++j) { u[j] = ok && y >= 0 ? u[j] : 0.f; v[j] = ok && y < 3 ? v[j] : 0.f; }
 #pragma unroll
-          for (int phi = 0; phi < 3; ++phi) {
-            float g[8];
+        for (int phi = 0; phi < 3; ++phi) {
+          float g[8];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int x = phi - 1 + j;
-              g[j] = x >= 0 && x < 4 ? u[x < 0 ? 0 : (x > 3 ? 3 : x)] : 0.f;
-              g[4 + j] = x >= 0 && x < 4 ? v[x < 0 ? 0 : (x > 3 ? 3 : x)] : 0.f;
-            }
-            put(dst + phi * 3 * 512, g);
+          for (int j = 0; j < 4; ++j) {
+            const int x = phi - 1 + j;
+            g[j] = x >= 0 && x < 4 ? u[x < 0 ? 0 : (x > 3 ? 3 : x)] : 0.f;
+            g[4 + j] = x >= 0 && x < 4 ? v[x < 0 ? 0 : (x > 3 ? 3 : x)] : 0.f;
           }
-        } else {
-          const int y = band * G::TR + r - 1;
-          const bool ok = c0 + c < C && y >= 0 && y < H;
-          float u[W_];
-          row_load(a.x + ((long)e * C + (ok ? c0 + c : 0)) * HW + (ok ? y * W_ : 0), u);
-#pragma unroll
-          for (int j = 0; j < W_; ++j) u[j] = ok ? u[j] : 0.f;
-#pragma unroll
-          for (int phi = 0; phi < G::PHI; ++phi) {
-            float g[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const int x = phi - 1 + S * j;
-              g[j] = x >= 0 && x < W_ ? u[x < 0 ? 0 : (x >= W_ ? W_ - 1 : x)] : 0.f;
-            }
-            put(dst + phi * 3 * 512, g);
-          }
+          put(dst + phi * 3 * 512, g);
         }
       }
       // ---- dy rows: item (block of output channels, row, channel)
@@ -124,11 +128,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
         const int it = tid + 256 * q, d = it & 31, rr = it >> 5, b = rr / G::YR, r = rr - b * G::YR;
         if (DBW * G::YR * 32 % 256 != 0 && b >= DBW) break;
         char *dst = ys + b * G::YBYTES + (r * S * 3 * 32 + d) * 16;
-        const int im = W_ == 4 ? r >> 1 : 0;
+        const int im = r >> 1;
         const bool ok = d0 + 32 * b + d < D && e + im < ex1;
         const float f = ok ? (NORM ? 1.f : a.scale[e + im]) : 0.f;
-        constexpr int N = W_ == 4 ? 8 : W_;
-        const float *p = a.dy + ((long)(ok ? e + im : 0) * D + (ok ? d0 + 32 * b + d : 0)) * HW + (W_ == 4 ? (r & 1) * 8 : (band * G::TR + r) * W_);
+        constexpr int N = 8;
+        const float *p = a.dy + ((long)(ok ? e + im : 0) * D + (ok ? d0 + 32 * b + d : 0)) * HW + (r & 1) * 8;
         float u[N];
 #pragma unroll
         for (int t = 0; t < N / 4; ++t) {
@@ -147,33 +151,88 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
         for (int s = 0; s < S; ++s) {
           float g[8];
 #pragma unroll
-          for (int j = 0; j < 8; ++j) g[j] = W_ == 4 ? u[j] : u[s + S * j];
+          for (int j = 0; j < 8; ++j) g[j] = u[j];
           put(dst + s * 3 * 512, g);
         }
       }
       __syncthreads();
-      // ---- this wave's k steps
+      multiply();
+    }
+  } else {
+    // One list of rows to stage, the input's and then dy's, whole rows (W_ registers) per thread; a wave's items are of one
+    // kind.  The next band's rows travel in registers during the multiplies (without that a band waited for memory
+    // between its barriers: 60 us for 48 -> 48 channels on 32x32 planes at 61 examples).
+    constexpr int XI = G::XR * 32, ALL = XI + DBW * G::YR * 32, IT = (ALL + 255) / 256;
+    static_assert(XI % 64 == 0, "a wave stages rows of one kind");
+    float raw[IT][W_];
+    auto fetch = [&](int e, int band) {
 #pragma unroll
-      for (int q = 0; q < G::KSTEPS / KW; ++q) {
-        const int k = kp + q * KW;
-        const int rho = k / S, s = k - rho * S;
-        SbFrag yf[1];
-        const char *yp = ys + db * G::YBYTES + (((2 * rho + lk) * S + s) * 3 * 32 + li) * 16;
+      for (int q = 0; q < IT; ++q) {
+        const int it = tid + 256 * q;
+        const float *p = a.x; // (always a valid address)
+        if (it < XI) {
+          const int c = c0 + (it & 31), y = band * G::TR + (it >> 5) - 1;
+          if (c < C && y >= 0 && y < H) p = a.x + ((long)e * C + c) * HW + y * W_;
+        } else {
+          const int rr = (it - XI) >> 5, b = rr / G::YR, d = d0 + 32 * b + (it & 31), y = band * G::TR + rr - b * G::YR;
+          if (b < DBW && d < D) p = a.dy + ((long)e * D + d) * HW + y * W_;
+        }
+        row_load(p, raw[q]);
+      }
+    };
+    auto stash = [&](int e, int band) {
+      const float f = NORM ? 1.f : a.scale[e];
 #pragma unroll
-        for (int p = 0; p < 3; ++p) yf[0].p[p] = *reinterpret_cast<const sb_u32x4 *>(yp + p * 512);
-        // (4-wide: k step = image; the half lk starts at row 2 lk, so its pair for tap row ky is 2 lk + ky of the five)
-        const char *xp = xs + (((W_ == 4 ? rho * 5 + 2 * lk : 2 * rho + lk) * G::PHI + (W_ == 4 ? 0 : s)) * 3 * 32 + li) * 16;
+      for (int q = 0; q < IT; ++q) {
+        const int it = tid + 256 * q;
+        if (it < XI) {
+          const int c = it & 31, r = it >> 5, y = band * G::TR + r - 1;
+          const bool ok = c0 + c < C && y >= 0 && y < H;
+          char *dst = xs + (r * G::PHI * 3 * 32 + c) * 16;
 #pragma unroll
-        for (int ky = 0; ky < 3; ++ky) {
-          SbFrag xf[3];
+          for (int phi = 0; phi < G::PHI; ++phi) {
+            float g[8];
 #pragma unroll
-          for (int kx = 0; kx < 3; ++kx)
+            for (int j = 0; j < 8; ++j) {
+              const int x = phi - 1 + S * j;
+              g[j] = x >= 0 && x < W_ && ok ? raw[q][x < 0 ? 0 : (x >= W_ ? W_ - 1 : x)] : 0.f;
+            }
+            put(dst + phi * 3 * 512, g);
+          }
+        } else if (it < ALL) {
+          const int rr = (it - XI) >> 5, b = rr / G::YR, r = rr - b * G::YR, d = it & 31;
+          const bool ok = d0 + 32 * b + d < D;
+          char *dst = ys + b * G::YBYTES + (r * S * 3 * 32 + d) * 16;
+          float sum = 0.f;
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
-              xf[kx].p[p] = *reinterpret_cast<const sb_u32x4 *>(xp + ((ky * G::PHI + kx) * 3 + p) * 512);
-          sb_mfma(yf, xf, *reinterpret_cast<sb_f32x16 (*)[1][3]>(&acc[3 * ky]));
+          for (int j = 0; j < W_; ++j) {
+            raw[q][j] = ok ? (NORM ? raw[q][j] : raw[q][j] * f) : 0.f;
+            sum += raw[q][j];
+          }
+#pragma unroll
+          for (int bb = 0; bb < DBW; ++bb) bsum[bb][0] += DBW == 1 || bb == b ? sum : 0.f;
+#pragma unroll
+          for (int s = 0; s < S; ++s) {
+            float g[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) g[j] = raw[q][s + S * j];
+            put(dst + s * 3 * 512, g);
+          }
         }
       }
+    };
+    int e = ex0, band = 0;
+    fetch(e, band);
+    while (e < ex1) {
+      __syncthreads(); // the last band's operands have been read
+      stash(e, band);
+      __syncthreads();
+      int en = e, bn = band + 1;
+      if (bn == bands) { bn = 0; ++en; }
+      fetch(min(en, ex1 - 1), bn); // (past the last band: read again, unused)
+      __builtin_amdgcn_sched_barrier(0);
+      multiply();
+      e = en; band = bn;
     }
   }
 

@@ -77,3 +77,22 @@ def test_convolutions_on_the_bf16_matrix_units(cin, widths, plane, act, pool, ba
     _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} {act} {pool} B{batch}", stepper=st)
     st = DpStep(m, batch, no_stored_gradients=1)
     _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} recomputed", stepper=st)
+
+
+@pytest.mark.parametrize("out", ["last", "seq"])
+@pytest.mark.parametrize("dim,hidden,seq,batch", [
+    (1, 1, 1, 1),        # the smallest of everything
+    (17, 33, 5, 7),      # rows that start on 4 bytes; K one past a step, N past a block of columns
+    (112, 104, 33, 3),   # the widest that the projection's and the input gradient's waves hold; a ragged last tile of rows
+    (113, 105, 3, 5),    # one past both: the tiled contraction
+    (128, 16, 4, 9),     # the projection with its K in two halves
+    (64, 56, 140, 3),    # several tiles per workgroup's run would need more rows: stored per-example gradients
+])
+def test_lstm_products_with_weights_in_registers(dim, hidden, seq, batch, out):
+    layers = [W.embedding(40, dim), (W.lstm_last if out == "last" else W.lstm_seq)(dim, hidden)]
+    layers += ([W.seq_mean()] if out == "seq" else []) + [W.dense(hidden, 3)]
+    m = W.model(W.token_input(seq), layers, 3)
+    rng = np.random.default_rng(dim + hidden)
+    x, y = W.make_inputs(m, batch, rng, zipf_exponent=0.8)
+    theta = W.init_params(m, rng, bias_scale=0.3) * np.float32(2)
+    _check_all_regimes(m, x, y, theta, f"lstm {out} D{dim} H{hidden} T{seq} B{batch}")
