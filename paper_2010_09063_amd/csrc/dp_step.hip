@@ -25,10 +25,10 @@
 #include "emb_pairs.h"
 #include "kernels_misc.h"
 #include "kernels_seq.h"
-#include "lstm_wgrad.h"
 #include "operands.h"
 #include "problems.h"
 #include "split_conv.h"
+#include "split_lstm.h"
 #include "split_rows.h"
 #include "split_wgrad.h"
 
@@ -88,7 +88,7 @@ struct Layer {
   // embedding: counting-sort workspace of the clipped sum
   int *e_count = nullptr, *e_start = nullptr, *e_chunk0 = nullptr, *e_cursor = nullptr, *e_list = nullptr;
   // lstm
-  bool lstm_wg = false; // per-example weight gradient by lstm_wgrad_kernel (16x16 MFMA blocks, one example per two workgroups)
+  bool lstm_wg = false; // weight gradient on the bf16 matrix units (split_lstm.hip)
   float *gates = nullptr, *cs = nullptr, *hs = nullptr;
   void *frag_x = nullptr, *frag_dx = nullptr; // split W_ih of the input projection, split W_ih^T of the input gradient
   int T = 0, Din = 0, H = 0;
@@ -317,6 +317,9 @@ static void plan_direct_conv(Layer &l, int maxB, const dp_plan_options &opt) {
   // weight gradient
   const bool flat = g.C * 9 <= 32 && g.D <= 32;
   if (flat) l.split_wg = false;
+  // (one workgroup per example makes the Gram kernel of 8x8 planes slow at small batches: 192 -> 192 channels at 61
+  // examples 40 against 32 us, 128 -> 128 at 256 examples 30 against 46)
+  if (l.split_wg && l.gram && g.OH == 8 && maxB < 96 && !l.wino_wgu) l.gram = false;
   l.split_norm = l.split_wg && !l.gram && !l.wino_wgu;
   if ((g.C >= 16 || flat) && (g.OW & 3) == 0 && (g.W & 3) == 0) {
     int db = g.D <= 32 ? 1 : (g.D <= 64 ? 2 : 4);
@@ -568,10 +571,10 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
       if (!is_seq || l.d.hidden < 1 || l.d.in_features != curH) { rc = DP_EINVAL; break; }
       if (l.d.hidden > 128 || i == 0 || model->layers[i - 1].kind != DP_EMBEDDING) { rc = DP_EUNSUPPORTED; break; }
       l.T = curC; l.Din = curH; l.H = l.d.hidden;
-      l.lstm_wg = lstm_wgrad_fits(l.Din, l.H, l.T) && !c->opt.no_lstm_wgrad;
+      l.lstm_wg = split_lstm_fits(l.Din, l.H) && !c->opt.no_lstm_wgrad;
       l.p_count = (long)l.Din * 4 * l.H + (long)l.H * 4 * l.H + 4 * l.H;
       l.max_slots = ceil_div(l.Din + l.H + 1, 32) * ceil_div(4 * l.H, 32);
-      if (l.lstm_wg) l.max_slots = std::max(l.max_slots, LWG_SLOTS);
+      if (l.lstm_wg) l.max_slots = std::max(l.max_slots, SPLIT_LSTM_SLOTS);
       if (l.d.kind == DP_LSTM_SEQ) {
         if (i + 1 >= model->n_layers || model->layers[i + 1].kind != DP_SEQ_MEAN) { rc = DP_EUNSUPPORTED; break; }
         l.outC = l.T; l.outH = l.H; l.outW = 1; // stays a sequence
@@ -620,8 +623,7 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
   {
     bool any = false;
     for (auto &l : c->L) any = any || l.lstm_wg;
-    if (any && hipFuncSetAttribute((const void *)lstm_wgrad_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)lstm_wgrad_lds_bytes()) != hipSuccess) {
+    if (any && !split_lstm_enable()) {
       (void)hipGetLastError();
       for (auto &l : c->L) l.lstm_wg = false;
     }
@@ -1661,17 +1663,11 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
         const int G = 4 * l.H;
         const float *Whh = W + (long)l.Din * G;
         LSTM_DISPATCH(launch_lstm_bwd, l.H, Ln, l, Whh, B, LL("lstm_bwd"));
-        if (priv && l.lstm_wg && aligned16(lin) && aligned16(l.hs) && aligned16(l.gates)) {
-          LstmWgArgs a{};
+        if (priv && l.lstm_wg) {
+          SplitLstmArgs a{};
           a.x = lin; a.hs = l.hs; a.dg = l.gates; a.slots = c->slots; a.slot_stride = slot_stride; a.slot0 = slot_next;
           a.gstore = l.gst; a.gstride = l.p_count; a.B = B; a.T = l.T; a.Din = l.Din; a.H = l.H;
-          const int halves = G > LWG_NH * 16 ? 2 : 1;
-          slot_next += halves * 8; // one partial per wave
-          // persistent workgroups, one per CU (their LDS leaves room for no second one): 128 x 2 halves
-          dim3 grid(std::min(B, 256 / halves), halves), block(LWG_THREADS);
-          Ln(LL("lstm_wgrad_norm"), grid, block, [&](hipStream_t st) {
-            hipLaunchKernelGGL(lstm_wgrad_kernel, grid, block, lstm_wgrad_lds_bytes(), st, a);
-          });
+          Ln(LL("lstm_wgrad_norm"), dim3(1), dim3(512), [&](hipStream_t st) { slot_next += split_lstm_norm(st, a); });
         } else if (priv) {
           auto run = [&](auto vt) {
             constexpr bool V = decltype(vt)::value;
@@ -1887,6 +1883,13 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
             hipLaunchKernelGGL(weighted_sum_kernel, grid, block, 0, st, (const float *)l.gst, l.p_count, sc, l.part,
                                l.pstride, l.gorder, B, eps);
           });
+          break;
+        }
+        if (l.lstm_wg) {
+          SplitLstmArgs a{};
+          a.x = lin; a.hs = l.hs; a.dg = l.gates; a.scale = sc; a.part = l.part; a.part_stride = l.pstride;
+          a.B = B; a.T = l.T; a.Din = l.Din; a.H = l.H;
+          Ln(LL("lstm_clipped_sum"), dim3(1), dim3(512), [&](hipStream_t st) { nsplit = split_lstm_sum(st, a, l.max_split); });
           break;
         }
         auto run = [&](auto vt) {
