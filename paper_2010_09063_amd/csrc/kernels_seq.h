@@ -4,8 +4,8 @@
 // The recurrence is a chain of T dependent (examples x H)*(H x 4H) products; per step it is far too small for a
 // tiled contraction, and examples are independent.  Each workgroup of LSTM_THREADS threads therefore owns one
 // example for the whole sequence and keeps W_hh in registers (forward: a quarter of the rows for the four gate
-// columns of one hidden unit per thread, summed over a quad of lanes with DPP moves; backward: one gate's part
-// of a row per thread), so a step costs no weight traffic at all: only the hidden state goes through LDS
+// columns of one hidden unit per thread, summed over a quad of lanes with DPP moves; backward: a sixteenth of the
+// columns for four hidden units per thread, summed over a row of lanes), so a step costs no weight traffic at all: only the hidden state goes through LDS
 // (broadcast reads).  A step is a chain of dependent phases, so what bounds it is latency: eight waves per
 // example (two per SIMD) overlap each other's LDS reads, and every global load is issued a whole step before its
 // value is used.  The input projection x_t W_ih + b and the input / weight gradients are hoisted out of the loop
@@ -150,6 +150,13 @@ __device__ __forceinline__ float quad_bcast(float v) { // every lane of the quad
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), Q * 0x55, 0xF, 0xF, true));
 }
 
+__device__ __forceinline__ float row_swap8(float v) { // the halves of a row of sixteen lanes change places
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float half_mirror(float v) { // each eight lanes in reverse order
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));
+}
+
 // Forward.  gates: in  x_t W_ih + b for every (b, t); out activated i, f, g, o.
 // hs, cs: [B, T, H] hidden and cell states; hlast [B, H] = h_T, or the mean of every h_t (mean != 0: the sequence mean
 // that follows the layer in the Appendix B network costs one addition a step here and was a launch of 33 us at 128
@@ -243,86 +250,109 @@ __global__ __launch_bounds__(LSTM_THREADS) void lstm_fwd_kernel(float *__restric
 }
 
 // Back-propagation through time.  gates: in activated gates, out d(loss)/d(gate pre-activations).
-// One workgroup per example; thread (k = tid % 128, q = tid / 128) owns W_hh[k][qH .. qH + H), the columns of
-// gate q, and computes that gate's share of dL/dh_{t-1}[k].
+// One workgroup per example.  Its product dL/dh_{t-1} = W_hh dgates_t is dealt out as (four hidden units kk = tid / 16, a
+// sixteenth s = tid % 16 of the 4H columns).  The sixteen partial sums of the four units are added so that the unit
+// 4 kk + s / 4 ends up in the quad of lanes s / 4, where lane s % 4 makes that gate's gradient of it: a step is product,
+// sum, gate gradient, LDS write and one barrier, and everything else that the step needs is there before its product.
+// (With a gate's part of one unit per thread the sums went through LDS to the two waves that updated the cells, two
+// barriers a step.)  256 steps, H = 100: 222 -> 173 us at 128 examples, where a step's chain of latencies bounds it;
+// 306 -> 294 us at 512, two examples per compute unit, where the issue of 4 waves x (100 multiply-adds + 60 other
+// instructions) per SIMD does.
 // dh_out is [B, H].  SEQ = false: the gradient of h_T, which is all that the loss sees.  SEQ = true: the gradient of the
 // mean over every h_t: each step adds its share dh_out / T to what the later steps send back.
 template <int HP, bool SEQ>
 __global__ __launch_bounds__(LSTM_THREADS, (HP <= 100 ? 4 : 2)) void lstm_bwd_kernel(float *__restrict__ gates, const float *__restrict__ cs,
                                                                  const float *__restrict__ Whh,
                                                                  const float *__restrict__ dh_out, int B, int T, int H) {
-  __shared__ __attribute__((aligned(16))) float dg_s[4 * HP]; // gate-major, each gate padded to HP (zeros)
-  __shared__ float part_s[4][128];
+  constexpr int QC = HP / 4;                // columns per thread: the flat index g * HP + j cut into sixteen
+  constexpr int QCP = ((QC + 3) / 4 | 1) * 4; // a sixteenth's stride in LDS: 16-byte reads, an odd number of them apart (no bank twice)
+  __shared__ __attribute__((aligned(16))) float dg_s[2][16 * QCP];
   const int tid = threadIdx.x;
   const int b = blockIdx.x; // the grid is exactly B workgroups
   const int G = 4 * H;
-  const int k = tid & 127, q = tid >> 7;
-  float w[HP];
+  const int kk = tid >> 4, s16 = tid & 15, q = tid & 3;
+  const int u = 4 * kk + (s16 >> 2);
+  const bool unit_ok = u < H;
+  const int ul = unit_ok ? u : 0;
+  float w[4][QC];
 #pragma unroll
-  for (int j = 0; j < HP; ++j) w[j] = (k < H && j < H) ? Whh[(long)k * G + q * H + j] : 0.f;
-  for (int i = tid; i < 4 * HP; i += LSTM_THREADS) dg_s[i] = 0.f;
-  for (int i = tid; i < 4 * 128; i += LSTM_THREADS) (&part_s[0][0])[i] = 0.f;
-  const bool upd_thread = tid < H;
-  const int ur = upd_thread ? tid : 0;
-  const unsigned urb = 4u * ur;
+  for (int i = 0; i < QC; ++i) {
+    const int f = s16 * QC + i, g = f / HP, j = f - g * HP;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) w[m][i] = (4 * kk + m < H && j < H) ? Whh[(long)(4 * kk + m) * G + g * H + j] : 0.f;
+  }
+  for (int i = tid; i < 2 * 16 * QCP; i += LSTM_THREADS) (&dg_s[0][0])[i] = 0.f;
+  // the thread's gate column, its unit and the place of its gradient in LDS, in one register: the weights leave few
+  const unsigned where = (q * H + ul) | ul << 10 | ((4 * q + ul / QC) * QCP + ul % QC) << 18;
   float *const grow0 = gates + (long)b * T * G;
   const float *const crow0 = cs + (long)b * T * H;
-  const float *const drow0 = dh_out + (long)b * H;
-  // Operands of the step being processed, held by the cell-update threads only.  They are declared without a
-  // value and loaded and used inside the same branch: an initial value, a load under one branch used under
-  // another, or a loaded value copied into a second variable would each be waited for at once, not at the use.
-  float gi, gf, gg, go, cp, dh_own, ct;
+  float dh_own = dh_out[(long)b * H + ul];
+  if (SEQ) dh_own /= (float)T;
   float dc = 0.f;
-  if (upd_thread) {
-    const float *g = grow0 + (long)(T - 1) * G;
-    gi = lane_ld(g, urb); gf = lane_ld(g + H, urb); gg = lane_ld(g + 2 * H, urb); go = lane_ld(g + 3 * H, urb);
-    ct = lane_ld(crow0 + (long)(T - 1) * H, urb);
-    cp = lane_ld(crow0 + (long)max(T - 2, 0) * H, urb); // c_{t-1}; unused at t = 0
-    dh_own = lane_ld(drow0, urb);
-    if (SEQ) dh_own /= (float)T;
-  }
   __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the weight loads end here, not at their first use inside the loop
   __syncthreads();
-  for (int t = T - 1; t >= 0; --t) {
-    if (upd_thread) { // (the waves without a cell-update thread skip this)
-      // (lane offset re-materialised inside the loop: hoisted out of it, it would be widened to 64 bits)
-      unsigned urx = urb;
-      asm volatile("" : "+v"(urx));
-      // what the later steps send back (zero at the last step: part_s starts cleared) plus the loss's own share
-      float dh = (part_s[0][ur] + part_s[1][ur]) + (part_s[2][ur] + part_s[3][ur]);
-      if (SEQ || t == T - 1) dh += dh_own;
-      const float cprev = t > 0 ? cp : 0.f;
-      const float tc = fast_tanh(ct);
-      const float dct = dc + dh * go * (1.f - tc * tc);
-      const float d_o = dh * tc * go * (1.f - go);
-      const float d_i = dct * gg * gi * (1.f - gi);
-      const float d_f = dct * cprev * gf * (1.f - gf);
-      const float d_g = dct * gi * (1.f - gg * gg);
-      dc = dct * gf;
-      float *g = grow0 + (long)t * G;
-      lane_at(g, urx) = d_i; lane_at(g + H, urx) = d_f; lane_at(g + 2 * H, urx) = d_g; lane_at(g + 3 * H, urx) = d_o;
-      dg_s[ur] = d_i; dg_s[HP + ur] = d_f; dg_s[2 * HP + ur] = d_g; dg_s[3 * HP + ur] = d_o;
-      // operands of step t - 1 (row clamped at the first step) into the registers just freed; they land while
-      // the product below runs
-      const int tn = max(t - 1, 0);
-      const float *gn = grow0 + (long)tn * G;
-      gi = lane_ld(gn, urx); gf = lane_ld(gn + H, urx); gg = lane_ld(gn + 2 * H, urx); go = lane_ld(gn + 3 * H, urx);
-      ct = lane_ld(crow0 + (long)tn * H, urx); // (loaded again rather than copied from cp: see above)
-      cp = lane_ld(crow0 + (long)max(tn - 1, 0) * H, urx);
-    }
-    __syncthreads();
-    if (t > 0) {
-      float acc = 0.f; // (two waves per SIMD alternate, which covers the latency of the dependent chain)
+  // Step t with its activated gate, c_t and c_{t-1}; requests the gate of step t - 1 and c_{t-2} (rows clamped at 0).
+  // din is what step t + 1 wrote (zeros at the last step).
+  auto step = [&](const int t, const float v, const float ct, const float cp, float &vnext, float &cnext, const float *din,
+                  float *dout) {
+    unsigned at = where; // (taken apart inside the loop: hoisted, the offsets would be widened to 64 bits)
+    asm volatile("" : "+v"(at));
+    vnext = lane_ld(grow0 + (long)max(t - 1, 0) * G, 4 * (at & 1023));
+    cnext = lane_ld(crow0 + (long)max(t - 2, 0) * H, 4 * (at >> 10 & 255));
+    // beside dL/dh: a gate's gradient is dL/dc_t (output gate: dL/dh_t) times `k`, dL/dc_t = dc + dL/dh_t * a
+    const float gi = quad_bcast<0>(v), gf = quad_bcast<1>(v), gg = quad_bcast<2>(v), go = quad_bcast<3>(v);
+    const float tc = fast_tanh(ct);
+    const float a = go * (1.f - tc * tc);
+    const float cprev = t > 0 ? cp : 0.f;
+    float k = fmaf(-v, v, q == 2 ? 1.f : v); // the activation's derivative: 1 - v^2 of a tanh, v - v^2 of a sigmoid
+    const float k0 = q == 0 ? gg : gi, k1 = q == 1 ? cprev : tc;
+    k *= (q & 1) ? k1 : k0;
+    __builtin_amdgcn_sched_barrier(0);
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    const float *dq = din + s16 * QCP;
 #pragma unroll
-      for (int j = 0; j < HP; j += 4) {
-        const float4 d4 = *reinterpret_cast<const float4 *>(&dg_s[q * HP + j]);
-        acc = fmaf(d4.x, w[j], acc); acc = fmaf(d4.y, w[j + 1], acc);
-        acc = fmaf(d4.z, w[j + 2], acc); acc = fmaf(d4.w, w[j + 3], acc);
+    for (int i = 0; i + 4 <= QC; i += 4) {
+      const float4 d4 = *reinterpret_cast<const float4 *>(dq + i);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        acc[m] = fmaf(d4.x, w[m][i], acc[m]); acc[m] = fmaf(d4.y, w[m][i + 1], acc[m]);
+        acc[m] = fmaf(d4.z, w[m][i + 2], acc[m]); acc[m] = fmaf(d4.w, w[m][i + 3], acc[m]);
       }
-      part_s[q][k] = acc;
+      if (i % 8 == 4) __builtin_amdgcn_sched_barrier(0); // (all reads at once would take registers that the weights need)
+    }
+#pragma unroll
+    for (int i = QC & ~3; i < QC; ++i) {
+      const float dv = dq[i];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) acc[m] = fmaf(dv, w[m][i], acc[m]);
+    }
+    // sums: the halves of a row exchange two units each, then its quads one, then the quad adds up
+    const bool hi = s16 >= 8, odd = (s16 & 4) != 0;
+    const float r0 = (hi ? acc[2] : acc[0]) + row_swap8(hi ? acc[0] : acc[2]);
+    const float r1 = (hi ? acc[3] : acc[1]) + row_swap8(hi ? acc[1] : acc[3]);
+    float dh = (odd ? r1 : r0) + half_mirror(odd ? r0 : r1);
+    dh += quad_xor1(dh);
+    dh += quad_xor2(dh);
+    if (SEQ || t == T - 1) dh += dh_own;
+    const float dct = dc + dh * a;
+    const float d = (q == 3 ? dh : dct) * k;
+    dc = dct * gf;
+    if (unit_ok) {
+      asm volatile("" : "+v"(at));
+      dout[at >> 18] = d;
+      lane_at(grow0 + (long)t * G, 4 * (at & 1023)) = d;
     }
     __syncthreads();
+  };
+  float va = lane_ld(grow0 + (long)(T - 1) * G, 4 * (q * H + ul)), vb;
+  float c0 = lane_ld(crow0 + (long)(T - 1) * H, 4 * ul), c1 = lane_ld(crow0 + (long)max(T - 2, 0) * H, 4 * ul), c2;
+  int t = T - 1;
+  for (; t > 0; t -= 2) {
+    step(t, va, c0, c1, vb, c2, dg_s[0], dg_s[1]);
+    step(t - 1, vb, c1, c2, va, c1, dg_s[1], dg_s[0]);
+    c0 = c2;
   }
+  if (t == 0) step(0, va, c0, c1, vb, c2, dg_s[0], dg_s[1]);
 }
 
 // Embedding layer, per-example squared norm: row v of g_i is the sum of dx_{i,t}

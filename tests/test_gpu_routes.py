@@ -86,6 +86,8 @@ def test_convolutions_on_the_bf16_matrix_units(cin, widths, plane, act, pool, ba
     (112, 104, 33, 3),   # the widest that the projection's and the input gradient's waves hold; a ragged last tile of rows
     (113, 105, 3, 5),    # one past both: the tiled contraction
     (128, 16, 4, 9),     # the projection with its K in two halves
+    (9, 100, 2, 6),      # the recurrence's narrower padding filled, an even number of steps
+    (12, 128, 2, 3),     # its wider padding filled
     (64, 56, 140, 3),    # several tiles per workgroup's run would need more rows: stored per-example gradients
 ])
 def test_lstm_products_with_weights_in_registers(dim, hidden, seq, batch, out):
