@@ -56,6 +56,28 @@ static_assert(D2 * 32 * 4 <= CK2 * P2 && D1 * 64 * 4 <= CK2 * P2, "the K-split p
 constexpr int THREADS = 1024;
 } // namespace cnnf
 
+// Sums and maxima over the sixteen lanes of a row with DPP moves, and over a wave from the four rows: no LDS unit in the
+// chain (a shuffle is an LDS operation of about 60 cycles).  Every lane of the row gets the result; all lanes take part.
+template <int CTRL>
+__device__ __forceinline__ float cnn_dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float cnn_row_sum(float v) { // pairs, quads, the quads of a half, the halves
+  v += cnn_dpp<0xB1>(v); v += cnn_dpp<0x4E>(v); v += cnn_dpp<0x141>(v);
+  return v + cnn_dpp<0x140>(v);
+}
+__device__ __forceinline__ float cnn_row_max(float v) {
+  v = fmaxf(v, cnn_dpp<0xB1>(v)); v = fmaxf(v, cnn_dpp<0x4E>(v)); v = fmaxf(v, cnn_dpp<0x141>(v));
+  return fmaxf(v, cnn_dpp<0x140>(v));
+}
+__device__ __forceinline__ float cnn_lane(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ float cnn_wave_sum(float v) {
+  v = cnn_row_sum(v);
+  return (cnn_lane(v, 0) + cnn_lane(v, 16)) + (cnn_lane(v, 32) + cnn_lane(v, 48));
+}
+
 struct CnnFusedArgs {
   const float *params; // [26010]
   const float *x;      // [B][784]
@@ -188,59 +210,55 @@ __global__ __launch_bounds__(cnnf::THREADS) void cnn_small_fused_kernel(const Cn
       cols[fk * 32 + fn] = z;
     }
     __syncthreads();
-    if (tid < HID) {
-      float z0 = 0.f, z1 = 0.f;
-#pragma unroll
-      for (int k = 0; k < 32; k += 2) { z0 += cols[k * 32 + tid]; z1 += cols[(k + 1) * 32 + tid]; }
-      a3[tid] = act_apply(a.act3, z0 + z1 + b3[tid]);
-    }
-    __syncthreads();
-    // ---- fc2, loss gradient, the two dense layers' squared norms, delta3 (wave 0)
+    // ---- fc1's sums, fc2, loss gradient, delta3 (wave 0), with all that passes between lanes in registers: the other
+    // waves wait here, so the length of this chain counts (with 28 dependent shuffles, the pooled plane's norm and a barrier
+    // after fc1's sums in it, the launch took 93.2 us instead of 86.8 at 1,024 examples); the squared
+    // norms of the dense layers' inputs and gradients for the norm below (the pooled plane's by wave 1)
     if (wave == 0) {
-      float sp2 = 0.f;
+      const int j = i16 < NC ? i16 : 0; // each row of sixteen lanes holds the ten classes
+      float wc[HID];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) { const float v = p2[lane + 64 * i]; sp2 = fmaf(v, v, sp2); }
-      const float a3v = a3[lane & 31];
-      float sa3 = lane < 32 ? a3v * a3v : 0.f;
+      for (int n = 0; n < HID; ++n) wc[n] = w4[n * NC + j];
+      float s0 = 0.f, s1 = 0.f; // half of unit fn's 32 partial sums per lane
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) { sp2 += __shfl_xor(sp2, o, 64); sa3 += __shfl_xor(sa3, o, 64); }
-      float z = -INFINITY;
-      if (lane < NC) {
-        z = b4[lane];
+      for (int k = 0; k < 16; k += 2) { s0 += cols[((lane & 32) / 2 + k) * 32 + fn]; s1 += cols[((lane & 32) / 2 + k + 1) * 32 + fn]; }
+      s0 += s1;
+      const float a3v = act_apply(a.act3, s0 + __shfl_xor(s0, 32, 64) + b3[fn]);
+      if (lane < HID) a3[lane] = a3v;
+      float z0 = b4[j], z1 = 0.f;
 #pragma unroll
-        for (int n = 0; n < HID; ++n) z = fmaf(a3[n], w4[n * NC + lane], z);
+      for (int n = 0; n < HID; n += 2) {
+        z0 = fmaf(cnn_lane(a3v, n), wc[n], z0);
+        z1 = fmaf(cnn_lane(a3v, n + 1), wc[n + 1], z1);
       }
-      float mx = z;
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-      mx = __shfl(mx, 0, 64);
-      const float e = lane < NC ? expf(z - mx) : 0.f;
-      float se = e;
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) se += __shfl_xor(se, o, 64);
-      se = __shfl(se, 0, 64);
-      const float dv = lane < NC ? e / se - (lane == yy ? 1.f : 0.f) : 0.f;
-      float sd4 = dv * dv;
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) sd4 += __shfl_xor(sd4, o, 64);
-      sd4 = __shfl(sd4, 0, 64);
+      const float z = i16 < NC ? z0 + z1 : -INFINITY;
+      const float mx = cnn_row_max(z); // (outside the selection: every lane takes part)
+      const float e = i16 < NC ? expf(z - mx) : 0.f;
+      const float se = cnn_row_sum(e);
+      const float dv = i16 < NC ? e / se - (i16 == yy ? 1.f : 0.f) : 0.f;
       if (lane < 16) d4[lane] = dv;
       // delta3[n] = act'(a3[n]) * sum_j W4[n][j] delta4[j]
       float t = 0.f;
 #pragma unroll
-      for (int j = 0; j < NC; ++j) t = fmaf(w4[(lane & 31) * NC + j], __shfl(dv, j, 64), t);
+      for (int jj = 0; jj < NC; ++jj) t = fmaf(w4[fn * NC + jj], cnn_lane(dv, jj), t);
       t *= act_deriv_from_out(a.act3, a3v);
-      if (lane < 32) d3[lane] = t;
-      float sd3 = lane < 32 ? t * t : 0.f;
+      if (lane < HID) d3[lane] = t;
+      const float sd4 = cnn_row_sum(dv * dv), r3 = cnn_row_sum(t * t), ra = cnn_row_sum(a3v * a3v);
+      const float sd3 = cnn_lane(r3, 0) + cnn_lane(r3, 16), sa3 = cnn_lane(ra, 0) + cnn_lane(ra, 16);
+      if (lane == 0) { scl[1] = sd3; scl[2] = (sa3 + 1.f) * sd4; }
+    } else if (wave == 1) {
+      float sp2 = 0.f;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) sd3 += __shfl_xor(sd3, o, 64);
-      if (lane == 0) scl[1] = (sp2 + 1.f) * sd3 + (sa3 + 1.f) * sd4; // dense identity, both layers
+      for (int i = 0; i < 8; ++i) { const float v = p2[lane + 64 * i]; sp2 = fmaf(v, v, sp2); }
+      sp2 = cnn_wave_sum(sp2);
+      if (lane == 0) scl[3] = sp2 + 1.f;
     }
     __syncthreads();
     // ---- fc1 backward-data: dp2[k] = sum_n W3[k][n] delta3[n] from the weights the thread already holds: thread
     // (unit fn, features fk*16 ..) has the sixteen products W3[k][fn] delta3[fn]; the 32 lanes of a feature block
-    // add them up by a halving exchange (16 + 8 + 4 + 2 + 1 lanes apart: each step a lane keeps half of its values
-    // and receives the partner's sums for them), 16 exchanges instead of 80, in a fixed order
+    // add them up by a halving exchange (each step a lane keeps half of its values and receives the partner's sums for
+    // them: the rows of sixteen by a row swap, the rest by DPP moves), 16 exchanges instead of 80, in a fixed order.
+    // As shuffles they were LDS operations, 256 an example: the launch took 87.1 -> 85.6 us without them.
     {
       const float dn = d3[fn];
       const bool b4 = lane & 16, b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
@@ -248,14 +266,16 @@ __global__ __launch_bounds__(cnnf::THREADS) void cnn_small_fused_kernel(const Cn
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const float lo = w3r[j] * dn, hi = w3r[8 + j] * dn;
-        u8[j] = (b4 ? hi : lo) + __shfl_xor(b4 ? lo : hi, 16, 64);
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+        u8[j] = __uint_as_float(x[0]) + __uint_as_float(x[1]); // even rows: lo + the next row's lo; odd rows: hi
       }
+      // (partners that differ in the bit that is decided and in lower ones: what is added up is the same)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) u4[j] = (b3 ? u8[4 + j] : u8[j]) + __shfl_xor(b3 ? u8[j] : u8[4 + j], 8, 64);
+      for (int j = 0; j < 4; ++j) u4[j] = (b3 ? u8[4 + j] : u8[j]) + cnn_dpp<0x140>(b3 ? u8[j] : u8[4 + j]);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) u2[j] = (b2 ? u4[2 + j] : u4[j]) + __shfl_xor(b2 ? u4[j] : u4[2 + j], 4, 64);
-      float u1 = (b1 ? u2[1] : u2[0]) + __shfl_xor(b1 ? u2[0] : u2[1], 2, 64);
-      u1 += __shfl_xor(u1, 1, 64);
+      for (int j = 0; j < 2; ++j) u2[j] = (b2 ? u4[2 + j] : u4[j]) + cnn_dpp<0x141>(b2 ? u4[j] : u4[2 + j]);
+      float u1 = (b1 ? u2[1] : u2[0]) + cnn_dpp<0x4E>(b1 ? u2[0] : u2[1]);
+      u1 += cnn_dpp<0xB1>(u1);
       if ((lane & 1) == 0) dp2[fk * 16 + (b4 ? 8 : 0) + (b3 ? 4 : 0) + (b2 ? 2 : 0) + (b1 ? 1 : 0)] = u1;
     }
     __syncthreads();
@@ -378,9 +398,7 @@ __global__ __launch_bounds__(cnnf::THREADS) void cnn_small_fused_kernel(const Cn
       float t = 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) { const int p = lane + 64 * i; t += p < P1 ? a1[wave * P1 + p] : 0.f; }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-      gb1 = t; // every lane of wave d holds the bias gradient of channel d
+      gb1 = cnn_wave_sum(t); // every lane of wave d holds the bias gradient of channel d
     }
     float gb2 = 0.f;
     if (tid < D2) {
@@ -389,7 +407,7 @@ __global__ __launch_bounds__(cnnf::THREADS) void cnn_small_fused_kernel(const Cn
     }
     __syncthreads();
     const float g1 = (cols[tid] + cols[1024 + tid]) + (cols[2048 + tid] + cols[3072 + tid]); // (d, tap) = (tid / 64, tid % 64)
-    // ---- the example's squared norm: convolution coordinates here, dense layers by the identity (scl[1])
+    // ---- the example's squared norm: convolution coordinates here, dense layers by the identity (scl[1..3])
     {
       float q = g1 * g1;
 #pragma unroll
@@ -398,14 +416,13 @@ __global__ __launch_bounds__(cnnf::THREADS) void cnn_small_fused_kernel(const Cn
         for (int r = 0; r < 4; ++r) q = fmaf(g2[mb][r], g2[mb][r], q);
       if (lane == 0) q = fmaf(gb1, gb1, q);
       if (tid < D2) q = fmaf(gb2, gb2, q);
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+      q = cnn_wave_sum(q);
       if (lane == 0) red[wave] = q;
     }
     __syncthreads();
     float sc;
     {
-      float q = scl[1];
+      float q = scl[3] * scl[1] + scl[2]; // (||pooled||^2 + 1) ||delta3||^2 + (||a3||^2 + 1) ||delta4||^2
 #pragma unroll
       for (int w = 0; w < 16; ++w) q += red[w];
       const float n = sqrtf(q);
