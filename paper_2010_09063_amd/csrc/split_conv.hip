@@ -36,11 +36,11 @@ __device__ __forceinline__ float conv_swap1(float v) { // lanes swap within pair
 }
 
 // A wave works alone: 64 output pixels (two blocks of 32: the even and the odd rows, so that a 2x2 pool window is two
-// lanes of both blocks) x 32 MB output channels, KS waves sharing the input channels of a tile.  Per 16 input channels
+// lanes of both blocks) x 32 output channels, KS waves sharing the input channels of a tile.  Per 16 input channels
 // it fetches the haloed pixels with the channel as the register index, splits them once and leaves them in an LDS area
 // of its own, channels innermost ([piece][channel half][pixel][8]), so that the operand of every tap is one 16-byte
 // read per piece at a constant offset; the weight fragments come from the L2.  No barrier until the KS partial sums
-// meet.  The next chunk travels in registers meanwhile.  72 MB x 6 / 2 matrix instructions of 32 cycles per chunk
+// meet.  The next chunk travels in registers meanwhile.  108 matrix instructions of 32 cycles per chunk
 // against about 300 others and 54 LDS reads: bound by the matrix units and the power they draw (a register-only loop
 // sustains 1.9 of the nominal 2.5 PFLOP/s).
 template <int LW>
@@ -50,10 +50,10 @@ struct SplitConvGeom {
   static constexpr int ITEMS = (2 * PIX + 63) / 64, PLANE = 2 * PIX * 16;              // per lane; bytes of one piece
 };
 
-template <int LW, int MB, int KS, bool RAGGED>
+template <int LW, int KS, bool RAGGED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void split_conv_kernel(const SplitConvArgs a) {
   typedef SplitConvGeom<LW> G;
-  constexpr int W = G::W, LD = G::LD;
+  constexpr int W = G::W, LD = G::LD, MB = 1; // (blocks of 32 output channels)
   __shared__ __attribute__((aligned(16))) char lds[4][3 * G::PLANE];
   const int lane = threadIdx.x & 63, li = lane & 31, lk = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -114,13 +114,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int px = li & (W - 1), pr2 = 2 * (li >> LW), pseg = pr2 / seg_rows, py = pr2 - pseg * seg_rows;
   const char *rd = my + (lk * G::PIX + (pseg * (seg_rows + 2) + py) * LD + px) * 16;
 
-  sb_f32x16 acc[MB][2];
+  sb_f32x16 acc[MB][2], low[MB][2];
 #pragma unroll
   for (int m = 0; m < MB; ++m)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[m][i][r] = 0.f;
+      for (int r = 0; r < 16; ++r) acc[m][i][r] = low[m][i][r] = 0.f;
   const sb_u32x4 *fr = (const sb_u32x4 *)a.frag + (long)mb0 * 192 + lane;
   const long fstep = (long)mb_tot * 192;
   if (part < chunks) fetch(part);
@@ -149,9 +149,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int p = 0; p < 3; ++p)
           x[i].p[p] = *reinterpret_cast<const sb_u32x4 *>(rd + p * G::PLANE + ((tap / 3 + i) * LD + tap % 3) * 16);
-      sb_mfma(w[tap & 1], x, acc);
+      sb_mfma2(w[tap & 1], x, acc, low);
     }
   }
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[m][i][r] += low[m][i][r];
 
   // the partial sums of the KS waves: each leaves its own in its LDS area and finishes 16 / KS of the sixteen registers
   float sum[2][MB][16 / KS];
@@ -263,30 +269,30 @@ void split_conv_weights(hipStream_t st, const float *params, SplitConvWeights w)
   if (n > 0) hipLaunchKernelGGL(split_conv_weights_kernel, dim3(n), dim3(64), 0, st, params, w);
 }
 
-template <int LW, int MB, int KS, bool RAGGED>
+template <int LW, int KS, bool RAGGED>
 static void launch_one(hipStream_t st, const SplitConvArgs &a) {
   const int tiles = (a.B * a.H + SplitConvGeom<LW>::ROWS - 1) / SplitConvGeom<LW>::ROWS;
-  dim3 grid((tiles + 4 / KS - 1) / (4 / KS), ((a.M + 31) / 32 + MB - 1) / MB);
-  hipLaunchKernelGGL((split_conv_kernel<LW, MB, KS, RAGGED>), grid, dim3(256), 0, st, a);
+  dim3 grid((tiles + 4 / KS - 1) / (4 / KS), (a.M + 31) / 32);
+  hipLaunchKernelGGL((split_conv_kernel<LW, KS, RAGGED>), grid, dim3(256), 0, st, a);
 }
 
 template <int LW>
 static void launch_lw(hipStream_t st, const SplitConvArgs &a) {
   const long tiles = ((long)a.B * a.H * a.W + 63) / 64;
   const int mbt = (a.M + 31) / 32, chunks = (a.Cin + 15) / 16;
-  // as many output channels per wave as leave every SIMD (1024) two waves; where even one block of 32 leaves it clearly
-  // less, the input channels are shared by two or four waves (128 -> 128 on 8x8 planes at 256 examples, 1024 waves: 64 us,
+  // one block of 32 output channels per wave (its two accumulators leave no registers for a second block; two with one
+  // accumulator took the same time); where that leaves the SIMDs (1024) clearly fewer than two waves each,
+  // the input channels are shared by two or four waves (128 -> 128 on 8x8 planes at 256 examples, 1024 waves: 64 us,
   // 2048: 35; 48 -> 48 on 32x32 at 61, 1952 waves: 30 us, 3904: 37)
   if (a.Cin % 16 == 0) {
-    if (mbt % 2 == 0 && tiles * (mbt / 2) >= 2048) { launch_one<LW, 2, 1, false>(st, a); return; }
-    if (tiles * mbt >= 1536 || chunks < 2) { launch_one<LW, 1, 1, false>(st, a); return; }
-    if (tiles * mbt >= 640 || chunks < 4) { launch_one<LW, 1, 2, false>(st, a); return; }
-    launch_one<LW, 1, 4, false>(st, a);
+    if (tiles * mbt >= 1536 || chunks < 2) { launch_one<LW, 1, false>(st, a); return; }
+    if (tiles * mbt >= 640 || chunks < 4) { launch_one<LW, 2, false>(st, a); return; }
+    launch_one<LW, 4, false>(st, a);
     return;
   }
-  if (tiles * mbt >= 1536 || chunks < 2) { launch_one<LW, 1, 1, true>(st, a); return; }
-  if (tiles * mbt >= 640 || chunks < 4) { launch_one<LW, 1, 2, true>(st, a); return; }
-  launch_one<LW, 1, 4, true>(st, a);
+  if (tiles * mbt >= 1536 || chunks < 2) { launch_one<LW, 1, true>(st, a); return; }
+  if (tiles * mbt >= 640 || chunks < 4) { launch_one<LW, 2, true>(st, a); return; }
+  launch_one<LW, 4, true>(st, a);
 }
 
 void split_conv_launch(hipStream_t st, const SplitConvArgs &a) {

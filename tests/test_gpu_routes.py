@@ -79,6 +79,37 @@ def test_convolutions_on_the_bf16_matrix_units(cin, widths, plane, act, pool, ba
     _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} recomputed", stepper=st)
 
 
+def test_split_convolutions_add_no_bias():
+    """The bf16 instruction rounds its sums downwards.  A bias gradient adds up 32,768 backprops here: an error of 2**-24 of
+    each with one sign shows as 1e-5 of the tensor's size (1.1e-5 with all six products in one accumulator); with random
+    signs the two routes differ by up to 2.6e-6.  The bar is twice that."""
+    import torch
+    from paper_2010_09063_amd import DpStep
+    m = W.model(W.image_input(48, 16, 16), [W.conv2d(48, 48, 3, stride=1, pad=1, act="tanh") for _ in range(4)] +
+                [W.maxpool2d(2, 2), W.dense(48 * 64, 3)], 3)
+    rng = np.random.default_rng(1)
+    x, y = W.make_inputs(m, 128, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.05)
+    dev = torch.device("cuda")
+    tt, tx, ty = (torch.from_numpy(np.ascontiguousarray(v)).to(dev) for v in (theta, x, y))
+    out = []
+    for opt in ({}, {"generic_conv": 1}):
+        st = DpStep(m, 128, **opt)
+        g = torch.empty_like(tt)
+        st.dp_step_nonprivate(tt, tx, ty, 128, g)
+        out.append(g.double())
+        st.dp_step_free()
+    d = out[0] - out[1]
+    at = 0
+    for l in range(4):
+        n = 48 * 48 * 9
+        b = slice(at + n, at + n + 48)
+        rms = out[1][at:at + n + 48].norm() / (n + 48) ** 0.5
+        print(f"layer {l}: bias differs by up to {float(d[b].abs().max() / rms):.2e}, on average {float(d[b].mean() / rms):.2e}", flush=True)
+        assert float(d[b].abs().max() / rms) <= 6e-6
+        at += n + 48
+
+
 @pytest.mark.parametrize("out", ["last", "seq"])
 @pytest.mark.parametrize("dim,hidden,seq,batch", [
     (1, 1, 1, 1),        # the smallest of everything
