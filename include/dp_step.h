@@ -106,8 +106,8 @@ int dp_step_init(const dp_model_desc *model, int max_batch, void *hip_stream, dp
  */
 typedef struct {
   int generic_conv;               /* 3x3 stride-1 convolutions on the generic tiled contraction                   */
-  int no_minimal_filtering;       /* no kernel of the F(2x2,3x3) / F(3x3,2x2) family                              */
-  int no_minimal_filtering_wgrad; /* only that family's weight-gradient kernels off                               */
+  int no_minimal_filtering;       /* no kernel of the F(2x2,3x3) / F(3x3,2x2) family, none on the bf16 matrix units */
+  int no_minimal_filtering_wgrad; /* only those families' weight-gradient kernels off                             */
   int minimal_filtering_all;      /* its forward / backward-data kernels for every eligible shape                 */
   int no_pool_fusion;             /* 2x2 / stride-2 pools as launches of their own, not in the conv epilogue      */
   int no_gram;                    /* small-plane convolution norms by the per-example contraction                 */
@@ -121,12 +121,12 @@ typedef struct {
   int no_fused_cnn;               /* the small MNIST-shaped CNN layer by layer instead of in one launch            */
   int no_lstm_wgrad;              /* the LSTM's per-example weight gradient on the generic tiled contraction       */
   int no_rows_gemm;               /* the LSTM's input projection / input gradient on the generic tiled contraction */
-  int no_single_bucket;           /* the embedding's counting sort as three launches, whatever the batch           */
+  int no_single_bucket;           /* the embedding by sorted lists, their counting sort as three launches          */
   int no_small_gemm;              /* two-layer networks: both batch-wide products on the split-K contraction, not
                                      on the kernel that splits K inside the workgroup                               */
   int no_resident_weights;        /* minimal-filtering form, 32 -> (at most) 32 channels: the per-group kernel instead of
                                      the persistent one that keeps the transformed weights in registers              */
-  int no_side_stream;             /* the embedding's counting sort in line on the caller's stream instead of beside the
+  int no_side_stream;             /* the embedding by sorted lists, their sort in line on the caller's stream, not beside the
                                      forward pass on a stream of the library's own                                 */
   int no_first_layer_kernel;      /* an RGB first layer's forward pass on the generic direct kernel                  */
 } dp_plan_options;
