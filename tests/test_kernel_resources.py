@@ -1,0 +1,52 @@
+"""What the compiler gave the device code of the built library: a kernel that keeps staged values or accumulators in scratch
+memory still gives right results, several times slower."""
+import os
+import struct
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2010_09063_amd", "libdpstep.so")
+
+
+def _kernels():
+    """Metadata of every kernel: the AMDGPU notes of the code objects in the library's offload bundles."""
+    msgpack = pytest.importorskip("msgpack")
+    if not os.path.exists(LIB):
+        from paper_2010_09063_amd.build import build_library
+        build_library()
+    data, out = open(LIB, "rb").read(), {}
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    at = data.find(magic)
+    while at >= 0:
+        n, p = struct.unpack_from("<Q", data, at + 24)[0], at + 32
+        for _ in range(n if n < 16 else 0):
+            off, size, idlen = struct.unpack_from("<QQQ", data, p)
+            name = data[p + 24:p + 24 + idlen]
+            p += 24 + idlen
+            elf = data[at + off:at + off + size]
+            if b"gfx950" not in name or elf[:4] != b"\x7fELF":
+                continue
+            phoff, phsize, phnum = struct.unpack_from("<Q", elf, 32)[0], *struct.unpack_from("<HH", elf, 54)
+            for i in range(phnum):
+                kind, _, o, _, _, sz = struct.unpack_from("<IIQQQQ", elf, phoff + i * phsize)
+                if kind != 4:  # PT_NOTE
+                    continue
+                q = o
+                while q < o + sz:
+                    nn, nd, t = struct.unpack_from("<III", elf, q)
+                    d = q + 12 + (nn + 3) // 4 * 4
+                    if t == 32:  # NT_AMDGPU_METADATA
+                        for k in msgpack.unpackb(elf[d:d + nd])["amdhsa.kernels"]:
+                            out[k[".name"]] = k
+                    q = d + (nd + 3) // 4 * 4
+        at = data.find(magic, at + 1)
+    return out
+
+
+def test_no_scratch_memory_in_the_split_kernels():
+    ks = {n: k for n, k in _kernels().items() if "split_" in n}
+    assert len(ks) > 30, sorted(ks)
+    for n, k in sorted(ks.items()):
+        print(n, "scratch", k[".private_segment_fixed_size"], "spilled", k[".sgpr_spill_count"], k[".vgpr_spill_count"])
+    assert [n for n, k in ks.items() if k[".private_segment_fixed_size"] > 32 or k[".sgpr_spill_count"] > 256] == []
