@@ -38,35 +38,38 @@ __device__ __forceinline__ void sb_split8(const float (&v)[8], SbFrag &f) {
     f.p[0][j] = h; f.p[1][j] = m; f.p[2][j] = l;
   }
 }
-// The instruction cuts off what lies below the accumulator's last bit, downwards: a long sum of all six products in one
-// accumulator comes out low by 5e-8 of its size (K = 1024, signed operands, root mean square error 4.8e-7; the fp32
-// instruction: 3e-9 and 5.8e-7), and a sum over many such values, a bias gradient behind several layers, shows it.  So where
-// results feed further sums the five small products have an accumulator of their own, added at the end: 2e-9 and 1.7e-7.
-template <int NI, int NJ>
-__device__ __forceinline__ void sb_mfma2(const SbFrag (&a)[NI], const SbFrag (&b)[NJ], sb_f32x16 (&acc)[NI][NJ], sb_f32x16 (&low)[NI][NJ]) {
+// The instruction rounds its sums with a bias downwards: it cuts off what lies below the last bits of the largest term, the
+// accumulator among them.  For one product matrix that is nothing (1e-9 to 1e-8 of its size, its random error 3e-8 to
+// 2e-7), but what adds up many of them shows it: the sum of 128 products of K = 256 was low by 1.0e-7 to 1.8e-7 of its size,
+// with a root mean square error of 2.1e-7 to 3.7e-7 (the fp32 instruction: below 6e-9, and 2.0e-7 to 3.7e-7).  Hence
+// - the sign of one operand alternates between products that are added up later (examples, rows, the shares of a contraction
+//   among waves), and the result's with it: half of the errors point upwards (below 2e-8, and 2.0e-7 to 3.3e-7).  In
+//   split_rows.hip, split_lstm.hip and split_wgrad.hip, where it costs nothing that can be measured;
+// - the small products, which have the most bits to lose, do not meet a large sum inside the instruction where that can be had:
+//   in an accumulator of their own, added at the end (sb_mfma2: one product matrix of K = 1024 off by 1.7e-7 instead of
+//   4.8e-7), or before all of the large ones in the same accumulator (split_rows.hip, which has all of K at hand).
+
+// acc[i][j] += the products FIRST .. LAST - 1 of A[i] B[j], smallest first (five small ones, then the one of the leading
+// pieces), for NI x NJ blocks of 32 x 32 x 16.  The blocks take turns: an instruction that adds to the accumulator of the one
+// before waits for it.
+template <int FIRST, int LAST, int NI, int NJ>
+__device__ __forceinline__ void sb_products(const SbFrag (&a)[NI], const SbFrag (&b)[NJ], sb_f32x16 (&acc)[NI][NJ]) {
   constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
-  for (int q = 0; q < 6; ++q)
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        sb_f32x16 &d = q < 5 ? low[i][j] : acc[i][j];
-        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sb_bf16x8, a[i].p[pa[q]]),
-                                                    __builtin_bit_cast(sb_bf16x8, b[j].p[pb[q]]), d, 0, 0, 0);
-      }
-}
-// acc[i][j] += A[i] B[j] for NI x NJ blocks of 32 x 32 x 16, smallest terms first.  The blocks take turns: an instruction
-// that adds to the accumulator of the one before waits for it.
-template <int NI, int NJ>
-__device__ __forceinline__ void sb_mfma(const SbFrag (&a)[NI], const SbFrag (&b)[NJ], sb_f32x16 (&acc)[NI][NJ]) {
-  constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
-#pragma unroll
-  for (int q = 0; q < 6; ++q)
+  for (int q = FIRST; q < LAST; ++q)
 #pragma unroll
     for (int i = 0; i < NI; ++i)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(sb_bf16x8, a[i].p[pa[q]]),
                                                             __builtin_bit_cast(sb_bf16x8, b[j].p[pb[q]]), acc[i][j], 0, 0, 0);
+}
+template <int NI, int NJ>
+__device__ __forceinline__ void sb_mfma(const SbFrag (&a)[NI], const SbFrag (&b)[NJ], sb_f32x16 (&acc)[NI][NJ]) {
+  sb_products<0, 6>(a, b, acc);
+}
+template <int NI, int NJ>
+__device__ __forceinline__ void sb_mfma2(const SbFrag (&a)[NI], const SbFrag (&b)[NJ], sb_f32x16 (&acc)[NI][NJ], sb_f32x16 (&low)[NI][NJ]) {
+  sb_products<0, 5>(a, b, low);
+  sb_products<5, 6>(a, b, acc);
 }

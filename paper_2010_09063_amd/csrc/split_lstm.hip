@@ -65,8 +65,10 @@ __global__ __launch_bounds__(SL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       }
     }
   };
+  // the gate gradients change sign with the example, in sums with the partial row, and so does what is added up here (split_bf16.h)
+  auto sign = [&](int e) SL_INLINE { return (NORM ? e : (int)blockIdx.x) & 1 ? -1.f : 1.f; };
   auto stash = [&](char *buf, int e, int t0) SL_INLINE {
-    const float f = NORM ? 1.f : a.scale[e];
+    const float f = NORM ? sign(e) : sign(e) * a.scale[e];
 #pragma unroll
     for (int q = 0; q < ITEMS; ++q) {
       const int blk = wave + 8 * q;
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(SL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         const bool ok = t < T && kind[q] != 0;
         float w = kind[q] == 3 ? 1.f : raw[q][j];
         if (kind[q] == 2 && t == 0) w = 0.f;
-        if (!NORM && blk >= mb_tot) w *= f;
+        if (blk >= mb_tot) w *= f;
         v[j] = ok ? w : 0.f;
       }
       SbFrag fr;
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(SL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
           for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     };
     // accumulator register r of a lane: row 8 (r / 4) + 4 lk + r % 4, column li of its block
-    auto store = [&](float *g) SL_INLINE { // g: the matrix in the parameter layout; returns the sum of the squares
+    auto store = [&](float *g, float sg) SL_INLINE { // g: the matrix in the parameter layout, sg its sign here; returns the sum of the squares
       float q2 = 0.f;
       // (the rows' offsets and lane masks are made here: hoisted out of the loop over units they are 1,600 spilled scalar registers)
       const int gc = __builtin_amdgcn_readfirstlane(Gc);
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(SL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
               const int ru = 8 * (r >> 2) + (r & 3);
-              const float v = acc[i][j][r];
+              const float v = sg * acc[i][j][r];
               q2 = fmaf(v, v, q2); // (zero beyond the matrix: nothing else was staged)
               if (g != nullptr && ru < left) *reinterpret_cast<float *>(reinterpret_cast<char *>(gi + (long)ru * gc) + off) = v;
             }
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(SL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       return q2;
     };
     auto finish = [&](int e) SL_INLINE {
-      float q2 = store(a.gstore != nullptr ? a.gstore + (long)e * a.gstride : nullptr);
+      float q2 = store(a.gstore != nullptr ? a.gstore + (long)e * a.gstride : nullptr, sign(e));
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) q2 += __shfl_xor(q2, o, 64);
       if (lane == 0) a.slots[(long)(a.slot0 + half * 8 + wave) * a.slot_stride + e] = q2;
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(SL_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     if (NORM) {
       if (done >= 0) finish(done);
     } else {
-      (void)store(a.part + (long)blockIdx.x * a.part_stride);
+      (void)store(a.part + (long)blockIdx.x * a.part_stride, sign(0));
     }
   };
 #define SL_NC(mc_) \

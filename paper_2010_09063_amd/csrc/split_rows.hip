@@ -47,7 +47,9 @@ __global__ __launch_bounds__(SR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
   const int kh = KH == 1 ? 0 : wave >> 2;
   const long tiles = (a.M + 31) >> 5;
 
-  // staging items: (k half step, row of the tile), rows along the lanes
+  // staging items: (k half step, row of the tile), rows along the lanes; odd rows with the opposite sign, as far as the
+  // accumulators: a token's gradient adds up thousands of them (split_bf16.h)
+  const float sign = lane & 1 ? -1.f : 1.f;
   sb_f32x4u raw[ITEMS][2];
   auto fetch = [&](long tile) {
 #pragma unroll
@@ -65,7 +67,7 @@ __global__ __launch_bounds__(SR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
       const int it = tid + SR_THREADS * q, kk = it >> 5;
       float v[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = 8 * kk + j < K ? raw[q][j >> 2][j & 3] : 0.f; // (what lies past K is somebody else's)
+      for (int j = 0; j < 8; ++j) v[j] = 8 * kk + j < K ? sign * raw[q][j >> 2][j & 3] : 0.f; // (what lies past K is somebody else's)
       SbFrag f;
       sb_split8(v, f);
       if (kk < 2 * KST) {
@@ -109,17 +111,24 @@ __global__ __launch_bounds__(SR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         for (int r = 0; r < 16; ++r) acc[0][j][r] = 0.f;
       if constexpr (NB > 0) {
         SbFrag x[2][1]; // one k step ahead (further ahead there are no registers left)
-        auto operand = [&](int s) {
+        auto operand = [&](int s, int pieces) {
 #pragma unroll
-          for (int p = 0; p < 3; ++p)
+          for (int p = 0; p < pieces; ++p)
             x[s & 1][0].p[p] = *reinterpret_cast<const sb_u32x4 *>(buf + (kh * KSW + s) * 3072 + p * 1024 + lane * 16);
         };
-        operand(0);
+        operand(0, 3);
 #pragma unroll
         for (int s = 0; s < KSW; ++s) {
-          if (s + 1 < KSW) operand(s + 1);
+          if (s + 1 < KSW) operand(s + 1, 3);
           __builtin_amdgcn_sched_barrier(0);
-          sb_mfma(x[s & 1], w[s], acc);
+          sb_products<0, 5>(x[s & 1], w[s], acc);
+        }
+        operand(0, 1); // the leading pieces again, for the large products
+#pragma unroll
+        for (int s = 0; s < KSW; ++s) {
+          if (s + 1 < KSW) operand(s + 1, 1);
+          __builtin_amdgcn_sched_barrier(0);
+          sb_products<5, 6>(x[s & 1], w[s], acc);
         }
       }
       if constexpr (KH == 2) { // the second half's sums meet the first's in the buffer that was just read
@@ -145,7 +154,7 @@ __global__ __launch_bounds__(SR_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
           for (int r = 0; r < 16; ++r) { // accumulator register r of a lane: row 8 (r / 4) + 4 lk + r % 4, column li
             const int ru = 8 * (r >> 2) + (r & 3);
             if (in && ru < rows_left)
-              *reinterpret_cast<float *>(reinterpret_cast<char *>(cj + ru * a.ldc) + lane_off) = acc[0][j][r] + bv[j];
+              *reinterpret_cast<float *>(reinterpret_cast<char *>(cj + ru * a.ldc) + lane_off) = r & 1 ? bv[j] - acc[0][j][r] : bv[j] + acc[0][j][r];
           }
         }
       }

@@ -16,7 +16,8 @@
 // A workgroup of four waves owns a block of 32 input channels and 32 DBW output channels; the 4 / DBW waves of a block of
 // output channels share the k steps of a band of rows and add up at the end.  54 matrix instructions of 32 cycles per
 // k step against 30 LDS reads; staging costs about 300 vector instructions per thread and band, which the second
-// workgroup of the CU covers.
+// workgroup of the CU covers.  dy of odd k steps is staged with the opposite sign and the odd waves' sums are subtracted at
+// the end: the instruction's one-sided error (split_bf16.h) was up to 4.3e-7 of a gradient's size, most of its error.
 template <int W_>
 struct SplitWgGeom {
   static constexpr int W = W_;
@@ -147,13 +148,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
         for (int bb = 0; bb < DBW; ++bb)
 #pragma unroll
           for (int m = 0; m < (APART ? 4 : 1); ++m) bsum[bb][m] += (DBW == 1 || bb == b) && (!APART || m == im) ? sum : 0.f;
+        const float sign = !APART && (im & 1) ? -1.f : 1.f;
+        float g[8];
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-          float g[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) g[j] = u[j];
-          put(dst + s * 3 * 512, g);
-        }
+        for (int j = 0; j < 8; ++j) g[j] = sign * u[j];
+        put(dst, g);
       }
       __syncthreads();
       multiply();
@@ -215,7 +214,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
           for (int s = 0; s < S; ++s) {
             float g[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) g[j] = raw[q][s + S * j];
+            for (int j = 0; j < 8; ++j) g[j] = ((S == 1 ? r >> 1 : s) & 1) ? -raw[q][s + S * j] : raw[q][s + S * j];
             put(dst + s * 3 * 512, g);
           }
         }
@@ -260,8 +259,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
         for (int r = 0; r < RN; ++r) {
           float v = 0.f;
 #pragma unroll
-          for (int w = 0; w < KW; ++w)
-            v += *reinterpret_cast<const float *>(lds + (db * KW + w) * EXCH + ((t * 16 + r0 + r) * 64 + lane) * 4);
+          for (int w = 0; w < KW; ++w) { // (odd k steps, which are the odd waves', were staged with the opposite sign)
+            const float part = *reinterpret_cast<const float *>(lds + (db * KW + w) * EXCH + ((t * 16 + r0 + r) * 64 + lane) * 4);
+            v += w & 1 ? -part : part;
+          }
           fin[t3 + t][r] = v;
         }
     }

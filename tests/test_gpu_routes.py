@@ -110,6 +110,50 @@ def test_split_convolutions_add_no_bias():
         at += n + 48
 
 
+def _split_case(kind):
+    if kind == "lstm":
+        m = W.model(W.token_input(256), [W.embedding(300, 100), W.lstm_last(100, 100), W.dense(100, 2)], 2)
+        rng, batch = np.random.default_rng(3), 128
+        x, y = W.make_inputs(m, batch, rng, zipf_exponent=1.1)
+        return m, x, y, W.init_params(m, rng, bias_scale=0.05)
+    m = W.model(W.image_input(16, 32, 32), [W.conv2d(16, 16, 3, stride=1, pad=1, act="tanh") for _ in range(2)] +
+                [W.avgpool2d(2, 2), W.dense(16 * 256, 3)], 3)
+    rng, batch = np.random.default_rng(4), 256
+    x, y = W.make_inputs(m, batch, rng, x_dist="normal")
+    return m, x, y, W.init_params(m, rng, bias_scale=0.05)
+
+
+@pytest.mark.parametrize("kind,private", [("lstm", True), ("lstm", False), ("conv", True), ("conv", False)])
+def test_split_products_have_no_one_sided_error(kind, private):
+    """The bf16 instruction rounds its sums downwards, and gradients add up many of its results: per-example gradients
+    (private) and partial sums over the batch, a frequent token's rows over all steps.  The mean error of a tensor
+    against 64 bits, over its root mean square: random errors of 2e-7 to 6e-7 average to 1e-9 to 3e-9 (40,000 weights),
+    6e-9 (2,304) and 1e-8 (800 coordinates of frequent tokens), somewhat more as they are not independent; the fp32
+    kernels gave up to 5e-9, 1.2e-8 and 1.8e-8.  With every product of one sign it was -5e-8, -4.6e-7 and -7.5e-8."""
+    import torch
+    from oracle import dpsgd_oracle as O
+    from paper_2010_09063_amd import DpStep
+    m, x, y, theta = _split_case(kind)
+    ref = np.asarray(O.dp_step(m, theta, x, y, 0.5 if private else 1e30, 0.0, 0)["clipped_sum"])
+    dev = torch.device("cuda")
+    tt, tx, ty = (torch.from_numpy(np.ascontiguousarray(v)).to(dev) for v in (theta, x, y))
+    st, g = DpStep(m, len(y)), torch.empty_like(tt)
+    if private:
+        st.dp_step(tt, tx, ty, len(y), 0.5, 0.0, 0, g)
+    else:
+        st.dp_step_nonprivate(tt, tx, ty, len(y), g)
+    err = g.double().cpu().numpy() - ref
+    st.dp_step_free()
+    bars = {"E": 6e-8, "W_ih": 1.5e-8, "W_hh": 1.5e-8, "W": 8e-8}
+    for li, name, shape, off in W.param_tensors(m):
+        if name == "b" or m["layers"][li]["kind"] == "dense":
+            continue
+        s = slice(off, off + (8 * shape[1] if name == "E" else int(np.prod(shape))))  # (the embedding: its eight most frequent tokens)
+        rms = np.sqrt(np.mean(ref[s] ** 2))
+        print(f"layer {li} {name}: mean error {err[s].mean() / rms:+.2e}, rms {np.sqrt(np.mean(err[s] ** 2)) / rms:.2e}", flush=True)
+        assert abs(err[s].mean() / rms) <= bars[name], (li, name)
+
+
 @pytest.mark.parametrize("out", ["last", "seq"])
 @pytest.mark.parametrize("dim,hidden,seq,batch", [
     (1, 1, 1, 1),        # the smallest of everything
