@@ -542,15 +542,10 @@ struct SmallGemmArgs {
 typedef float sg_f32x16 __attribute__((ext_vector_type(16)));
 #define SG_LD 33
 
-// What the kernel can take: one of an operand's two strides is 1.
-static inline bool dense_small_gemm_fits(const SmallGemmArgs &a) {
-  return a.K >= 1 && (a.a_sk == 1 || a.a_sr == 1) && a.b_sr == 1;
-}
 // 16-byte loads: base pointers, the non-unit strides and K are multiples of 4 floats; an operand whose rows are the
 // contiguous index has a row count that is one too, or rows of memory padded to the next multiple (its k stride covers
 // it), so that the last group of four may be read whole.  Everything else (a hidden width of 50) is staged with four
-// 4-byte loads in the place of each: the split-K contraction and its partials, which these widths took before, cost the
-// 104-50-10 network 15.6 + 13.6 us at 128 examples.
+// 4-byte loads in the place of each, up to the batch of dense2_small_batch.
 static inline bool dense_small_gemm_vec(const SmallGemmArgs &a) {
   auto al = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   const bool a_kc = a.a_sk == 1;
@@ -558,6 +553,17 @@ static inline bool dense_small_gemm_vec(const SmallGemmArgs &a) {
   if (a_kc ? (a.a_sr & 3) != 0 : ((a.a_sk & 3) != 0 || a.a_sk < ((a.M + 3) & ~3))) return false;
   if ((a.b_sk & 3) != 0 || a.b_sk < ((a.N + 3) & ~3)) return false;
   return true;
+}
+
+// A two-layer network's products with 4-byte loads.  The batch is the K of its clipped sums, which a workgroup takes whole:
+// with few tiles of 32 x 32 weights their time grows by 10 us per 1,024 examples on a mostly idle chip, while the split-K
+// contraction cuts the batch among workgroups.  Whole steps, this kernel and that: 104-50-10 (10 tiles) 32 and 49 us at 1,024
+// examples, 64 and 58 at 3,072, 988 and 356 at 65,536; 63-33-2 (6 tiles) 30 and 32 at 1,024, 44 and 36 at 2,048; 75-595-2
+// (76 tiles) 75 and 50 at 1,718; 639-639-7 (420 tiles) 127 and 159 at 2,048; 999-639-10 (660) 171 and 216 at 2,048, 250 and 248 at
+// 3,072.
+static inline bool dense2_small_batch(int d_in, int hidden, int n_classes, int B) {
+  const long tiles = (long)((d_in + 32) / 32) * ((hidden + 31) / 32) + (long)((hidden + 32) / 32) * ((n_classes + 31) / 32);
+  return B <= (tiles >= 256 ? 2048 : 1024);
 }
 
 // One operand slice: rows r0 .. r0 + 31 (R real rows, row R the constant 1 if ONES), k0 .. k0 + 31, as four 16-byte

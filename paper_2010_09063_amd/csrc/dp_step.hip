@@ -1119,6 +1119,8 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
     int fused_pool = -1;
     const bool no_pool_fusion = c->opt.no_pool_fusion != 0;
     const bool f2 = c->fused2, h2 = c->head2;
+    // a two-layer network of any widths and alignment on the kernel that splits K inside the workgroup
+    const bool f2_any = f2 && dense2_small_batch(c->L[0].d.in_features, c->L[0].d.out_features, c->L[1].d.out_features, B);
     int mid_ns = 0, mid_tiles = 0;
     SmallGemmArgs joint_g[2] = {};
     bool joint = false;
@@ -1136,7 +1138,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
           g.bias = W + (long)l.d.in_features * l.d.out_features; g.act = l.d.act;
           g.C = l.a; g.c_sm = l.d.out_features; g.c_sn = 1; g.C_ones = nullptr;
           g.M = B; g.N = l.d.out_features; g.K = l.d.in_features; g.a_ones = 0;
-          if (f2 ? dense_small_gemm_fits(g) : dense_small_gemm_vec(g)) {
+          if (f2_any || dense_small_gemm_vec(g)) {
             Ln(LL("dense_fwd"), dim3(1), dim3(256), [&](hipStream_t st) { launch_dense_small_gemm(st, g); });
             break;
           }
@@ -1367,7 +1369,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
         g1.B = l1.g; g1.b_sr = 1; g1.b_sk = 16;
         g1.C = l1.part; g1.c_sm = l1.d.out_features; g1.c_sn = 1; g1.C_ones = l1.part + (long)l1.d.in_features * l1.d.out_features;
         g1.M = l1.d.in_features; g1.N = l1.d.out_features; g1.K = B; g1.act = DP_ACT_NONE;
-        joint = dense_small_gemm_fits(g0) && dense_small_gemm_fits(g1);
+        joint = f2_any || (dense_small_gemm_vec(g0) && dense_small_gemm_vec(g1));
         if (joint) { a.head = 2; a.delta2_out = l1.g; a.part2 = nullptr; }
       }
       Ln("dense2_mid", dim3(1), dim3(256), [&](hipStream_t st) {
@@ -1786,7 +1788,7 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
           g.bias = nullptr; g.act = DP_ACT_NONE;
           g.C = l.part; g.c_sm = l.d.out_features; g.c_sn = 1; g.C_ones = l.part + (long)l.d.in_features * l.d.out_features;
           g.M = l.d.in_features; g.N = l.d.out_features; g.K = B;
-          if (dense_small_gemm_fits(g)) {
+          if (f2_any || dense_small_gemm_vec(g)) {
             Ln(LL("dense_clipped_sum"), dim3(1), dim3(256), [&](hipStream_t st) { launch_dense_small_gemm(st, g); });
             nsplit = 1;
             break;
@@ -2105,7 +2107,14 @@ extern "C" int dp_step_describe_plan(const dp_ctx *c, char *buf, size_t cap) {
     case DP_DENSE:
       fwd = c->fused1 ? "fused" : "generic"; bwd = i > 0 ? "generic" : "-";
       norm = c->fused1 ? "fused" : "identity"; sum = c->fused1 ? "fused" : "generic";
-      if (c->fused2) { norm = "fused"; if (i == 1) { fwd = bwd = "fused"; sum = c->joint2 ? "joint" : "fused"; } }
+      if (c->fused2) {
+        norm = "fused";
+        if (i == 1) {
+          const int d_in = c->L[0].d.in_features, h = c->L[0].d.out_features;
+          const bool joint = c->joint2 && ((d_in % 4 == 0 && h % 4 == 0) || dense2_small_batch(d_in, h, l.d.out_features, c->maxB));
+          fwd = bwd = "fused"; sum = joint ? "joint" : "fused"; // (at the largest batch)
+        }
+      }
       if (c->head2 && i + 2 >= c->L.size()) { norm = "head"; if (i + 1 == c->L.size()) { fwd = bwd = "head"; if (c->joint2) sum = "joint"; } }
       if (c->fusedcnn) fwd = bwd = norm = sum = "fused-net";
       if (c->class_head && i + 1 == c->L.size()) { fwd = bwd = norm = "fused"; sum = "pairs"; }

@@ -49,6 +49,31 @@ def test_two_layer_networks_of_widths_off_the_vector_size(d_in, hidden, classes,
     _check_all_regimes(m, x, y, theta, f"dense {d_in}->{hidden}->{classes}/B{batch}")
 
 
+@pytest.mark.parametrize("d_in,hidden,classes,batch,small", [
+    (104, 50, 10, 1024, True), (104, 50, 10, 1025, False),  # few tiles of weights
+    (513, 449, 3, 2048, True), (513, 449, 3, 2049, False),  # 270 of them
+    (104, 52, 10, 4096, True)])                             # whole groups of four floats: any batch
+def test_two_layer_networks_where_the_batch_is_a_long_k(d_in, hidden, classes, batch, small):
+    """Off the vector size the clipped sums leave the kernel whose workgroups take the whole batch as their K (which also
+    makes the final write) before it falls behind; the two routes on both sides of the line."""
+    import torch
+    from paper_2010_09063_amd import DpStep
+    m = W.model(W.image_input(d_in), [W.dense(d_in, hidden, act="tanh"), W.dense(hidden, classes)], classes)
+    rng = np.random.default_rng(hidden)
+    x, y = W.make_inputs(m, batch, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.3)
+    st = DpStep(m, batch)
+    assert (st.dp_step_describe_plan()[1]["sum"] == "joint") == small
+    _check_all_regimes(m, x, y, theta, f"dense {d_in}->{hidden}->{classes}/B{batch}", stepper=st)
+    dev = torch.device("cuda")
+    tt, tx, ty = (torch.from_numpy(np.ascontiguousarray(v)).to(dev) for v in (theta, x, y))
+    st.dp_step_profile(True)
+    st.dp_step(tt, tx, ty, batch, 1.0, 1.0, 1, torch.empty_like(tt))
+    labels = [r[0] for r in st.dp_step_profile_read()]
+    st.dp_step_free()
+    assert ("finalize_noise" not in labels) == small, labels
+
+
 @pytest.mark.parametrize("cin,widths,plane,act,pool,batch", [
     (3, (16, 48), (32, 32), "tanh", "max", 3),      # one and two blocks of output channels, the second half empty
     (3, (48, 100, 20), (4, 32), "relu", "avg", 5),  # the fewest rows of a 32-wide plane; ragged blocks on both sides
