@@ -558,12 +558,12 @@ static inline bool dense_small_gemm_vec(const SmallGemmArgs &a) {
 // A two-layer network's products with 4-byte loads.  The batch is the K of its clipped sums, which a workgroup takes whole:
 // with few tiles of 32 x 32 weights their time grows by 10 us per 1,024 examples on a mostly idle chip, while the split-K
 // contraction cuts the batch among workgroups.  Whole steps, this kernel and that: 104-50-10 (10 tiles) 32 and 49 us at 1,024
-// examples, 64 and 58 at 3,072, 988 and 356 at 65,536; 63-33-2 (6 tiles) 30 and 32 at 1,024, 44 and 36 at 2,048; 75-595-2
-// (76 tiles) 75 and 50 at 1,718; 639-639-7 (420 tiles) 127 and 159 at 2,048; 999-639-10 (660) 171 and 216 at 2,048, 250 and 248 at
-// 3,072.
+// examples, 64 and 58 at 3,072, 988 and 356 at 65,536; 63-33-2 (6) 30 and 32 at 1,024, 44 and 36 at 2,048; 65-639-10 (80) 41 and
+// 61 at 1,024, 87 and 76 at 3,072; 255-1023-3 (288) 66 and 75 at 900, 68 and 65 at 1,024.  Wide inputs keep it longer: 639-639-7
+// (420) 126 and 159 at 2,048, 183 and 184 at 3,072; 999-639-10 (660) 171 and 216 at 2,048, 250 and 248 at 3,072.
 static inline bool dense2_small_batch(int d_in, int hidden, int n_classes, int B) {
   const long tiles = (long)((d_in + 32) / 32) * ((hidden + 31) / 32) + (long)((hidden + 32) / 32) * ((n_classes + 31) / 32);
-  return B <= (tiles >= 256 ? 2048 : 1024);
+  return B <= (tiles >= 256 && 4l * d_in >= 3l * hidden ? 2048 : 1024);
 }
 
 // One operand slice: rows r0 .. r0 + 31 (R real rows, row R the constant 1 if ONES), k0 .. k0 + 31, as four 16-byte
@@ -700,8 +700,10 @@ __global__ __launch_bounds__(64 * NW) void dense_small_gemm_kernel(const SmallGe
   if (!second) {
     // Workgroups go to the eight XCDs in turn, each with an L2 of its own: XCD x takes a run of consecutive tiles of
     // the list "panels of eight tile columns, row by row inside a panel", a compact block of the output, so that it
-    // reads a few row strips of A and column strips of B instead of all of one operand.
-    const int gx = gridDim.x, T = gx * ny0, L = blockIdx.x + gx * blockIdx.y;
+    // reads a few row strips of A and column strips of B instead of all of one operand.  The list is of the first product's
+    // tiles alone: with the rows of a taller second product in it (a hidden layer wider than the input) some XCDs had nothing to do.
+    const int gx = (p0.M + (p0.a_ones ? 1 : 0) + 31) >> 5, T = gx * ny0, L = blockIdx.x + gridDim.x * blockIdx.y;
+    if (L >= T) return;
     const int xcd = L & 7, i = L >> 3, qn = T >> 3, rn = T & 7;
     const int t = xcd * qn + min(xcd, rn) + i;
     const int p = t / (gx * 8), rem = t - p * (gx * 8), w = min(8, ny0 - 8 * p);

@@ -52,6 +52,7 @@ def test_two_layer_networks_of_widths_off_the_vector_size(d_in, hidden, classes,
 @pytest.mark.parametrize("d_in,hidden,classes,batch,small", [
     (104, 50, 10, 1024, True), (104, 50, 10, 1025, False),  # few tiles of weights
     (513, 449, 3, 2048, True), (513, 449, 3, 2049, False),  # 270 of them
+    (63, 511, 3, 1024, True), (252, 1000, 3, 2048, True),   # more tiles in the second product than in the first
     (104, 52, 10, 4096, True)])                             # whole groups of four floats: any batch
 def test_two_layer_networks_where_the_batch_is_a_long_k(d_in, hidden, classes, batch, small):
     """Off the vector size the clipped sums leave the kernel whose workgroups take the whole batch as their K (which also
