@@ -317,9 +317,7 @@ static void plan_direct_conv(Layer &l, int maxB, const dp_plan_options &opt) {
   // weight gradient
   const bool flat = g.C * 9 <= 32 && g.D <= 32;
   if (flat) l.split_wg = false;
-  // (one workgroup per example makes the Gram kernel of 8x8 planes slow at small batches: 192 -> 192 channels at 61
-  // examples 40 against 32 us, 128 -> 128 at 256 examples 30 against 46)
-  if (l.split_wg && l.gram && g.OH == 8 && maxB < 96 && !l.wino_wgu) l.gram = false;
+  if (l.split_wg && l.gram && g.OH == 8 && !l.wino_wgu && split_wgrad_beats_gram(maxB, g.C, g.D)) l.gram = false;
   l.split_norm = l.split_wg && !l.gram && !l.wino_wgu;
   if ((g.C >= 16 || flat) && (g.OW & 3) == 0 && (g.W & 3) == 0) {
     int db = g.D <= 32 ? 1 : (g.D <= 64 ? 2 : 4);

@@ -348,10 +348,7 @@ static int launch_one(hipStream_t st, const SplitWgArgs &a, int groups) {
 }
 
 int split_wgrad_norm(hipStream_t st, const SplitWgArgs &a) {
-  const int cb = (a.C + 31) / 32, dbl = (a.D + 31) / 32;
-  // two blocks of output channels per workgroup share its input rows; where that wastes none and leaves the chip two
-  // workgroups per CU
-  const bool two = dbl % 2 == 0 && (long)a.B * cb * (dbl / 2) >= 512;
+  const bool two = split_wgrad_pairs(a.B, a.C, a.D);
   if (a.W == 4) return launch_one<4, 1, true>(st, a, (a.B + 3) / 4);
   if (a.W == 8) return two ? launch_one<8, 2, true>(st, a, a.B) : launch_one<8, 1, true>(st, a, a.B);
   if (a.W == 16) return two ? launch_one<16, 2, true>(st, a, a.B) : launch_one<16, 1, true>(st, a, a.B);

@@ -105,6 +105,21 @@ def test_convolutions_on_the_bf16_matrix_units(cin, widths, plane, act, pool, ba
     _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} recomputed", stepper=st)
 
 
+@pytest.mark.parametrize("cin,cout,max_batch,norm", [
+    (64, 128, 128, "split"), (64, 128, 160, "gram"), (96, 96, 120, "split"), (128, 128, 128, "split"), (128, 128, 160, "gram"),
+    (192, 192, 90, "split"), (192, 192, 128, "gram"), (256, 256, 64, "split"), (256, 256, 90, "gram"), (128, 128, 257, "gram")])
+def test_norms_of_8x8_planes_take_the_faster_kernel(cin, cout, max_batch, norm):
+    from paper_2010_09063_amd import DpStep
+    m = W.model(W.image_input(cin, 8, 8), [W.conv2d(cin, cout, 3, stride=1, pad=1, act="tanh"), W.avgpool2d(2, 2), W.dense(16 * cout, 3)], 3)
+    rng = np.random.default_rng(cin)
+    x, y = W.make_inputs(m, 5, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.3)
+    st = DpStep(m, max_batch)
+    assert st.dp_step_describe_plan()[0]["norm"] == norm
+    _check_all_regimes(m, x, y, theta, f"8x8 {cin}->{cout} {norm}", stepper=st)
+    st.dp_step_free()
+
+
 def test_split_convolutions_add_no_bias():
     """The bf16 instruction rounds its sums downwards.  A bias gradient adds up 32,768 backprops here: an error of 2**-24 of
     each with one sign shows as 1e-5 of the tensor's size (1.1e-5 with all six products in one accumulator); with random
