@@ -43,10 +43,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lk = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kp = wave % KW, db = wave / KW;
   const int C = a.C, D = a.D, H = a.H, HW = H * W_;
-  const int c0 = blockIdx.x * 32, d0 = blockIdx.z * 32 * DBW;
-  const bool bias_wg = blockIdx.x == 0;
+  // (groups of examples and blocks of input channels share the x dimension of the grid: the others end at 65,535)
+  const int cblocks = (C + 31) >> 5, group = (int)blockIdx.x / cblocks, cblk = (int)blockIdx.x - group * cblocks;
+  const int c0 = cblk * 32, d0 = blockIdx.y * 32 * DBW;
+  const bool bias_wg = cblk == 0;
   constexpr int EX_BAND = W_ == 4 ? 4 : 1;
-  const int ex0 = NORM ? (int)blockIdx.y * EX_BAND : (int)blockIdx.y * a.ex_per_block;
+  const int ex0 = group * (NORM ? EX_BAND : a.ex_per_block);
   const int ex1 = NORM ? min(a.B, ex0 + EX_BAND) : min(a.B, ex0 + a.ex_per_block);
   const int bands = W_ == 4 ? 1 : H / G::TR;
 
@@ -313,7 +315,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o, 64);
-    const long slot = (long)(a.slot0 + (int)(blockIdx.x * gridDim.z + blockIdx.z)) * a.slot_stride;
+    const long slot = (long)(a.slot0 + (int)(cblk * gridDim.y + blockIdx.y)) * a.slot_stride;
     if constexpr (APART) {
       if (lane == 0 && mine) a.slots[slot + e] = n2;
     } else {
@@ -323,7 +325,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
       if (tid == 0 && mine) a.slots[slot + e] = (red[0] + red[1]) + (red[2] + red[3]);
     }
   } else {
-    float *pp = a.part + (long)blockIdx.y * a.part_stride;
+    float *pp = a.part + (long)group * a.part_stride;
 #pragma unroll
     for (int r = 0; r < RN; ++r) {
       const int d = dw + 8 * ((r0 + r) >> 2) + 4 * lk + ((r0 + r) & 3);
@@ -342,9 +344,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W_ == 4 ? 1
 
 template <int W_, int DBW, bool NORM>
 static int launch_one(hipStream_t st, const SplitWgArgs &a, int groups) {
-  dim3 grid((a.C + 31) / 32, groups, (a.D + 32 * DBW - 1) / (32 * DBW));
+  const int cblocks = (a.C + 31) / 32;
+  dim3 grid((unsigned)cblocks * groups, (a.D + 32 * DBW - 1) / (32 * DBW));
   hipLaunchKernelGGL((split_wgrad_kernel<W_, DBW, NORM>), grid, dim3(256), 0, st, a);
-  return (int)(grid.x * grid.z);
+  return cblocks * (int)grid.y;
 }
 
 int split_wgrad_norm(hipStream_t st, const SplitWgArgs &a) {

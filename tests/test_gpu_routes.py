@@ -120,6 +120,26 @@ def test_norms_of_8x8_planes_take_the_faster_kernel(cin, cout, max_batch, norm):
     st.dp_step_free()
 
 
+def test_norm_kernel_above_65535_examples():
+    """One workgroup per example, in a dimension of the grid that goes that far.  Six examples 11,000 times over: the sum
+    is 11,000 times theirs."""
+    from oracle import dpsgd_oracle as O
+    from paper_2010_09063_amd import DpStep
+    from tests.gpu_util import assert_parity, run_gpu
+    m = W.model(W.image_input(16, 8, 8), [W.conv2d(16, 20, 3, stride=1, pad=1, act="tanh"), W.avgpool2d(4, 4), W.dense(80, 3)], 3)
+    rng = np.random.default_rng(7)
+    x, y = W.make_inputs(m, 6, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.3)
+    n = 11000
+    st = DpStep(m, 6 * n)
+    assert st.dp_step_describe_plan()[0]["norm"] == "split"
+    st_out, norms = run_gpu(m, theta, np.tile(x, (n,) + (1,) * (x.ndim - 1)), np.tile(y, n), 0.5, 0.0, 0, stepper=st)
+    st.dp_step_free()
+    ref = O.dp_step(m, theta, x, y, 0.5, 0.0, 0)
+    assert_parity(m, st_out, n * np.asarray(ref["clipped_sum"]), "66,000 examples", n * np.asarray(ref["abs_sum"]))
+    assert np.allclose(norms.reshape(n, 6), np.asarray(ref["norms"])[None], rtol=1e-4)
+
+
 def test_split_convolutions_add_no_bias():
     """The bf16 instruction rounds its sums downwards.  A bias gradient adds up 32,768 backprops here: an error of 2**-24 of
     each with one sign shows as 1e-5 of the tensor's size (1.1e-5 with all six products in one accumulator); with random
