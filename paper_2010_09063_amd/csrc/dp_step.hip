@@ -703,7 +703,8 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
     const bool emb = l.d.kind == DP_EMBEDDING;
     if (!c->bag) { // (bag_net_kernel keeps them in one workgroup)
       rc = dev_alloc(c, &l.a, mb * l.out_size + (emb ? SPLIT_ROWS_SLACK : 0)); // embedding: the gathered rows x[B, T, D]
-      if (rc == DP_OK) rc = dev_alloc(c, &l.g, mb * std::max<long>(l.out_size, &l == &c->L.back() ? 16 : 0)); // (the loss gradient: rows of up to 16 floats)
+      if (rc == DP_OK && l.d.kind != DP_LSTM_SEQ) // (its recurrence takes the gradient of the mean that follows it)
+        rc = dev_alloc(c, &l.g, mb * std::max<long>(l.out_size, &l == &c->L.back() ? 16 : 0)); // (the loss gradient: rows of up to 16 floats)
     }
     if (rc == DP_OK && l.d.kind == DP_MAXPOOL2D) rc = dev_alloc(c, &l.arg, mb * l.out_size);
     if (rc == DP_OK && l.p_count > 0) {

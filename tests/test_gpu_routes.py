@@ -234,3 +234,16 @@ def test_lstm_products_with_weights_in_registers(dim, hidden, seq, batch, out):
     x, y = W.make_inputs(m, batch, rng, zipf_exponent=0.8)
     theta = W.init_params(m, rng, bias_scale=0.3) * np.float32(2)
     _check_all_regimes(m, x, y, theta, f"lstm {out} D{dim} H{hidden} T{seq} B{batch}")
+
+
+def test_sequence_mean_holds_one_hidden_sequence():
+    """The network with a mean over the hidden states needs no [batch][steps][hidden] buffer that the one on the last state
+    does without: the recurrence takes the mean's gradient, and hidden states are there for the weight gradient anyway."""
+    from paper_2010_09063_amd import DpStep
+    ws = []
+    for lstm, mean in ((W.lstm_last, []), (W.lstm_seq, [W.seq_mean()])):
+        m = W.model(W.token_input(64), [W.embedding(50, 8), lstm(8, 100)] + mean + [W.dense(100, 2)], 2)
+        st = DpStep(m, 64)
+        ws.append(st.workspace_bytes)
+        st.dp_step_free()
+    assert ws[1] - ws[0] < 4 * 64 * 64 * 100 // 4, ws
