@@ -254,7 +254,8 @@ int dp_step_profile_read(dp_ctx *ctx, int cap, const char **labels, int *launche
 /*
  * dp_step_describe_plan -- which kernel family each parameter layer was planned on, as text
  * "<layer>:fwd=..,bwd=..,norm=..,sum=..;" ("mf32"/"mf64"/"mf": minimal-filtering form, 16 multiplies where the
- * direct form has 36; "gram"; "+store"/"weighted": stored per-example gradients).  Utility, no passage; the
+ * direct form has 36; "split": fp32 operands in three pieces on the bf16 matrix units; "gram"; "pairs": (token, example)
+ * pairs; "+store"/"weighted": stored per-example gradients).  Utility, no passage; the
  * benchmark uses it to price each launch by the multiplies its route really issues.
  *   buf, cap   host buffer; DP_EINVAL if the text does not fit.
  */

@@ -2137,7 +2137,13 @@ extern "C" int dp_step_describe_plan(const dp_ctx *c, char *buf, size_t cap) {
       if (c->bag) { fwd = norm = "fused"; sum = "pairs"; }
       break;
     case DP_LSTM_LAST:
-    case DP_LSTM_SEQ: fwd = "recurrence"; bwd = "recurrence"; norm = l.gst ? "generic+store" : "generic"; sum = l.gst ? "weighted" : "generic"; break;
+    case DP_LSTM_SEQ:
+      fwd = l.frag_x ? "split+recurrence" : "generic+recurrence";
+      bwd = l.frag_dx ? "recurrence+split" : "recurrence+generic";
+      norm = l.lstm_wg ? "split" : "generic";
+      sum = l.gst ? "weighted" : norm;
+      if (l.gst) norm += "+store";
+      break;
     default: break;
     }
     o += std::to_string(i) + ":fwd=" + fwd + ",bwd=" + bwd + ",norm=" + norm + ",sum=" + sum + ";";

@@ -555,22 +555,36 @@ def test_long_sequence_stored_gradients():
 
 @pytest.mark.parametrize("seq_len", [300, 700, 1024])
 def test_long_token_sequences(seq_len):
-    """Sequences above 256 and above 512 steps: the per-example sort of the embedding norm holds two or four keys
-    per thread (few distinct tokens, so every example has long runs of duplicates to add before squaring)."""
+    """Sequences above 256 and above 512 steps: the per-example sorts hold two or four keys per thread (few distinct
+    tokens, so every example has long runs of duplicates to add before squaring), in the kernel of the whole network, in
+    the one that sums an example's rows below other layers, and in the norm of the sorted lists."""
     m = W.cfg6_embedding(vocab=37, seq_len=seq_len, dim=12)
     rng = np.random.default_rng(seq_len)
     x, y = W.make_inputs(m, 9, rng, zipf_exponent=0.7)
     theta = W.init_params(m, rng, bias_scale=0.2) * np.float32(4)
     _check_all_regimes(m, x, y, theta, f"embedding/T{seq_len}")
+    from paper_2010_09063_amd import DpStep
+    for option, routes in (("no_fused_dense", ("pairs", "pairs")), ("no_side_stream", ("sorted-segments", "scatter"))):
+        st = DpStep(m, len(y), **{option: 1})
+        plan = st.dp_step_describe_plan()[0]
+        assert (plan["norm"], plan["sum"]) == routes
+        _check_all_regimes(m, x, y, theta, f"embedding/T{seq_len}/{option}", stepper=st)
 
 
-def test_large_vocabulary_embedding_path():
-    """Vocabularies above the LDS-histogram limit take the plain-atomic bucket kernels."""
-    m = W.cfg5_lstm(vocab=20000, seq_len=24, dim=20, hidden=33)
+@pytest.mark.parametrize("vocab,dim,options,route", [
+    (20000, 20, {}, "pairs"),
+    (20000, 20, dict(no_single_bucket=1), "scatter"),  # above the LDS histogram's limit: the plain-atomic bucket kernels
+    (97300, 100, {}, "scatter"),                       # a table that does not fit the LDS of the pairs' workgroups: the same, on the side stream
+], ids=["pairs", "lists", "too large"])
+def test_large_vocabulary_embedding_path(vocab, dim, options, route):
+    from paper_2010_09063_amd import DpStep
+    m = W.cfg5_lstm(vocab=vocab, seq_len=24, dim=dim, hidden=33)
     rng = np.random.default_rng(8)
-    x, y = W.make_inputs(m, 11, rng)
+    x, y = W.make_inputs(m, 11 if vocab < 50000 else 3, rng)
     theta = W.init_params(m, rng, bias_scale=0.2) * np.float32(3)
-    _check_all_regimes(m, x, y, theta, "lstm/V20000/H33")
+    st = DpStep(m, len(y), **options)
+    assert st.dp_step_describe_plan()[0]["sum"] == route
+    _check_all_regimes(m, x, y, theta, f"lstm/V{vocab}/H33/{route}", stepper=st)
 
 
 @pytest.mark.parametrize("build", [W.cfg5_lstm, W.paper_lstm], ids=["last", "seq"])
@@ -584,9 +598,9 @@ def test_lstm_hidden_sizes(hidden, build):
 
 
 def test_lstm_weight_gradient_routes():
-    """The per-example LSTM weight gradient on 16x16 MFMA blocks (one example per two workgroups) at shapes other
-    than the benchmark's: one and two column halves, row counts that end inside a block, sequences shorter than one
-    chunk of 32 steps, ending inside a chunk, and of several chunks (with and without stored gradients); then the
+    """The per-example LSTM weight gradient on the bf16 matrix units (one example per two workgroups) at shapes other
+    than the benchmark's: one and two column halves, row counts that end inside a block of 32, sequences shorter than
+    one unit of 16 steps, ending inside a unit, and of several units (with and without stored gradients); then the
     benchmark shape on the generic contraction."""
     rng = np.random.default_rng(12)
     for build in (W.cfg5_lstm, W.paper_lstm):

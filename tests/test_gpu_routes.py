@@ -25,6 +25,8 @@ def _tokens(batch, seq, vocab, rng, kind):
     (2000, 20, 1024, 4, 70, "uniform"),   # four keys per thread; more pairs than a workgroup's list holds at a time
     (5000, 8, 40, 3, 1100, "zipf"),       # more examples than a pass takes; tokens of several chunks
     (70000, 36, 12, 2, 33, "uniform"),    # a table too large for 256 workgroups' LDS
+    (300, 129, 40, 3, 9, "zipf"),         # rows wider than the kernel of the whole network takes: pairs with rows of their own
+    (90, 132, 300, 16, 5, "zipf"),
 ])
 def test_embedding_mean_classifier_network(vocab, dim, seq, classes, batch, kind):
     from paper_2010_09063_amd import DpStep
@@ -34,7 +36,7 @@ def test_embedding_mean_classifier_network(vocab, dim, seq, classes, batch, kind
     y = rng.integers(0, classes, size=batch).astype(np.int32)
     theta = W.init_params(m, rng, bias_scale=0.2) * np.float32(4)
     st = DpStep(m, batch)
-    assert st.dp_step_describe_plan()[0]["sum"] == "pairs"
+    assert _routes(st, 1) == ["fused - fused pairs" if dim <= 128 else "gather - pairs pairs"]
     _check_all_regimes(m, x, y, theta, f"embedding V{vocab} D{dim} T{seq} N{classes} B{batch} {kind}", stepper=st)
 
 
@@ -75,17 +77,35 @@ def test_two_layer_networks_where_the_batch_is_a_long_k(d_in, hidden, classes, b
     assert ("finalize_noise" not in labels) == small, labels
 
 
-@pytest.mark.parametrize("cin,widths,plane,act,pool,batch", [
-    (3, (16, 48), (32, 32), "tanh", "max", 3),      # one and two blocks of output channels, the second half empty
-    (3, (48, 100, 20), (4, 32), "relu", "avg", 5),  # the fewest rows of a 32-wide plane; ragged blocks on both sides
-    (16, (96, 33), (16, 16), "tanh", "max", 4),     # three blocks; one channel past a block
-    (17, (20, 70), (4, 16), "relu", "avg", 3),      # a chunk of sixteen input channels and one more
-    (16, (40, 130), (8, 8), "tanh", "avg", 9),      # norms of both kinds on 8x8 planes
-    (24, (64, 16), (4, 8), "relu", "max", 7),       # two images of a tile, a ragged last tile
-    (32, (64, 10), (4, 4), "relu", "avg", 13),      # four images of a tile; batch sums over a ragged last run
-    (16, (160, 32), (8, 4), "tanh", "max", 1),
+def _routes(st, layers):
+    plan = st.dp_step_describe_plan()
+    return [" ".join(plan[l][k] for k in ("fwd", "bwd", "norm", "sum")) for l in range(layers)]
+
+
+# the last column: the kernels of each convolution (forward, backward-data, norm, clipped sum)
+@pytest.mark.parametrize("cin,widths,plane,act,pool,batch,routes", [
+    (3, (16, 48), (32, 32), "tanh", "max", 3,      # one and two blocks of output channels, the second half empty
+     ["first - direct+store weighted", "split+maxpool split split+store weighted"]),
+    (3, (48, 100, 20), (4, 32), "relu", "avg", 5,  # the fewest rows of a 32-wide plane; ragged blocks on both sides
+     ["direct - split split", "split split split split", "split+avgpool split split split"]),
+    (16, (96, 33), (16, 16), "tanh", "max", 4,     # three blocks; one channel past a block
+     ["split - split+store weighted", "split+maxpool split split+store weighted"]),
+    (17, (20, 70), (4, 16), "relu", "avg", 3,      # a chunk of sixteen input channels and one more
+     ["split - split split", "split+avgpool split split split"]),
+    (16, (40, 130), (8, 8), "tanh", "avg", 9,
+     ["split - split split", "split+avgpool split split split"]),
+    (24, (64, 16), (4, 8), "relu", "max", 7,       # two images of a tile, a ragged last tile
+     ["split - direct direct", "split+maxpool split generic generic"]),
+    (32, (64, 10), (4, 4), "relu", "avg", 13,      # four images of a tile; batch sums over a ragged last run
+     ["split - gram split", "split+avgpool direct split split"]),
+    (16, (160, 32), (8, 4), "tanh", "max", 1,
+     ["split - ws ws", "split+maxpool split generic generic"]),
+    # norms with two blocks of output channels per workgroup (from 512 workgroups on), a plane of each width
+    (130, (60,), (8, 8), "tanh", "avg", 104, ["split+avgpool - split split"]),
+    (64, (128,), (16, 16), "tanh", "avg", 128, ["mf64+avgpool - split+store weighted"]),
+    (40, (128,), (8, 32), "tanh", "avg", 128, ["mf64+avgpool - split+store weighted"]),
 ])
-def test_convolutions_on_the_bf16_matrix_units(cin, widths, plane, act, pool, batch):
+def test_convolutions_on_the_bf16_matrix_units(cin, widths, plane, act, pool, batch, routes):
     from paper_2010_09063_amd import DpStep
     h, w = plane
     layers, c = [], cin
@@ -98,10 +118,11 @@ def test_convolutions_on_the_bf16_matrix_units(cin, widths, plane, act, pool, ba
     x, y = W.make_inputs(m, batch, rng, x_dist="normal")
     theta = W.init_params(m, rng, bias_scale=0.3)
     st = DpStep(m, batch)
-    plan = st.dp_step_describe_plan()
-    assert any(v.startswith("split") for l in range(len(widths)) for v in plan[l].values()), plan
+    assert _routes(st, len(widths)) == routes
     _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} {act} {pool} B{batch}", stepper=st)
     st = DpStep(m, batch, no_stored_gradients=1)
+    assert _routes(st, len(widths)) == [r.replace("direct+store weighted", "direct direct").replace("split+store weighted", "split split")
+                                        for r in routes]
     _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} recomputed", stepper=st)
 
 
@@ -216,24 +237,29 @@ def test_split_products_have_no_one_sided_error(kind, private):
 
 
 @pytest.mark.parametrize("out", ["last", "seq"])
-@pytest.mark.parametrize("dim,hidden,seq,batch", [
-    (1, 1, 1, 1),        # the smallest of everything
-    (17, 33, 5, 7),      # rows that start on 4 bytes; K one past a step, N past a block of columns
-    (112, 104, 33, 3),   # the widest that the projection's and the input gradient's waves hold; a ragged last tile of rows
-    (113, 105, 3, 5),    # one past both: the tiled contraction
-    (128, 16, 4, 9),     # the projection with its K in two halves
-    (9, 100, 2, 6),      # the recurrence's narrower padding filled, an even number of steps
-    (12, 128, 2, 3),     # its wider padding filled
-    (64, 56, 140, 3),    # several tiles per workgroup's run would need more rows: stored per-example gradients
+@pytest.mark.parametrize("dim,hidden,seq,batch,projection,dx", [
+    (1, 1, 1, 1, "split", "split"),           # the smallest of everything
+    (17, 33, 5, 7, "split", "split"),         # rows that start on 4 bytes; K one past a step, N past a block of columns
+    (112, 104, 33, 3, "split", "split"),      # the widest that the projection's and the input gradient's waves hold; a ragged last tile of rows
+    (113, 105, 3, 5, "generic", "generic"),   # one past both: the tiled contraction
+    (128, 16, 4, 9, "split", "split"),        # the projection with its K in two halves
+    (9, 100, 2, 6, "split", "split"),         # the recurrence's narrower padding filled, an even number of steps
+    (12, 128, 2, 3, "split", "generic"),      # its wider padding filled
+    (128, 128, 37, 5, "generic", "generic"),  # nine blocks of rows: three staged blocks per wave in the weight gradient
+    (64, 56, 140, 3, "split", "split"),       # several tiles per workgroup's run would need more rows: stored per-example gradients
 ])
-def test_lstm_products_with_weights_in_registers(dim, hidden, seq, batch, out):
+def test_lstm_products_with_weights_in_registers(dim, hidden, seq, batch, projection, dx, out):
+    from paper_2010_09063_amd import DpStep
     layers = [W.embedding(40, dim), (W.lstm_last if out == "last" else W.lstm_seq)(dim, hidden)]
     layers += ([W.seq_mean()] if out == "seq" else []) + [W.dense(hidden, 3)]
     m = W.model(W.token_input(seq), layers, 3)
     rng = np.random.default_rng(dim + hidden)
     x, y = W.make_inputs(m, batch, rng, zipf_exponent=0.8)
     theta = W.init_params(m, rng, bias_scale=0.3) * np.float32(2)
-    _check_all_regimes(m, x, y, theta, f"lstm {out} D{dim} H{hidden} T{seq} B{batch}")
+    st = DpStep(m, batch)
+    assert _routes(st, 2) == ["gather - pairs pairs", f"{projection}+recurrence recurrence+{dx} " +
+                              ("split+store weighted" if seq >= 128 else "split split")]
+    _check_all_regimes(m, x, y, theta, f"lstm {out} D{dim} H{hidden} T{seq} B{batch}", stepper=st)
 
 
 def test_sequence_mean_holds_one_hidden_sequence():
@@ -247,3 +273,45 @@ def test_sequence_mean_holds_one_hidden_sequence():
         ws.append(st.workspace_bytes)
         st.dp_step_free()
     assert ws[1] - ws[0] < 4 * 64 * 64 * 100 // 4, ws
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 1e30])
+@pytest.mark.parametrize("kind", ["conv", "conv4", "lstm"])
+def test_an_example_out_of_range_stays_its_own(kind, value):
+    """One input value (a token's embedding for the LSTM) that is infinite, not a number or huge: the other examples'
+    norms do not change, and the example's own is as finite as on the fp32 kernels (1e30 squared is not, in a Gram matrix)."""
+    import torch
+    from paper_2010_09063_amd import DpStep
+    rng = np.random.default_rng(3)
+    if kind == "lstm":
+        m = W.model(W.token_input(12), [W.embedding(30, 16), W.lstm_last(16, 20), W.dense(20, 3)], 3)
+        x, y = W.make_inputs(m, 7, rng, zipf_exponent=0.5)
+        x[x == 29] = 3
+    else:
+        cin, cout, p = (16, 48, 16) if kind == "conv" else (24, 20, 4)
+        m = W.model(W.image_input(cin, p, p), [W.conv2d(cin, cout, 3, stride=1, pad=1, act="tanh"),
+                                               W.conv2d(cout, cout, 3, stride=1, pad=1, act="tanh"), W.avgpool2d(2, 2), W.dense(cout * p * p // 4, 3)], 3)
+        x, y = W.make_inputs(m, 7, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.1)
+    dev = torch.device("cuda")
+
+    def norms(theta, x, **options):
+        st, out = DpStep(m, 7, **options), torch.empty(7, device=dev)
+        tt, tx, ty = (torch.from_numpy(np.ascontiguousarray(v)).to(dev) for v in (theta, x, y))
+        st.dp_step(tt, tx, ty, 7, 1.0, 0.0, 0, torch.empty_like(tt))
+        st.dp_step_last_norms(out)
+        out = out.cpu().numpy()
+        st.dp_step_free()
+        return out
+
+    clean, bad_x, bad_theta = norms(theta, x), x.copy(), theta.copy()
+    if kind == "lstm":
+        bad_x[2, 5] = 29
+        bad_theta[29 * 16 + 4] = value
+    else:
+        bad_x.reshape(7, -1)[2, 77] = value
+    here = norms(bad_theta, bad_x)
+    plain = norms(bad_theta, bad_x, no_minimal_filtering=1, no_lstm_wgrad=1, no_rows_gemm=1, no_side_stream=1)
+    others = [0, 1, 3, 4, 5, 6]
+    assert np.array_equal(here[others], clean[others])
+    assert np.isfinite(here[2]) == np.isfinite(plain[2]), (here[2], plain[2])
