@@ -5,8 +5,9 @@
 // taken; the three that are dropped are together below 2^-24 of it with random sign, and a 32 x 32 x 16 instruction adds
 // sixteen products to the fp32 accumulator at once where v_mfma_f32_32x32x2_f32 rounds after every second one.
 // Measured against 64 bits the sums are no further off than the fp32 instruction's.  Six instructions of 32 cycles per 16
-// of K against eight of 64.  (An infinite operand gives NaN: its remainder is inf - inf.  So it does in the
-// minimal-filtering kernels.)
+// of K against eight of 64.  Every finite operand is split exactly.  An infinite one gives NaN in all that it is multiplied
+// with, also where fp32 gives an infinity: its remainder is inf - inf, and infinity times a piece that is zero.  So it does in
+// the minimal-filtering kernels.  (The example's norm is NaN on the fp32 kernels too: a saturated unit's zero times infinity.)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -23,7 +24,8 @@ __device__ __forceinline__ uint32_t sb_pack(float a, float b) { // v_cvt_pk_bf16
 }
 // two values -> their three pieces, packed two by two
 __device__ __forceinline__ void sb_split2(float a, float b, uint32_t &h, uint32_t &m, uint32_t &l) {
-  h = sb_pack(a, b);
+  const float top = __uint_as_float(0x7F7F0000u); // the largest bf16: what lies above, a mask of the type's lowest value, would round to infinity
+  h = sb_pack(__builtin_amdgcn_fmed3f(a, -top, top), __builtin_amdgcn_fmed3f(b, -top, top));
   a -= __uint_as_float(h << 16); b -= __uint_as_float(h & 0xFFFF0000u);
   m = sb_pack(a, b);
   a -= __uint_as_float(m << 16); b -= __uint_as_float(m & 0xFFFF0000u);

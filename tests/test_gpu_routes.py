@@ -275,11 +275,11 @@ def test_sequence_mean_holds_one_hidden_sequence():
     assert ws[1] - ws[0] < 4 * 64 * 64 * 100 // 4, ws
 
 
-@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 1e30])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 1e30, float(np.finfo(np.float32).max), float(np.finfo(np.float32).min)])
 @pytest.mark.parametrize("kind", ["conv", "conv4", "lstm"])
 def test_an_example_out_of_range_stays_its_own(kind, value):
-    """One input value (a token's embedding for the LSTM) that is infinite, not a number or huge: the other examples'
-    norms do not change, and the example's own is as finite as on the fp32 kernels (1e30 squared is not, in a Gram matrix)."""
+    """One input value (a token's embedding for the LSTM) that is infinite, not a number, huge or the type's largest or
+    lowest, as a mask is (a bf16 rounds that to infinity): the other examples' norms do not change, and the example's own is as finite as on the fp32 kernels (1e30 squared is not, in a Gram matrix)."""
     import torch
     from paper_2010_09063_amd import DpStep
     rng = np.random.default_rng(3)
