@@ -76,6 +76,10 @@ def label_work(m, B, plan=None):
             fl = 2.0 * B * di * do
             if r.get("fwd") == "fused" and li == 0:   # one-layer model: forward, loss, norm, clip factor and partial sums in one launch
                 add("dense1_fused", 2 * fl + 2.0 * B * (di + do), 4.0 * (B * di + di * do + (B // 4) * (di + 1) * do))
+            elif r.get("sum") == "pairs":  # a sequence network's classifier: one launch per example, its sums beside the embedding's
+                whole = plan[0].get("fwd") == "fused"  # ... with the embedding and the mean in the same launch
+                add("bag_net" if whole else "class_head", 2 * fl + 2.0 * B * (di + do), 4.0 * (2 * B * di + di * do + 16 * B))
+                add("emb_pair_sum" if whole else "emb_scatter", fl, 4.0 * (B * di + 16 * B + di * do), layer=0)
             elif r.get("fwd") == "fused" and r.get("sum") == "joint":
                 # logit layer of a two-layer model: forward, backward-data and both norms in one launch; its clipped
                 # sum rides in the hidden layer's launch (s * delta in rows of 16 floats)
@@ -137,12 +141,21 @@ def label_work(m, B, plan=None):
             add("avgpool_bwd", 1.0 * n_in, 4.0 * (2 * n_in + n_out))
         elif k == "embedding":
             T, D_ = inp["seq_len"], L["dim"]
+            if r.get("fwd") == "fused":  # mean of the rows, norm and row per example in one launch; the batch sum over pairs
+                add("bag_net", 1.0 * B * T * D_, 4.0 * (B * T * 2 + L["vocab"] * D_ + 2 * B * D_))
+                add("emb_pair_sum", 2.0 * B * T * D_, 4.0 * (B * T + B * D_ + L["vocab"] * D_))
+                cur = o
+                continue
             add("emb_gather", 0.0, 4.0 * B * T * (2 * D_ + 1))
             add("emb_norm", 2.0 * B * T * D_, 4.0 * B * T * (D_ + 1))
-            add("emb_bucket", 0.0, 4.0 * (4 * B * T + 4 * L["vocab"]))  # counting sort: tokens read 3x, list written
+            if r.get("sum") != "pairs":
+                add("emb_bucket", 0.0, 4.0 * (4 * B * T + 4 * L["vocab"]))  # counting sort: tokens read 3x, list written
             add("emb_scatter", 2.0 * B * T * D_, 4.0 * (B * T * (D_ + 1) + L["vocab"] * D_))
         elif k == "seq_mean":
             T, D_ = cur[1], cur[2]
+            if m["layers"][li - 1]["kind"] == "lstm_seq" or plan.get(0, {}).get("fwd") == "fused":  # inside the kernel before it
+                cur = o
+                continue
             add("seq_mean_fwd", 1.0 * B * T * D_, 4.0 * B * (T * D_ + D_))
             add("seq_mean_bwd", 1.0 * B * T * D_, 4.0 * B * (T * D_ + D_))
         elif k in ("lstm_last", "lstm_seq"):
@@ -395,9 +408,10 @@ def main():
                 launches_per_step=dom["launches_per_step"],
                 algorithmic_flops_per_launch=dom["flops_per_step"] / lps,
                 algorithmic_bytes_per_launch=dom["bytes_per_step"] / lps,
-                share_of_step=dom["ms_per_step"] / max(res["ms_private_profiled"], 1e-9),
-                traffic_source="profiles/hbm_traffic.json (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this command, "
-                               "scaled by a plain copy; not re-measured by this run)")
+                share_of_step=dom["ms_per_step"] / max(res["ms_private_profiled"], 1e-9))
+    if traffic is not None:
+        roof["traffic_source"] = ("profiles/hbm_traffic.json (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE over private steps of this "
+                                  "workload, scaled by a plain copy; not re-measured by this run)")
     # the whole step three ways: flops as the survey of the method prices them (direct forms everywhere), flops of
     # the routes taken (Gram norms, weighted sums of stored gradients), and the multiplies really issued
     acc = dict(tflops_routes=res["tflops"], frac_routes=res["tflops"] / PEAK_MFMA_FP32_TFLOPS,

@@ -255,9 +255,10 @@ __global__ __launch_bounds__(LSTM_THREADS) void lstm_fwd_kernel(float *__restric
 // 4 kk + s / 4 ends up in the quad of lanes s / 4, where lane s % 4 makes that gate's gradient of it: a step is product,
 // sum, gate gradient, LDS write and one barrier, and everything else that the step needs is there before its product.
 // (With a gate's part of one unit per thread the sums went through LDS to the two waves that updated the cells, two
-// barriers a step.)  256 steps, H = 100: 222 -> 173 us at 128 examples, where a step's chain of latencies bounds it;
-// 306 -> 294 us at 512, two examples per compute unit, where the issue of 4 waves x (100 multiply-adds + 60 other
-// instructions) per SIMD does.
+// barriers a step.)  256 steps, H = 100: 222 -> 173 us at 128 examples, 306 -> 294 us at 512, two examples per compute unit.
+// Bound by the issue of vector instructions, 100 multiply-adds and about 60 others per wave and step: 1,280 of the 1,600
+// cycles of a step for two waves per SIMD, all of them for four.  (128 registers, so that two workgroups share a
+// compute unit, are two short: they spill.)
 // dh_out is [B, H].  SEQ = false: the gradient of h_T, which is all that the loss sees.  SEQ = true: the gradient of the
 // mean over every h_t: each step adds its share dh_out / T to what the later steps send back.
 template <int HP, bool SEQ>

@@ -1,4 +1,5 @@
-// fp32 products on the bf16 matrix units, without giving up fp32 operands.
+// fp32 products on the bf16 matrix units, without giving up fp32 operands (Henry, Tang, Heinecke, "Leveraging the bfloat16
+// Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019).
 //
 // An fp32 value is the exact sum of three bf16 values (8 + 8 + 8 significand bits, each the rounded remainder of the one
 // before), and a product of two such sums is nine bf16 products, of which the six down to 2^-16 of the largest are

@@ -40,9 +40,11 @@ __device__ __forceinline__ float conv_swap1(float v) { // lanes swap within pair
 // it fetches the haloed pixels with the channel as the register index, splits them once and leaves them in an LDS area
 // of its own, channels innermost ([piece][channel half][pixel][8]), so that the operand of every tap is one 16-byte
 // read per piece at a constant offset; the weight fragments come from the L2.  No barrier until the KS partial sums
-// meet.  The next chunk travels in registers meanwhile.  108 matrix instructions of 32 cycles per chunk
-// against about 300 others and 54 LDS reads: bound by the matrix units and the power they draw (a register-only loop
-// sustains 1.9 of the nominal 2.5 PFLOP/s).
+// meet.  The next chunk travels in registers meanwhile.  108 matrix instructions of 32 cycles per chunk against about 300
+// others and 54 LDS reads.  What bounds it is not the matrix units, which are busy for 10 to 34 % of the time (25 % for
+// 48 -> 48 channels on 32x32 planes at 61 examples, 30 % for 128 -> 128 on 8x8 at 256), but fetching and splitting, the
+// operands' reads (1.2 to 1.6 conflict cycles per active LDS cycle on planes up to 16 wide, none on 32) and one or two
+// waves per SIMD to cover for each other.
 template <int LW>
 struct SplitConvGeom {
   static constexpr int W = 1 << LW, ROWS = 64 / W, LD = W + 2;

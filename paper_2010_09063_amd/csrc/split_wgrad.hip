@@ -362,7 +362,8 @@ int split_wgrad_sum(hipStream_t st, SplitWgArgs a, int max_split) {
   const int cb = (a.C + 31) / 32, dbl = (a.D + 31) / 32;
   const bool two = dbl % 2 == 0;
   const int blocks = cb * (two ? dbl / 2 : dbl);
-  // about one round of two workgroups per CU; a partial row costs its write and a read by the final write
+  // about one round of two workgroups per CU (4-wide planes, whose LDS leaves room for one: two rounds); a partial row costs
+  // its write and a read by the final write
   const int want = std::max(1, std::min(max_split, (512 + blocks - 1) / blocks));
   int eps = (a.B + want - 1) / want;
   if (a.W == 4) eps = (eps + 3) / 4 * 4;
