@@ -783,9 +783,11 @@ extern "C" int dp_step_init_ex(const dp_model_desc *model, int max_batch, void *
         o.n_total = l.p_count;
       } else {
       o.C = l.geom.C; o.D = l.geom.D; o.KK = 9; o.flat = l.wg_flat ? 1 : 0;
-      o.WN = l.wg_flat ? 1 : 2;                       // wg_db is 1 or 2 here
+      // (its waves: WD along blocks of output channels, WN along the taps; more than 64 output channels get here where the
+      // specialised-wave kernel's bias exchange does not fit the plane, 24 or 28 wide for instance)
+      o.WN = l.wg_flat || l.wg_db == 4 ? 1 : 2;
       o.NW = l.wg_flat ? 1 : (l.wg_db == 1 ? 2 : 4);
-      o.NBW = l.wg_flat ? 1 : 5;
+      o.NBW = l.wg_flat ? 1 : (l.wg_db == 4 ? 9 : 5);
       const long cblocks = l.wg_flat ? 1 : ceil_div(l.geom.C, 32);
       o.n_w = cblocks * o.NW * o.NBW * 1024;
       o.n_total = o.n_w + o.D;

@@ -141,6 +141,25 @@ def test_norms_of_8x8_planes_take_the_faster_kernel(cin, cout, max_batch, norm):
     st.dp_step_free()
 
 
+@pytest.mark.parametrize("cin,cout,plane,batch,options", [
+    (48, 100, (24, 24), 5, {}), (33, 65, (16, 24), 9, {}), (16, 128, (28, 28), 2, {}),
+    (20, 96, (16, 16), 3, dict(no_minimal_filtering=1, no_specialised_waves=1))])
+def test_stored_gradients_of_wide_layers_on_the_direct_kernel(cin, cout, plane, batch, options):
+    """More than 64 output channels on planes that the specialised-wave kernel does not take: four wave groups of nine taps
+    a block of channels.  (Rows laid out for groups of five taps were too short: examples overwrote each other and the last one
+    what lies behind the buffer.)"""
+    from paper_2010_09063_amd import DpStep
+    h, w = plane
+    m = W.model(W.image_input(cin, h, w), [W.conv2d(cin, cout, 3, stride=1, pad=1, act="tanh"), W.avgpool2d(4, 4),
+                                           W.dense(cout * (h // 4) * (w // 4), 3)], 3)
+    rng = np.random.default_rng(cout)
+    x, y = W.make_inputs(m, batch, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.3)
+    st = DpStep(m, batch, **options)
+    assert _routes(st, 1)[0].endswith("direct+store weighted")
+    _check_all_regimes(m, x, y, theta, f"conv {cin}->{cout} {plane} stored rows", stepper=st)
+
+
 def test_norm_kernel_above_65535_examples():
     """One workgroup per example, in a dimension of the grid that goes that far.  Six examples 11,000 times over: the sum
     is 11,000 times theirs."""
