@@ -526,6 +526,9 @@ __global__ __launch_bounds__(256, (DB <= 2 ? 2 : 1)) void conv_s1_wgrad_kernel(c
         const int ch = cimg / a.t.NIMG, img = cimg - ch * a.t.NIMG;
         Xl[ch * a.t.XPLANE + img * a.t.IMGPL + rr * a.t.LDW + (h < a.pad ? h : a.W + h)] = 0.f;
       }
+      // ... and into the planes of a last block's channels beyond the layer's, which nothing stages: their columns are
+      // squared with the others
+      for (int e = min(xch, a.C - c0) * a.t.XPLANE + tid; e < xch * a.t.XPLANE; e += 256) Xl[e] = 0.f;
     }
   };
 

@@ -160,6 +160,31 @@ def test_stored_gradients_of_wide_layers_on_the_direct_kernel(cin, cout, plane, 
     _check_all_regimes(m, x, y, theta, f"conv {cin}->{cout} {plane} stored rows", stepper=st)
 
 
+@pytest.mark.parametrize("cin,cout,plane,options", [
+    (40, 14, (15, 32), {}), (90, 7, (16, 32), dict(no_minimal_filtering=1)), (33, 32, (32, 32), dict(no_minimal_filtering=1, no_stored_gradients=1))])
+def test_direct_norms_of_several_examples_per_workgroup(cin, cout, plane, options):
+    """Input channels that are no multiple of 32, at most 32 output channels and more examples than resident workgroups: the
+    waves add up through the staging area, and what they leave in the planes of channels that do not exist must not reach the
+    next example's norm (it was off by 4e-6 to 1.6e-4; the bar is ten times what is left)."""
+    from oracle import dpsgd_oracle as O
+    from paper_2010_09063_amd import DpStep
+    from tests.gpu_util import run_gpu
+    h, w = plane
+    m = W.model(W.image_input(cin, h, w), [W.conv2d(cin, cout, 3, stride=1, pad=1, act="tanh"), W.avgpool2d(3, 3),
+                                           W.dense(cout * (h // 3) * (w // 3), 3)], 3)
+    rng = np.random.default_rng(cin)
+    x, y = W.make_inputs(m, 7, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.3)
+    n = 120
+    st = DpStep(m, 7 * n, **options)
+    assert st.dp_step_describe_plan()[0]["norm"].startswith("direct")
+    norms = run_gpu(m, theta, np.tile(x, (n, 1, 1, 1)), np.tile(y, n), 0.5, 0.0, 0, stepper=st)[1]
+    st.dp_step_free()
+    err = np.abs(norms.reshape(n, 7) / np.asarray(O.dp_step(m, theta, x, y, 0.5, 0.0, 0)["norms"]) - 1)
+    print(f"{cin}->{cout} {plane}: norms off by up to {err.max():.1e}", flush=True)
+    assert err.max() <= 2e-6
+
+
 def test_norm_kernel_above_65535_examples():
     """One workgroup per example, in a dimension of the grid that goes that far.  Six examples 11,000 times over: the sum
     is 11,000 times theirs."""
