@@ -542,13 +542,16 @@ struct SmallGemmArgs {
 typedef float sg_f32x16 __attribute__((ext_vector_type(16)));
 #define SG_LD 33
 
+// Whether k is A's contiguous index.  Where both strides are 1 (one input feature) either reading is right for that product,
+// but a launch of two has one for both, and the clipped sums' is that of contiguous rows.
+static inline bool dense_small_gemm_kc(const SmallGemmArgs &a) { return a.a_sr != 1; }
 // 16-byte loads: base pointers, the non-unit strides and K are multiples of 4 floats; an operand whose rows are the
 // contiguous index has a row count that is one too, or rows of memory padded to the next multiple (its k stride covers
 // it), so that the last group of four may be read whole.  Everything else (a hidden width of 50) is staged with four
 // 4-byte loads in the place of each, up to the batch of dense2_small_batch.
 static inline bool dense_small_gemm_vec(const SmallGemmArgs &a) {
   auto al = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  const bool a_kc = a.a_sk == 1;
+  const bool a_kc = dense_small_gemm_kc(a);
   if (!al(a.A) || !al(a.B) || (a_kc && (a.K & 3) != 0)) return false;
   if (a_kc ? (a.a_sr & 3) != 0 : ((a.a_sk & 3) != 0 || a.a_sk < ((a.M + 3) & ~3))) return false;
   if ((a.b_sk & 3) != 0 || a.b_sk < ((a.N + 3) & ~3)) return false;
@@ -734,7 +737,7 @@ static inline void launch_dense_small_gemm(hipStream_t st, const SmallGemmArgs &
   const int ny0 = (a.N + 31) / 32, ny1 = b ? (b->N + 31) / 32 : 0;
   dim3 grid((std::max(Mtot, Mtot2) + 31) / 32, ny0 + ny1), block(64 * SG_WAVES);
   const size_t lds = dense_small_gemm_lds_bytes();
-  const bool a_kc = a.a_sk == 1;
+  const bool a_kc = dense_small_gemm_kc(a);
   const SmallGemmArgs &a2 = b ? *b : a;
   const bool vec = dense_small_gemm_vec(a) && (!b || dense_small_gemm_vec(*b));
 #define DP_SG_CASE(a_, v_)                                                                                              \

@@ -41,7 +41,7 @@ def test_embedding_mean_classifier_network(vocab, dim, seq, classes, batch, kind
 
 
 @pytest.mark.parametrize("d_in,hidden,classes,batch", [
-    (1, 1, 2, 1), (5, 31, 3, 33), (33, 32, 2, 31), (257, 129, 15, 65), (104, 50, 10, 1025), (1023, 639, 7, 96)])
+    (1, 1, 2, 1), (1, 4, 7, 8), (1, 130, 15, 33), (5, 31, 3, 33), (33, 32, 2, 31), (257, 129, 15, 65), (104, 50, 10, 1025), (1023, 639, 7, 96)])
 def test_two_layer_networks_of_widths_off_the_vector_size(d_in, hidden, classes, batch):
     """Widths that are no multiples of four floats: one short of, at and past a 32-wide tile or slice."""
     m = W.model(W.image_input(d_in), [W.dense(d_in, hidden, act="tanh"), W.dense(hidden, classes)], classes)
