@@ -11,9 +11,9 @@ struct SplitWgArgs {
   // gradients (gstore, null: not wanted) as rows [D][9][C], then the bias gradient
   float *slots; long slot_stride; int slot0;
   float *gstore; long gstride;
-  // sum: scale[b] times each example; one partial row per run of ex_per_block examples, in the parameter layout
+  // sum: scale[b] times each example; one partial row per run of bands of rows (4-wide planes: of examples), in the parameter layout
   const float *scale; float *part; long part_stride;
-  int ex_per_block;
+  int bands_per_block; // (set by the launcher)
 };
 
 static inline bool split_wgrad_fits(int H, int W) {
