@@ -87,7 +87,7 @@ def _routes(st, layers):
     (3, (16, 48), (32, 32), "tanh", "max", 3,      # one and two blocks of output channels, the second half empty
      ["first - direct+store weighted", "split+maxpool split split+store weighted"]),
     (3, (48, 100, 20), (4, 32), "relu", "avg", 5,  # the fewest rows of a 32-wide plane; ragged blocks on both sides
-     ["direct - split split", "split split split split", "split+avgpool split split split"]),
+     ["direct - split+store weighted", "split split split+store weighted", "split+avgpool split split+store weighted"]),
     (16, (96, 33), (16, 16), "tanh", "max", 4,     # three blocks; one channel past a block
      ["split - split+store weighted", "split+maxpool split split+store weighted"]),
     (17, (20, 70), (4, 16), "relu", "avg", 3,      # a chunk of sixteen input channels and one more
