@@ -76,8 +76,8 @@ struct Layer {
   int wino_f = 0, wino_b = 0;
   bool split_f = false, split_b = false; // forward / backward-data in direct form on the bf16 matrix units, three pieces per operand
   void *frag_f = nullptr, *frag_b = nullptr;
-  bool split_wg = false;   // weight gradient on the bf16 matrix units: batch sums, where no other family's apply
-  bool split_norm = false; // ... and the norm pass
+  bool split_wg = false;   // weight gradient on the bf16 matrix units: batch sums, where no other family's apply and it is ahead
+  bool split_norm = false; // ... and the norm pass, each by its own rule
   bool wino_wg = false; // batch sum of the weight gradient in the F(3x3, 2x2) form on 8x8 planes (any multiple of 64 output channels)
   bool u_f_planned = false; // pad-1 3x3 stride-1 layer with even planes: the minimal-filtering family applies
   bool wino_wgu = false;    // per-example and batch weight gradient in that form on 16- and 32-wide planes (32 / 64 output channels)
@@ -318,7 +318,8 @@ static void plan_direct_conv(Layer &l, int maxB, const dp_plan_options &opt) {
   const bool flat = g.C * 9 <= 32 && g.D <= 32;
   if (flat) l.split_wg = false;
   if (l.split_wg && l.gram && g.OH == 8 && !l.wino_wgu && split_wgrad_beats_gram(maxB, g.C, g.D)) l.gram = false;
-  l.split_norm = l.split_wg && !l.gram && !l.wino_wgu;
+  l.split_norm = l.split_wg && !l.gram && !l.wino_wgu && split_wgrad_norm_pays(maxB, g.C, g.D, g.P);
+  l.split_wg = l.split_wg && split_wgrad_sum_pays(maxB, g.C, g.D, g.P);
   if ((g.C >= 16 || flat) && (g.OW & 3) == 0 && (g.W & 3) == 0) {
     int db = g.D <= 32 ? 1 : (g.D <= 64 ? 2 : 4);
     int pch_max = flat ? 256 : (db <= 2 ? 128 : 64);

@@ -25,6 +25,29 @@ static inline bool split_wgrad_pairs(int B, int C, int D) {
   const int cb = (C + 31) / 32, db = (D + 31) / 32;
   return db % 2 == 0 && (long)B * cb * (db / 2) >= 512;
 }
+// The general kernels' tiles do not pad the channels to blocks of 32.  Whether this kernel is ahead of them all the same;
+// the figures are us of the norm pass with the clipped sum and, after the comma, of the plain batch sum: theirs -> this one's
+// (C -> D channels, plane, examples).
+//  - 4x4 planes, one step of work per example: from more than two columns of their tiles (9 C + 1 > 128) on.
+//      8 ->  8 at 256  16 -> 21, 8 -> 10     12 -> 97 at 600  27 -> 35, 16 -> 23    16 -> 16 at 600  30 -> 21, 14 -> 11
+//  - One column of their tiles (9 C + 1 <= 64) by more than 32 rows, where theirs is one whole tile or more:
+//      6 -> 97 on 32x32 at 256  84 -> 103, 70 -> 90    3 -> 97 on 16x16 at 600  34 -> 80, 30 -> 57    4 -> 48 on 8x8 at 600  27 -> 44, 15 -> 19
+//    Up to 64 rows theirs takes as long as 64, and the norm is ahead at up to 256 examples of 192 pixels or more:
+//      6 -> 64 on 32x32 at 256  91 -> 65, 45 -> 53     3 -> 33 on 16x16 at 61   27 -> 24, 10 -> 11    (64 rows by 32: 22 -> 29 at 256)
+//  - Few examples on small planes, where either launch is short:
+//      8 ->  8 on 8x8 at 61     18 -> 19,  8 -> 10     8 ->  8 on 8x16 at 61    20 -> 18,  8 -> 10
+//  - Up to five input channels, norms of large batches:
+//      4 -> 16 on 16x16 at 600  33 -> 39, 38 -> 24     4 -> 16 on 8x16 at 600   24 -> 30, 18 -> 17
+static inline bool split_wgrad_sum_pays(int B, int C, int D, int P) {
+  if (P == 16) return 9 * C + 1 > 128;
+  if (D > 32) return 9 * C + 1 > 64;
+  return C >= 16 || B > 128 || P > 128;
+}
+static inline bool split_wgrad_norm_pays(int B, int C, int D, int P) {
+  if (P == 16) return 9 * C + 1 > 128;
+  if (D > 32) return 9 * C + 1 > 64 || (P >= 192 && B <= 256 && (D < 64 || (D == 64 && 9 * C + 1 > 32)));
+  return (C >= 16 || B > 128 || P > 64) && (C > 5 || B < 512);
+}
 // Norms on 8x8 planes: whether this kernel is ahead of the one that forms Gram matrices (conv_gram.h), whose workgroup of
 // one example takes a time that is flat up to a round of 256 and linear in 9 C + D, while this one's is linear in the blocks.
 // Fitted to us, Gram and this (C -> D channels: at 64, 96, 128, 160, 256 examples):

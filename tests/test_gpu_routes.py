@@ -87,7 +87,9 @@ def _routes(st, layers):
     (3, (16, 48), (32, 32), "tanh", "max", 3,      # one and two blocks of output channels, the second half empty
      ["first - direct+store weighted", "split+maxpool split split+store weighted"]),
     (3, (48, 100, 20), (4, 32), "relu", "avg", 5,  # the fewest rows of a 32-wide plane; ragged blocks on both sides
-     ["direct - split+store weighted", "split split split+store weighted", "split+avgpool split split+store weighted"]),
+     ["direct - generic+store weighted", "split split split+store weighted", "split+avgpool split split+store weighted"]),
+    (4, (40, 12), (16, 16), "tanh", "avg", 9,      # few columns: split norms, general batch sums (with stored rows: without weights)
+     ["direct - split+store weighted", "split+avgpool direct split+store weighted"]),
     (16, (96, 33), (16, 16), "tanh", "max", 4,     # three blocks; one channel past a block
      ["split - split+store weighted", "split+maxpool split split+store weighted"]),
     (17, (20, 70), (4, 16), "relu", "avg", 3,      # a chunk of sixteen input channels and one more
@@ -121,8 +123,11 @@ def test_convolutions_on_the_bf16_matrix_units(cin, widths, plane, act, pool, ba
     assert _routes(st, len(widths)) == routes
     _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} {act} {pool} B{batch}", stepper=st)
     st = DpStep(m, batch, no_stored_gradients=1)
-    assert _routes(st, len(widths)) == [r.replace("direct+store weighted", "direct direct").replace("split+store weighted", "split split")
-                                        for r in routes]
+    recomputed = [r.replace("direct+store weighted", "direct direct").replace("generic+store weighted", "generic generic")
+                  .replace("split+store weighted", "split split") for r in routes]
+    if widths[0] > 32 and 9 * cin + 1 <= 64:
+        recomputed[0] = recomputed[0].replace("split split", "split generic")
+    assert _routes(st, len(widths)) == recomputed
     _check_all_regimes(m, x, y, theta, f"conv {cin}->{widths} {plane} recomputed", stepper=st)
 
 
@@ -203,6 +208,26 @@ def test_norm_kernel_above_65535_examples():
     ref = O.dp_step(m, theta, x, y, 0.5, 0.0, 0)
     assert_parity(m, st_out, n * np.asarray(ref["clipped_sum"]), "66,000 examples", n * np.asarray(ref["abs_sum"]))
     assert np.allclose(norms.reshape(n, 6), np.asarray(ref["norms"])[None], rtol=1e-4)
+
+
+# Few input channels, whose padding to blocks of 32 costs more than the faster unit gives: norms and sums, each by its rule.
+@pytest.mark.parametrize("cin,cout,plane,batch,norm,total", [
+    (7, 97, (16, 16), 61, "generic", "generic"), (8, 97, (16, 16), 61, "split", "split"),  # one column of 64, a second one
+    (7, 64, (16, 16), 61, "split", "generic"), (7, 65, (16, 16), 61, "generic", "generic"),
+    (3, 63, (16, 16), 61, "split", "generic"), (3, 64, (16, 16), 61, "generic", "generic"),
+    (7, 64, (16, 16), 257, "generic", "generic"), (7, 64, (8, 16), 61, "generic", "generic"), (7, 64, (6, 32), 61, "split", "generic"),
+    (14, 9, (4, 4), 61, "generic", "generic"), (15, 9, (4, 4), 61, "split", "split"),
+    (15, 32, (8, 8), 128, "generic", "generic"), (15, 32, (8, 8), 129, "split", "split"), (15, 33, (8, 8), 9, "split", "split"),
+    (8, 32, (8, 16), 128, "split", "generic"), (8, 32, (8, 16), 129, "split", "split"), (8, 32, (6, 32), 9, "split", "split"),
+    (5, 8, (16, 16), 511, "split", "split"), (5, 8, (16, 16), 512, "generic", "split"), (6, 8, (16, 16), 512, "split", "split")])
+def test_weight_gradients_of_few_channels_take_the_faster_kernel(cin, cout, plane, batch, norm, total):
+    from paper_2010_09063_amd import DpStep
+    m = W.model(W.image_input(cin, *plane), [W.conv2d(cin, cout, 3, stride=1, pad=1, act="relu"), W.avgpool2d(2, 2),
+                                             W.dense(cout * plane[0] * plane[1] // 4, 3)], 3)
+    st = DpStep(m, batch, no_stored_gradients=1)
+    plan = st.dp_step_describe_plan()[0]
+    st.dp_step_free()
+    assert (plan["norm"], plan["sum"]) == (norm, total)
 
 
 def test_split_convolutions_add_no_bias():
