@@ -1726,8 +1726,9 @@ static int run_step(dp_ctx *c, const float *params, const void *x, const int32_t
           const bool vec = (a.D & 3) == 0; // (dx and the rows are this library's own allocations)
           Ln(LL("emb_norm"), grid, block, [&](hipStream_t st) {
 #define DP_ROWS_CASE(kpt_) \
-            if (vec) hipLaunchKernelGGL((emb_rows_kernel<kpt_, true>), grid, block, 0, st, a); \
-            else hipLaunchKernelGGL((emb_rows_kernel<kpt_, false>), grid, block, 0, st, a);
+            if (vec) hipLaunchKernelGGL((emb_rows_kernel<kpt_, 4, true>), grid, block, 0, st, a); \
+            else if (a.D > 32) hipLaunchKernelGGL((emb_rows_kernel<kpt_, 4, false>), grid, block, 0, st, a); \
+            else hipLaunchKernelGGL((emb_rows_kernel<kpt_, 1, false>), grid, block, 0, st, a);
             if (a.T <= 256) { DP_ROWS_CASE(1) } else if (a.T <= 512) { DP_ROWS_CASE(2) } else { DP_ROWS_CASE(4) }
 #undef DP_ROWS_CASE
           });

@@ -263,9 +263,11 @@ struct EmbRowsArgs {
 };
 #define EMB_ROWS_THREADS 512
 
-template <int KPT, bool VEC>
+// Its lanes hold W_ coordinates of a row: four that follow each other (VEC), or, with rows that start on 4 bytes, every 32nd:
+// in rows of more than 32 coordinates one at a time left the walk waiting for one short load after another (251 wide, 349
+// steps, 25 examples: 80 -> 55 us; 107, 315, 16: 41 -> 28).  A token's only step is one load.
+template <int KPT, int W_, bool VEC>
 __global__ __launch_bounds__(EMB_ROWS_THREADS) void emb_rows_kernel(const EmbRowsArgs a) {
-  constexpr int W_ = VEC ? 4 : 1;
   __shared__ uint32_t key[KPT * 256];
   __shared__ uint16_t head[KPT * 256], start[EMB_WG_MAX + 1];
   __shared__ int wsum[KPT * 4];
@@ -292,31 +294,40 @@ __global__ __launch_bounds__(EMB_ROWS_THREADS) void emb_rows_kernel(const EmbRow
   for (int u = grp; u < total; u += EMB_ROWS_THREADS / 32) {
     const int p0 = head[u], p1 = u + 1 < total ? head[u + 1] : T;
     for (int e0 = 0; e0 < D; e0 += 32 * W_) {
-      const int e = e0 + sub * W_;
-      const bool on = e < D;
-      float acc[W_] = {};
-      for (int p = p0; p < p1; p += 8) {
-        float v[8][W_];
+      const int e = e0 + (VEC ? sub * W_ : sub);
+      auto load = [&](float (&v)[W_], int p) {
+        const float *r = dx + (long)(key[p] & 1023u) * D;
+        if constexpr (VEC) {
+          const float4 q = *reinterpret_cast<const float4 *>(r + (e < D ? e : 0));
+          v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+        } else {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const float *r = dx + (long)(key[min(p + j, p1 - 1)] & 1023u) * D + (on ? e : 0);
-          if constexpr (VEC) {
-            const float4 q = *reinterpret_cast<const float4 *>(r);
-            v[j][0] = q.x; v[j][1] = q.y; v[j][2] = q.z; v[j][3] = q.w;
-          } else {
-            v[j][0] = *r;
-          }
+          for (int w = 0; w < W_; ++w) v[w] = r[min(e + 32 * w, D - 1)];
         }
+      };
+      float acc[W_] = {};
+      if (p1 - p0 == 1) {
+        load(acc, p0);
+      } else {
+        for (int p = p0; p < p1; p += 8) {
+          float v[8][W_];
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+          for (int j = 0; j < 8; ++j) load(v[j], min(p + j, p1 - 1));
 #pragma unroll
-          for (int w = 0; w < W_; ++w) acc[w] += p + j < p1 ? v[j][w] : 0.f;
+          for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int w = 0; w < W_; ++w) acc[w] += p + j < p1 ? v[j][w] : 0.f;
+        }
       }
-      if (on) {
-        if constexpr (VEC) *reinterpret_cast<float4 *>(rows + (long)u * D + e) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-        else rows[(long)u * D + e] = acc[0];
+      if constexpr (VEC) {
+        if (e < D) *reinterpret_cast<float4 *>(rows + (long)u * D + e) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+      }
 #pragma unroll
-        for (int w = 0; w < W_; ++w) n2 = fmaf(acc[w], acc[w], n2);
+      for (int w = 0; w < W_; ++w) {
+        if (e + (VEC ? 0 : 32 * w) < D) {
+          if constexpr (!VEC) rows[(long)u * D + e + 32 * w] = acc[w];
+          n2 = fmaf(acc[w], acc[w], n2);
+        }
       }
     }
   }

@@ -384,3 +384,15 @@ def test_an_example_out_of_range_stays_its_own(kind, value):
     others = [0, 1, 3, 4, 5, 6]
     assert np.array_equal(here[others], clean[others])
     assert np.isfinite(here[2]) == np.isfinite(plain[2]), (here[2], plain[2])
+
+
+# rows of the pairs below a hidden layer: one coordinate per lane, four 32 apart (a last group of each size), four in line
+@pytest.mark.parametrize("dim,seq,vocab", [(31, 40, 7), (33, 40, 7), (65, 300, 400), (129, 600, 90), (251, 40, 3000), (132, 300, 25)])
+def test_embedding_rows_of_each_width_below_a_hidden_layer(dim, seq, vocab):
+    from paper_2010_09063_amd import DpStep
+    m = W.model(W.token_input(seq), [W.embedding(vocab, dim), W.seq_mean(), W.dense(dim, 12, "tanh"), W.dense(12, 5)], 5)
+    rng = np.random.default_rng(dim)
+    x, y = W.make_inputs(m, 9, rng)
+    x[0, :] = vocab - 1  # one token throughout
+    theta = W.init_params(m, rng, bias_scale=0.3)
+    _check_all_regimes(m, x, y, theta, f"embedding {vocab}x{dim} T{seq} below a hidden layer", stepper=DpStep(m, 9))
