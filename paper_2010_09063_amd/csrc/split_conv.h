@@ -14,9 +14,7 @@ struct SplitConvArgs {
   float *pool_out; uint8_t *pool_arg; // 2x2 / stride-2 pool after a forward pass: [B][M][H/2][W/2], the maximum's place
   int B, Cin, M, H, W, act;
   int pool;            // 0: none, 1: max, 2: mean
-  // two fp16 pieces only, forward:
-  const float *w;      // the weights as they are, [M][Cin][9]
-  int bounded;         // the input lies between -1 and 1
+  const float *w;      // two fp16 pieces only: the layer's weights as they are, [M][Cin][9] (backward-data: [Cin][M][9])
 };
 
 #define SPLIT_CONV_MAX 32

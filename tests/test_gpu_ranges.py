@@ -104,3 +104,103 @@ def test_weight_gradients_take_no_longer_for_small_values(plane, groups):
     st.dp_step_free()
     assert "conv_wgrad_norm#0" in times[0] and "conv_clipped_sum#0" in times[0], times[0]
     assert all(times[1][k] <= 2 * times[0][k] for k in times[0]), times
+
+
+def _fp16_network(plane, act="tanh"):
+    c = max(36, 1024 // plane)
+    return c, W.model(W.image_input(40, plane, plane), [W.conv2d(40, c, 3, stride=1, pad=1, act=act), W.conv2d(c, c, 3, stride=1, pad=1, act="tanh"),
+                                                        W.avgpool2d(2, 2), W.dense(c * plane * plane // 4, 3)], 3)
+
+
+FP16_PLANES = [(32, 65), (16, 257), (8, 513), (4, 2049)]  # (plane, largest batch): more than 256 tiles of 128 pixels
+
+
+def _same_as_direct(m, theta, x, y, max_batch, label):
+    plan, norms, clipped, plain = _both_gradients(m, theta, x, y, max_batch)
+    assert all(plan[l]["fwd"].startswith("f16") for l in (0, 1)) and plan[1]["bwd"] == "f16", plan
+    _, norms0, clipped0, plain0 = _both_gradients(m, theta, x, y, len(y), no_minimal_filtering=1)
+    # the two routes' rounding: 1.2e-6 at most in a tensor, 5.5e-7 in a norm; about four times that
+    assert np.isfinite(norms0).all() and np.allclose(norms, norms0, rtol=2e-6), (label, norms / norms0 - 1)
+    _by_tensor(m, clipped, clipped0, 5e-6, label + " clipped")
+    _by_tensor(m, plain, plain0, 5e-6, label + " plain")
+
+
+@pytest.mark.parametrize("kind", ["columns", "all but two columns", "all but three rows", "channels", "channels of half the filters"])
+@pytest.mark.parametrize("value", [2.0 ** 18, 2.0 ** 21, 1e9, -1e15])
+@pytest.mark.parametrize("plane,max_batch", FP16_PLANES)
+def test_forward_pass_beside_a_mask(plane, max_batch, value, kind):
+    """Huge inputs of one example saturate the units that see them; what the other units see of the image keeps its bits, whatever
+    share of it that is."""
+    c, m = _fp16_network(plane)
+    rng = np.random.default_rng(plane)
+    x, y = W.make_inputs(m, 5, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.1)
+    v, w = x.reshape(5, 40, plane, plane), theta[:c * 40 * 9].reshape(c, 40, 9)
+    if kind == "columns":
+        v[2, :, :, plane // 2:] = value
+    elif kind == "all but two columns":
+        v[2, :, :, 2:] = value
+    elif kind == "all but three rows":
+        v[2, :, 3:] = value
+    else:
+        v[2, ::4] = value
+        w[(slice(1, None, 2) if kind[8:] else slice(None)), ::4] = 0  # filters that do not look at these channels
+    _same_as_direct(m, theta, x, y, max_batch, f"{kind} {value}")
+
+
+@pytest.mark.parametrize("power", [15, 18, 21, 30, 60])
+@pytest.mark.parametrize("plane,max_batch", FP16_PLANES)
+def test_backprops_beside_a_large_part_that_does_not_count(plane, max_batch, power):
+    """Half of every plane has backprops 2^power larger than the rest, and the layer before is saturated there: its gradient is the other half's."""
+    c, m = _fp16_network(plane)
+    rng = np.random.default_rng(plane)
+    x, y = W.make_inputs(m, 5, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.1)
+    x.reshape(5, 40, plane, plane)[:, :, :, plane // 2:] = 1e6
+    last = theta[-(c * plane * plane // 4 * 3 + 3):-3].reshape(c, plane // 2, plane // 2, 3)
+    last[:, :, :max(plane // 4 - 1, 1)] *= np.float32(2.0 ** -power)  # (the columns between see both)
+    _same_as_direct(m, theta, x, y, max_batch, f"2^{power}")
+
+
+@pytest.mark.parametrize("power", [12, 16, 20, 27, 60])
+@pytest.mark.parametrize("plane,max_batch", FP16_PLANES)
+def test_filters_of_very_different_sizes(plane, max_batch, power):
+    """Three filters of four are 2^power smaller than the fourth, and the next layer makes up for it (no activation between: a tanh of a
+    small value is good to 2^-24, not to its own size)."""
+    c, m = _fp16_network(plane, "none")
+    rng = np.random.default_rng(plane)
+    x, y = W.make_inputs(m, 5, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.1)
+    n = c * 40 * 9
+    small = np.arange(c) % 4 != 0
+    theta[:n].reshape(c, 360)[small] *= np.float32(2.0 ** -power)
+    theta[n:n + c][small] *= np.float32(2.0 ** -power)
+    theta[n + c:n + c + c * c * 9].reshape(c, c, 9)[:, small] *= np.float32(2.0 ** power)
+    _same_as_direct(m, theta, x, y, max_batch, f"2^{power}")
+
+
+@pytest.mark.parametrize("plane,max_batch", FP16_PLANES)
+def test_forward_passes_take_no_longer_for_small_values(plane, max_batch):
+    """Two pixels of an image, all channels, 2^-40 of the rest: a sum that sees others besides is as exact as any, and no other way is gone."""
+    import torch
+    from paper_2010_09063_amd import DpStep
+    c, m = _fp16_network(plane)
+    rng = np.random.default_rng(plane)
+    x, y = W.make_inputs(m, 64, rng, x_dist="normal")
+    theta = W.init_params(m, rng, bias_scale=0.1)
+    small = x.copy()
+    small.reshape(64, 40, plane, plane)[3, :, 1, :2] *= np.float32(2.0 ** -40)
+    dev = torch.device("cuda")
+    st = DpStep(m, max_batch)
+    assert st.dp_step_describe_plan()[0]["fwd"] == "f16"
+    tt, ty, g = torch.from_numpy(theta).to(dev), torch.from_numpy(y).to(dev), torch.empty(len(theta), device=dev)
+    times = []
+    for v in (x, small):
+        tx, best = torch.from_numpy(np.ascontiguousarray(v)).to(dev), 1e9
+        for _ in range(8):
+            st.dp_step_profile(True)
+            st.dp_step(tt, tx, ty, 64, 1.0, 0.0, 0, g)
+            best = min([best] + [ms for label, _, ms in st.dp_step_profile_read() if label == "conv_fwd#0"])
+        times.append(best)
+    st.dp_step_free()
+    assert times[1] <= 2 * times[0], times
