@@ -265,6 +265,10 @@ __global__ __launch_bounds__(LSTM_THREADS) void lstm_fwd_kernel(float *__restric
 // and is bound by that.  Here 104 matrix instructions of 4.7 ns per SIMD and step are 0.49 us of 0.87, the chain of
 // activations, exchange and reads the rest; with one example (half of the columns) they take as long, and the vector kernel
 // is ahead: 168 against 211 us at 128.
+// A weight is off by up to 2^-40 of its column's largest, a sum (of 128 at most, |h| <= 1) by 2^-33 of it.  From 2^12 on that could
+// show in a gate's argument, where the unit behind the large weight is off: such networks are added up in fp32, a multiply-add
+// at a time.
+#define LSTM_WILD 4096.f
 template <int KS>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_fwd2_kernel(float *__restrict__ gates, const float *__restrict__ Whh,
                                                                        float *__restrict__ hs, float *__restrict__ cs,
@@ -280,14 +284,55 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const bool unit_ok = u < H, store = unit_ok && b0 + e < B;
   const int ul = unit_ok ? u : 0;
   // the weights of gate q of the unit, and what takes the four gates' scales out
+  float wv[8 * KS], top = 0.f;
+#pragma unroll
+  for (int k = 0; k < 8 * KS; ++k) wv[k] = Whh[(long)min(k, H - 1) * G + q * H + ul];
+#pragma unroll
+  for (int k = 0; k < 8 * KS; k += 2) top = sf_max3(wv[k], wv[k + 1], top); // (past the last row: the last one again)
+  for (int i = tid; i < 2 * 4 * KP; i += blockDim.x) (&h_s[0][0])[i] = (_Float16)0.f;
+  float c_reg = 0.f, h_sum = 0.f;
+  const unsigned colb = 4u * (p * H + ul), ub = 4u * ul, eb = (unsigned)(b - b0) * (unsigned)T * 4u; // (gates p and p + 2)
+  float *const grow0 = gates + (long)b0 * T * G;
+  float *const hrow0 = hs + (long)b0 * T * H, *const crow0 = cs + (long)b0 * T * H;
+  const bool wild = __syncthreads_or(top >= LSTM_WILD); // (the weight loads end here, not at their first use inside the loop)
+  // activations, state and what is written, from this lane's two gates' arguments; returns h
+  auto cell = [&](const int t, const float pre0, const float pre1, const unsigned colx, const unsigned ux) {
+    // (order i, f, g, o: gate 2 is the tanh one)
+    const float v0 = sigmoidf_(pre0), v1 = p ? sigmoidf_(pre1) : fast_tanh(pre1);
+    if (store) {
+      lane_at(grow0 + (long)t * G, colx) = v0;
+      lane_at(grow0 + (long)t * G, colx + 8u * H) = v1;
+    }
+    const float o0 = quad_xor1(v0), o1 = quad_xor1(v1);
+    c_reg = (p ? v0 : o0) * c_reg + (p ? o0 : v0) * (p ? o1 : v1);
+    return (p ? v1 : o1) * fast_tanh(c_reg);
+  };
+  auto write = [&](const int t, const float h, const unsigned ux) {
+    if (store) lane_at((p ? crow0 : hrow0) + (long)t * H, ux) = p ? c_reg : h;
+    h_sum += h;
+    if (t == T - 1 && store && p == 0) hlast[(long)b * H + ul] = mean ? h_sum / (float)T : h;
+  };
+  const unsigned col0 = colb + eb * (unsigned)G, u0 = ub + eb * (unsigned)H;
+  if (wild) {
+    float *const hf = reinterpret_cast<float *>(&h_s[0][0]) + e * H; // [step parity][example][unit]
+    static_assert(sizeof(h_s) >= 4 * 8 * KS * sizeof(float), "h in fp32");
+    for (int t = 0; t < T; ++t) {
+      float s0 = 0.f, s1 = 0.f;
+      const float *hp = hf + (t & 1) * 2 * H, *w0 = Whh + p * H + ul;
+      for (int k = 0; k < H; ++k) {
+        s0 = fmaf(hp[k], w0[(long)k * G], s0);
+        s1 = fmaf(hp[k], w0[(long)k * G + 2 * H], s1);
+      }
+      const float h = cell(t, s0 + lane_ld(grow0 + (long)t * G, col0), s1 + lane_ld(grow0 + (long)t * G, col0 + 8u * H), col0, u0);
+      if (unit_ok && p == 0) hf[((t + 1) & 1) * 2 * H + u] = h;
+      write(t, h, u0);
+      __syncthreads();
+    }
+    return;
+  }
   f16x4 w[2][2 * KS];
   float un[4];
   {
-    float wv[8 * KS], top = 0.f;
-#pragma unroll
-    for (int k = 0; k < 8 * KS; ++k) wv[k] = Whh[(long)min(k, H - 1) * G + q * H + ul];
-#pragma unroll
-    for (int k = 0; k < 8 * KS; k += 2) top = sf_max3(wv[k], wv[k + 1], top); // (past the last row: the last one again)
     const uint32_t ex = sf_exponent(__float_as_uint(top));
     const float sc = sf_scale(ex), back = sf_unscale(ex) * 6.103515625e-5f; // (h's 2^14 as well)
     un[0] = quad_bcast<0>(back); un[1] = quad_bcast<1>(back); un[2] = quad_bcast<2>(back); un[3] = quad_bcast<3>(back);
@@ -302,13 +347,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
   }
-  for (int i = tid; i < 2 * 4 * KP; i += blockDim.x) (&h_s[0][0])[i] = (_Float16)0.f;
-  float c_reg = 0.f, h_sum = 0.f;
-  const unsigned colb = 4u * (p * H + ul), ub = 4u * ul, eb = (unsigned)(b - b0) * (unsigned)T * 4u; // (gates p and p + 2)
-  float *const grow0 = gates + (long)b0 * T * G;
-  float *const hrow0 = hs + (long)b0 * T * H, *const crow0 = cs + (long)b0 * T * H;
-  __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the weight loads end here, not at their first use inside the loop
-  __syncthreads();
   auto step = [&](const int t, const float x0, const float x1, float &n0, float &n1, const _Float16 *hin, _Float16 *hout) {
     unsigned colx = colb, ux = ub, ex = eb; // (re-materialised inside the loop: hoisted, they would be widened to 64 bits)
     asm volatile("" : "+v"(colx), "+v"(ux), "+v"(ex));
@@ -334,27 +372,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       const float v = acc[0][g] + acc[1][g]; // this lane's piece of h; the other one is next door
       s[g] = (v + quad_xor1(v)) * un[g];
     }
-    // (order i, f, g, o: gate 2 is the tanh one)
-    const float pre0 = (p ? s[1] : s[0]) + x0, pre1 = (p ? s[3] : s[2]) + x1;
-    const float v0 = sigmoidf_(pre0), v1 = p ? sigmoidf_(pre1) : fast_tanh(pre1);
-    if (store) {
-      lane_at(grow0 + (long)t * G, colx) = v0;
-      lane_at(grow0 + (long)t * G, colx + 8u * H) = v1;
-    }
-    const float o0 = quad_xor1(v0), o1 = quad_xor1(v1);
-    c_reg = (p ? v0 : o0) * c_reg + (p ? o0 : v0) * (p ? o1 : v1);
-    const float h = (p ? v1 : o1) * fast_tanh(c_reg);
+    const float h = cell(t, (p ? s[1] : s[0]) + x0, (p ? s[3] : s[2]) + x1, colx, ux);
     if (unit_ok) { // the piece of h for the lane's column
       const float hsc = h * 16384.f;
       const _Float16 hi = (_Float16)hsc, lo = (_Float16)(hsc - (float)hi);
       hout[q * KP + u] = p ? lo : hi;
     }
-    if (store) lane_at((p ? crow0 : hrow0) + (long)t * H, ux) = p ? c_reg : h;
-    h_sum += h;
-    if (t == T - 1 && store && p == 0) hlast[(long)b * H + ul] = mean ? h_sum / (float)T : h;
+    write(t, h, ux);
     __syncthreads();
   };
-  float xa0 = lane_ld(grow0, colb + eb * (unsigned)G), xa1 = lane_ld(grow0, colb + eb * (unsigned)G + 8u * H), xb0, xb1;
+  float xa0 = lane_ld(grow0, col0), xa1 = lane_ld(grow0, col0 + 8u * H), xb0, xb1;
   int t = 0;
   for (; t + 1 < T; t += 2) {
     step(t, xa0, xa1, xb0, xb1, h_s[0], h_s[1]);
@@ -493,16 +520,68 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const bool unit_ok = u < H, store = unit_ok && b0 + e < B;
   const int ul = unit_ok ? u : 0;
   const int bg = (lane >> 2) & 3; // the block's gate
-  f16x4 w[2][2 * KS];
-  float un[4];
+  float wv[8 * KS], most = 0.f;
+  const int row = (tid >> 6) * 16 + 4 * (lane >> 4) + q; // the block's units, this lane's of them
   {
-    const int row = (tid >> 6) * 16 + 4 * (lane >> 4) + q; // the block's units, this lane's of them
     const float *wr = Whh + (long)min(row, H - 1) * G + bg * H;
-    float wv[8 * KS], most = 0.f;
 #pragma unroll
     for (int j = 0; j < 8 * KS; ++j) wv[j] = wr[min(j, H - 1)];
 #pragma unroll
     for (int j = 0; j < 8 * KS; j += 2) most = sf_max3(wv[j], wv[j + 1], most);
+  }
+  for (int i = tid; i < 2 * 16 * KP; i += blockDim.x) (&d_s[0][0])[i] = (_Float16)0.f;
+  if (tid < 6) top[tid >> 1][tid & 1] = 0;
+  const unsigned colb = 4u * (p * H + ul), ub = 4u * ul, eb = (unsigned)(b - b0) * (unsigned)T * 4u; // (gates p and p + 2)
+  float *const grow0 = gates + (long)b0 * T * G;
+  const float *const crow0 = cs + (long)b0 * T * H;
+  float dh_own = dh_out[(long)b * H + ul];
+  if (SEQ) dh_own /= (float)T;
+  float dc = 0.f;
+  uint32_t used[2] = {27u, 27u};  // exponents that the two examples' gradients in LDS are scaled by
+  uint32_t guess[2] = {27u, 27u}; // the last step's largest, which the next one's are scaled by
+  const bool wild = __syncthreads_or(most >= LSTM_WILD); // (as in lstm_fwd2_kernel: where such a weight's gate is saturated)
+  // beside dL/dc_t (output gate: dL/dh_t): this lane's two gates' factors, what dL/dh_t adds to dL/dc_t and what goes on to
+  // dL/dc_{t-1}; va, vb: the activated gates, ct, cp: c_t and c_{t-1}
+  struct Factors { float ka, kb, a, gf; };
+  auto factors = [&](const int t, const float va, const float vb, const float ct, const float cp) {
+    const float oa = quad_xor1(va), ob = quad_xor1(vb);
+    const float gi = p ? oa : va, gf = p ? va : oa, gg = p ? ob : vb, go = p ? vb : ob;
+    const float tc = fast_tanh(ct), cprev = t > 0 ? cp : 0.f;
+    return Factors{fmaf(-va, va, va) * (p ? cprev : gg), fmaf(-vb, vb, p ? vb : 1.f) * (p ? tc : gi), go * (1.f - tc * tc), gf};
+  };
+  auto cell = [&](const int t, const float dh, const Factors &f, const unsigned colx, float &da, float &db) {
+    const float dct = dc + dh * f.a;
+    da = dct * f.ka; db = (p ? dh : dct) * f.kb;
+    dc = dct * f.gf;
+    if (store) {
+      lane_at(grow0 + (long)t * G, colx) = da;
+      lane_at(grow0 + (long)t * G, colx + 8u * H) = db;
+    }
+  };
+  const unsigned col0 = colb + eb * (unsigned)G, u0 = ub + eb * (unsigned)H;
+  if (wild) {
+    float *const df = reinterpret_cast<float *>(&d_s[0][0]) + e * G; // [step parity][example][gate column]
+    static_assert(sizeof(d_s) >= 4 * 4 * 8 * KS * sizeof(float), "gate gradients in fp32");
+    for (int t = T - 1, n = 0; t >= 0; --t, ++n) {
+      const float *dp = df + (n & 1) * 2 * G, *wr = Whh + (long)ul * G;
+      float dh = 0.f, da, db;
+      for (int j = p; j < G; j += 2) dh = fmaf(wr[j], dp[j], dh);
+      dh += quad_xor1(dh);
+      if (SEQ || t == T - 1) dh += dh_own;
+      const float *gr = grow0 + (long)t * G;
+      cell(t, dh, factors(t, lane_ld(gr, col0), lane_ld(gr, col0 + 8u * H), lane_ld(crow0 + (long)t * H, u0), lane_ld(crow0 + (long)max(t - 1, 0) * H, u0)),
+           col0, da, db);
+      if (unit_ok) {
+        float *o = df + ((n + 1) & 1) * 2 * G + p * H + u;
+        o[0] = da; o[2 * H] = db;
+      }
+      __syncthreads();
+    }
+    return;
+  }
+  f16x4 w[2][2 * KS];
+  float un[4];
+  {
     const uint32_t ex = sf_exponent(__float_as_uint(most));
     const float sc = sf_scale(ex), back = sf_unscale(ex);
     un[0] = quad_bcast<0>(back); un[1] = quad_bcast<1>(back); un[2] = quad_bcast<2>(back); un[3] = quad_bcast<3>(back);
@@ -517,20 +596,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
   }
-  for (int i = tid; i < 2 * 16 * KP; i += blockDim.x) (&d_s[0][0])[i] = (_Float16)0.f;
-  if (tid < 6) top[tid >> 1][tid & 1] = 0;
-  const unsigned colb = 4u * (p * H + ul), ub = 4u * ul, eb = (unsigned)(b - b0) * (unsigned)T * 4u; // (gates p and p + 2)
-  float *const grow0 = gates + (long)b0 * T * G;
-  const float *const crow0 = cs + (long)b0 * T * H;
-  float dh_own = dh_out[(long)b * H + ul];
-  if (SEQ) dh_own /= (float)T;
-  float dc = 0.f;
-  uint32_t used[2] = {27u, 27u};  // exponents that the two examples' gradients in LDS are scaled by
-  uint32_t guess[2] = {27u, 27u}; // the last step's largest, which the next one's are scaled by
-  __builtin_amdgcn_s_waitcnt(0x0F70); // vmcnt(0): the weight loads end here, not at their first use inside the loop
-  __syncthreads();
   auto exponent = [](uint32_t bits) { return max(bits >> 23, 27u); };
-  // n counts the steps; din: what step t + 1 wrote.  va, vb: this lane's two activated gates, ct, cp: c_t and c_{t-1}
+  // n counts the steps; din: what step t + 1 wrote
   auto step = [&](const int t, const int n, const float va, const float vb, const float ct, const float cp, float &na, float &nb, float &cnext,
                   const _Float16 *din, _Float16 *dout) {
     unsigned colx = colb, ux = ub, ex = eb; // (re-materialised inside the loop: hoisted, they would be widened to 64 bits)
@@ -541,12 +608,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       na = lane_ld(ng, colx); nb = lane_ld(ng, colx + 8u * H);
       cnext = lane_ld(crow0 + (long)max(t - 2, 0) * H, ux);
     }
-    const float oa = quad_xor1(va), ob = quad_xor1(vb);
-    const float gi = p ? oa : va, gf = p ? va : oa, gg = p ? ob : vb, go = p ? vb : ob;
-    const float tc = fast_tanh(ct), cprev = t > 0 ? cp : 0.f;
-    const float a = go * (1.f - tc * tc);
-    // beside dL/dc_t (output gate: dL/dh_t): the two gates' factors
-    const float ka = fmaf(-va, va, va) * (p ? cprev : gg), kb = fmaf(-vb, vb, p ? vb : 1.f) * (p ? tc : gi);
+    const Factors f = factors(t, va, vb, ct, cp);
     f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     const _Float16 *dq = din + (bg * 4 + q) * KP;
 #pragma unroll
@@ -569,13 +631,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     dh += quad_xor1(dh); // the other piece
     dh *= __uint_as_float(((e ? used[1] : used[0]) - 8u) << 23);
     if (SEQ || t == T - 1) dh += dh_own;
-    const float dct = dc + dh * a;
-    const float da = dct * ka, db = (p ? dh : dct) * kb;
-    dc = dct * gf;
-    if (store) {
-      lane_at(grow0 + (long)t * G, colx) = da;
-      lane_at(grow0 + (long)t * G, colx + 8u * H) = db;
-    }
+    float da, db;
+    cell(t, dh, f, colx, da, db);
     // this step's largest, for the next one's scale
     uint32_t *const mine = top[n % 3];
     float m = unit_ok ? fmaxf(fabsf(da), fabsf(db)) : 0.f;
@@ -606,8 +663,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     used[0] = guess[0]; used[1] = guess[1];
     guess[0] = x0; guess[1] = x1;
   };
-  float va = lane_ld(grow0 + (long)(T - 1) * G, colb + eb * (unsigned)G), vb = lane_ld(grow0 + (long)(T - 1) * G, colb + eb * (unsigned)G + 8u * H), wa, wb;
-  float c0 = lane_ld(crow0 + (long)(T - 1) * H, ub + eb * (unsigned)H), c1 = lane_ld(crow0 + (long)max(T - 2, 0) * H, ub + eb * (unsigned)H), c2;
+  float va = lane_ld(grow0 + (long)(T - 1) * G, col0), vb = lane_ld(grow0 + (long)(T - 1) * G, col0 + 8u * H), wa, wb;
+  float c0 = lane_ld(crow0 + (long)(T - 1) * H, u0), c1 = lane_ld(crow0 + (long)max(T - 2, 0) * H, u0), c2;
   int t = T - 1, n = 0;
   for (; t > 0; t -= 2, n += 2) {
     step(t, n, va, vb, c0, c1, wa, wb, c2, d_s[0], d_s[1]);

@@ -204,3 +204,30 @@ def test_forward_passes_take_no_longer_for_small_values(plane, max_batch):
         times.append(best)
     st.dp_step_free()
     assert times[1] <= 2 * times[0], times
+
+
+@pytest.mark.parametrize("out", ["last", "seq"])
+@pytest.mark.parametrize("where", ["into a saturated gate", "from a unit that is off"])
+@pytest.mark.parametrize("hidden,power", [(48, 10), (48, 16), (48, 30), (100, 22), (100, 120), (128, 30)])
+def test_lstm_weights_of_very_different_sizes(hidden, power, where, out):
+    """Weights 2^power larger than the others that add nothing: those that lead into a gate which they saturate have no part in
+    the gradient of the unit they come from, those that come from a unit which is always zero none in the state.  Two examples per
+    workgroup against one, which is fp32 throughout."""
+    layers = [W.embedding(40, 9), (W.lstm_last if out == "last" else W.lstm_seq)(9, hidden)]
+    m = W.model(W.token_input(12), layers + ([W.seq_mean()] if out == "seq" else []) + [W.dense(hidden, 3)], 3)
+    rng = np.random.default_rng(hidden)
+    x, y = W.make_inputs(m, 258, rng, zipf_exponent=0.8)
+    theta = W.init_params(m, rng, bias_scale=0.3) * np.float32(2)
+    t = {name: theta[off:off + int(np.prod(shape))].reshape(shape) for li, name, shape, off in W.param_tensors(m) if li == 1}
+    if where == "into a saturated gate":  # unit 7's output gate, from every unit, the same sign: far from zero from the second step on
+        t["W_hh"][:, 3 * hidden + 7] = 2.0 ** power
+        t["b"][3 * hidden + 7] = 2.0 ** power * hidden * 1.5  # (whatever the state)
+    else:
+        t["b"][3 * hidden + 5] = -1e4
+        t["W_hh"][5, :] = 2.0 ** power
+    _, norms, clipped, plain = _both_gradients(m, theta, x, y, 258)
+    parts = [_both_gradients(m, theta, x[i:i + 129], y[i:i + 129], 129) for i in (0, 129)]
+    norms0 = np.concatenate([p[1] for p in parts])
+    assert np.isfinite(norms0).all() and np.allclose(norms, norms0, rtol=4e-6), np.abs(norms / norms0 - 1).max()
+    _by_tensor(m, clipped, parts[0][2] + parts[1][2], 4e-6, "clipped")
+    _by_tensor(m, plain, parts[0][3] + parts[1][3], 4e-6, "plain")
