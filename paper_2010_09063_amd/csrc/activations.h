@@ -30,3 +30,7 @@ __device__ __forceinline__ float act_deriv_from_out(int act, float a) {
   if (act == DP_ACT_TANH_) return 1.f - a * a;
   return 1.f;
 }
+// lanes swap within pairs: the other column of a 2x2 pool's window
+__device__ __forceinline__ float swap1(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
+}

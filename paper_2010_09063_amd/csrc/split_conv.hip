@@ -6,10 +6,6 @@
 #include "activations.h"
 #include "split_bf16.h"
 
-__device__ __forceinline__ float conv_swap1(float v) { // lanes swap within pairs
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
-}
-
 // A wave works alone: 64 output pixels (two blocks of 32: the even and the odd rows, so that a 2x2 pool window is two
 // lanes of both blocks) x 32 output channels, KS waves sharing the input channels of a tile.  Per 16 input channels
 // it fetches the haloed pixels with the channel as the register index, splits them once and leaves them in an LDS area
@@ -197,7 +193,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           if (MODE <= 2) { v0 = act_apply(ACT, v0 + bv[r]); v1 = act_apply(ACT, v1 + bv[r]); }
           if (MODE == 3) { v0 *= act_deriv_from_out(ACT, s[0][r]); v1 *= act_deriv_from_out(ACT, s[1][r]); }
           if (MODE == 1 || MODE == 2) {
-            const float u0 = conv_swap1(v0), u1 = conv_swap1(v1); // the window's other column
+            const float u0 = swap1(v0), u1 = swap1(v1); // the window's other column
             if ((px & 1) == 0) {
               const long po = ((long)img0 * a.M + mu) * (HW >> 2) + po_lane + (unsigned)(r * (HW >> 2));
               if (MODE == 1) { // first maximum in row-major order
