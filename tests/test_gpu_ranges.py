@@ -107,7 +107,7 @@ def test_weight_gradients_take_no_longer_for_small_values(plane, groups):
 
 
 def _fp16_network(plane, act="tanh"):
-    c = max(36, 1024 // plane)
+    c = max(33, 1024 // plane)  # (33: a block of 32 output channels and one of one)
     return c, W.model(W.image_input(40, plane, plane), [W.conv2d(40, c, 3, stride=1, pad=1, act=act), W.conv2d(c, c, 3, stride=1, pad=1, act="tanh"),
                                                         W.avgpool2d(2, 2), W.dense(c * plane * plane // 4, 3)], 3)
 
