@@ -253,6 +253,8 @@ __global__ __launch_bounds__(LSTM_THREADS) void lstm_fwd_kernel(float *__restric
   if (t < T) step(t, xa, xb, h_s[0], h_s[1]);
 }
 
+typedef float lstm_f32x4 __attribute__((ext_vector_type(4)));
+
 // The same for two examples per workgroup, which is ahead where every compute unit has two (above 256 examples).
 //
 // A step's product W_hh^T h is on the matrix units, operands as two fp16 pieces of a scaled value (split_f16.h): weights by
@@ -266,15 +268,35 @@ __global__ __launch_bounds__(LSTM_THREADS) void lstm_fwd_kernel(float *__restric
 // activations, exchange and reads the rest; with one example (half of the columns) they take as long, and the vector kernel
 // is ahead: 168 against 211 us at 128.
 // A weight is off by up to 2^-40 of its column's largest, a sum (of 128 at most, |h| <= 1) by 2^-33 of it.  From 2^12 on that could
-// show in a gate's argument, where the unit behind the large weight is off: such networks are added up in fp32, a multiply-add
-// at a time.
+// show in a gate's argument, where the unit behind the large weight is off: such networks are multiplied in fp32, by
+// v_mfma_f32_4x4x1_16b_f32 in the same blocks, columns (example, twice): 354 us instead of 243, the vector kernel 288 (one
+// multiply-add at a time took 2,860).
 #define LSTM_WILD 4096.f
+// fewest units that a kernel of KS is launched with
+template <int KS>
+constexpr int lstm_units_from() { return KS == 4 ? 1 : 8 * KS - 23; }
+// that product of a block: this lane's row of weights with the block's operand in LDS; four sums, each operand read four
+// multiplies of four ahead (all at once they would not fit beside the weights)
+template <int KS>
+__device__ __forceinline__ lstm_f32x4 lstm_fp32_product(const float (&w)[8 * KS], const float *x) {
+  lstm_f32x4 s[4] = {}, v[2 * KS];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const lstm_f32x4 *>(x + 4 * i);
+#pragma unroll
+  for (int i = 0; i < 2 * KS; ++i) {
+    if (i + 4 < 2 * KS) v[i + 4] = *reinterpret_cast<const lstm_f32x4 *>(x + 4 * i + 16);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s[j] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[4 * i + j], v[i][j], s[j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return (s[0] + s[1]) + (s[2] + s[3]);
+}
 template <int KS>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_fwd2_kernel(float *__restrict__ gates, const float *__restrict__ Whh,
                                                                        float *__restrict__ hs, float *__restrict__ cs,
                                                                        float *__restrict__ hlast, int mean, int B, int T, int H) {
   typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef lstm_f32x4 f32x4;
   constexpr int KP = 8 * KS + 8; // halves of a column in LDS (columns on different banks)
   __shared__ __attribute__((aligned(16))) _Float16 h_s[2][4 * KP];
   const int tid = threadIdx.x, q = tid & 3, u = tid >> 2; // quad: a unit; lane of the quad: a column
@@ -286,9 +308,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // the weights of gate q of the unit, and what takes the four gates' scales out
   float wv[8 * KS], top = 0.f;
 #pragma unroll
-  for (int k = 0; k < 8 * KS; ++k) wv[k] = Whh[(long)min(k, H - 1) * G + q * H + ul];
+  for (int k = 0; k < 8 * KS; ++k) {
+    wv[k] = Whh[(long)min(k, H - 1) * G + q * H + ul];
+    if (k >= lstm_units_from<KS>()) wv[k] = k < H ? wv[k] : 0.f;
+  }
 #pragma unroll
-  for (int k = 0; k < 8 * KS; k += 2) top = sf_max3(wv[k], wv[k + 1], top); // (past the last row: the last one again)
+  for (int k = 0; k < 8 * KS; k += 2) top = sf_max3(wv[k], wv[k + 1], top);
   for (int i = tid; i < 2 * 4 * KP; i += blockDim.x) (&h_s[0][0])[i] = (_Float16)0.f;
   float c_reg = 0.f, h_sum = 0.f;
   const unsigned colb = 4u * (p * H + ul), ub = 4u * ul, eb = (unsigned)(b - b0) * (unsigned)T * 4u; // (gates p and p + 2)
@@ -314,17 +339,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   };
   const unsigned col0 = colb + eb * (unsigned)G, u0 = ub + eb * (unsigned)H;
   if (wild) {
-    float *const hf = reinterpret_cast<float *>(&h_s[0][0]) + e * H; // [step parity][example][unit]
-    static_assert(sizeof(h_s) >= 4 * 8 * KS * sizeof(float), "h in fp32");
+    float *const hf = reinterpret_cast<float *>(&h_s[0][0]) + e * KP; // [step parity][example][unit]
+    static_assert(sizeof(h_s) == 4 * KP * sizeof(float), "h in fp32");
     for (int t = 0; t < T; ++t) {
-      float s0 = 0.f, s1 = 0.f;
-      const float *hp = hf + (t & 1) * 2 * H, *w0 = Whh + p * H + ul;
-      for (int k = 0; k < H; ++k) {
-        s0 = fmaf(hp[k], w0[(long)k * G], s0);
-        s1 = fmaf(hp[k], w0[(long)k * G + 2 * H], s1);
-      }
-      const float h = cell(t, s0 + lane_ld(grow0 + (long)t * G, col0), s1 + lane_ld(grow0 + (long)t * G, col0 + 8u * H), col0, u0);
-      if (unit_ok && p == 0) hf[((t + 1) & 1) * 2 * H + u] = h;
+      const float *gr = grow0 + (long)t * G, *hp = hf + (t & 1) * 2 * KP;
+      const float x0 = lane_ld(gr, col0), x1 = lane_ld(gr, col0 + 8u * H);
+      const f32x4 s = lstm_fp32_product<KS>(wv, hp);
+      const float h = cell(t, (p ? s[1] : s[0]) + x0, (p ? s[3] : s[2]) + x1, col0, u0);
+      if (unit_ok && p == 0) hf[((t + 1) & 1) * 2 * KP + u] = h;
       write(t, h, u0);
       __syncthreads();
     }
@@ -340,7 +362,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int i = 0; i < 2 * KS; ++i) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float v = 4 * i + j < H && unit_ok ? wv[4 * i + j] * sc : 0.f;
+        const float v = wv[4 * i + j] * sc;
         const _Float16 hi = (_Float16)v;
         w[0][i][j] = hi;
         w[1][i][j] = (_Float16)(v - (float)hi);
@@ -501,36 +523,49 @@ __global__ __launch_bounds__(LSTM_THREADS, (HP <= 100 ? 4 : 2)) void lstm_bwd_ke
 // (four units) x (gate): a block of v_mfma_f32_4x4x4_16b_f16 multiplies four units' rows of one gate's H columns by that
 // gate's gradients, columns (example, piece); the four gates' sums meet within a row of sixteen lanes, each unit's in the
 // quad of lanes that owns it, where lanes p = 0 make the gradients of gates i and g, p = 1 f and o.
-// Gate gradients have no bound: they are scaled to 2^8 of the largest of the step after (going back in time), and where a
-// step's own largest lies more than 2^7 from that, all write theirs once more with its own scale before anyone reads.
+// Gate gradients have no bound: they are scaled to 2^11 of the largest of the step after (going back in time), and where a
+// step's own largest lies more than 2^3 from that, all write theirs once more with its own scale before anyone reads.
+// The second pieces, of weights and gradients, are 2^11 times what the first ones leave, which their own accumulators and
+// columns take out again: a gradient is off by up to 2^-44 of the example's largest, a weight by 2^-51 of its row's.  What lies
+// 2^20 below the largest gradient keeps its bits so; further below, it would show in a unit none of whose weights lead to the
+// large ones: networks with weights that are zero or below 2^-26 of their row's largest are multiplied in fp32, as those with
+// large weights (one in 700 random ones): 256 steps at 512 examples 450 us instead of 284, the vector kernel 334.
 // 100 steps, H = 100, 512 examples: 170 -> 123 us.
 template <int KS, bool SEQ>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void lstm_bwd2_kernel(float *__restrict__ gates, const float *__restrict__ cs,
                                                                        const float *__restrict__ Whh, const float *__restrict__ dh_out,
                                                                        int B, int T, int H) {
   typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef lstm_f32x4 f32x4;
   constexpr int KP = KS < 16 ? 120 : 136; // halves of a (gate, column) in LDS: 16-byte reads of sixteen of them on different banks
   __shared__ __attribute__((aligned(16))) _Float16 d_s[2][16 * KP];
   __shared__ uint32_t top[3][2]; // [step][example]: a step's largest gradient
-  const int tid = threadIdx.x, lane = tid & 63, q = tid & 3, u = tid >> 2;
-  const int e = q >> 1, p = q & 1, b0 = 2 * (int)blockIdx.x;
-  const int b = min(b0 + e, B - 1); // (an example past the last one: the last one again, not stored)
-  const int G = 4 * H;
-  const bool unit_ok = u < H, store = unit_ok && b0 + e < B;
-  const int ul = unit_ok ? u : 0;
-  const int bg = (lane >> 2) & 3; // the block's gate
-  float wv[8 * KS], most = 0.f;
-  const int row = (tid >> 6) * 16 + 4 * (lane >> 4) + q; // the block's units, this lane's of them
+  int tid = threadIdx.x;
+  const int G = 4 * H, b0 = 2 * (int)blockIdx.x;
+  float wv[8 * KS], most = 0.f, least = INFINITY;
   {
-    const float *wr = Whh + (long)min(row, H - 1) * G + bg * H;
+    const int row = (tid >> 6) * 16 + 4 * ((tid >> 4) & 3) + (tid & 3); // the block's units, this lane's of them
+    const float *wr = Whh + (long)min(row, H - 1) * G + ((tid >> 2) & 3) * H;
 #pragma unroll
-    for (int j = 0; j < 8 * KS; ++j) wv[j] = wr[min(j, H - 1)];
+    for (int j = 0; j < 8 * KS; ++j) {
+      wv[j] = wr[min(j, H - 1)];
+      least = fminf(least, fabsf(wv[j])); // (past the last column: the last one again)
+      if (j >= lstm_units_from<KS>()) wv[j] = j < H ? wv[j] : 0.f;
+    }
 #pragma unroll
     for (int j = 0; j < 8 * KS; j += 2) most = sf_max3(wv[j], wv[j + 1], most);
   }
   for (int i = tid; i < 2 * 16 * KP; i += blockDim.x) (&d_s[0][0])[i] = (_Float16)0.f;
   if (tid < 6) top[tid >> 1][tid & 1] = 0;
+  float widest = fmaxf(most, quad_mirror(half_mirror(most))); // of the row's four gates
+  widest = fmaxf(widest, row_swap8(widest));
+  const bool wild = __syncthreads_or(widest >= LSTM_WILD || least < widest * 0x1p-26f); // (large ones as in lstm_fwd2_kernel: where such a weight's gate is saturated)
+  asm volatile("" : "+v"(tid)); // (what follows is not worked out, and kept, before the weights are loaded)
+  const int lane = tid & 63, q = tid & 3, u = tid >> 2, e = q >> 1, p = q & 1;
+  const int b = min(b0 + e, B - 1); // (an example past the last one: the last one again, not stored)
+  const bool unit_ok = u < H, store = unit_ok && b0 + e < B;
+  const int ul = unit_ok ? u : 0;
+  const int bg = (lane >> 2) & 3; // the block's gate
   const unsigned colb = 4u * (p * H + ul), ub = 4u * ul, eb = (unsigned)(b - b0) * (unsigned)T * 4u; // (gates p and p + 2)
   float *const grow0 = gates + (long)b0 * T * G;
   const float *const crow0 = cs + (long)b0 * T * H;
@@ -539,7 +574,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   float dc = 0.f;
   uint32_t used[2] = {27u, 27u};  // exponents that the two examples' gradients in LDS are scaled by
   uint32_t guess[2] = {27u, 27u}; // the last step's largest, which the next one's are scaled by
-  const bool wild = __syncthreads_or(most >= LSTM_WILD); // (as in lstm_fwd2_kernel: where such a weight's gate is saturated)
   // beside dL/dc_t (output gate: dL/dh_t): this lane's two gates' factors, what dL/dh_t adds to dL/dc_t and what goes on to
   // dL/dc_{t-1}; va, vb: the activated gates, ct, cp: c_t and c_{t-1}
   struct Factors { float ka, kb, a, gf; };
@@ -559,40 +593,45 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   };
   const unsigned col0 = colb + eb * (unsigned)G, u0 = ub + eb * (unsigned)H;
+  // the four gates' sums of the block's units: the halves of a row of sixteen lanes exchange two units each, then its quads
+  // one; this lane's unit
+  auto gates_sum = [&](const f32x4 s) {
+    const bool hi = lane & 8, odd = lane & 4;
+    const float r0 = (hi ? s[2] : s[0]) + row_swap8(hi ? s[0] : s[2]);
+    const float r1 = (hi ? s[3] : s[1]) + row_swap8(hi ? s[1] : s[3]);
+    return (odd ? r1 : r0) + quad_mirror(half_mirror(odd ? r0 : r1));
+  };
   if (wild) {
-    float *const df = reinterpret_cast<float *>(&d_s[0][0]) + e * G; // [step parity][example][gate column]
-    static_assert(sizeof(d_s) >= 4 * 4 * 8 * KS * sizeof(float), "gate gradients in fp32");
+    float *const df = reinterpret_cast<float *>(&d_s[0][0]) + e * 4 * KP; // [step parity][example][gate][unit]
+    static_assert(sizeof(d_s) == 16 * KP * sizeof(float), "gate gradients in fp32");
     for (int t = T - 1, n = 0; t >= 0; --t, ++n) {
-      const float *dp = df + (n & 1) * 2 * G, *wr = Whh + (long)ul * G;
-      float dh = 0.f, da, db;
-      for (int j = p; j < G; j += 2) dh = fmaf(wr[j], dp[j], dh);
-      dh += quad_xor1(dh);
+      const float *gr = grow0 + (long)t * G, *dp = df + (n & 1) * 8 * KP + bg * KP;
+      const Factors f = factors(t, lane_ld(gr, col0), lane_ld(gr, col0 + 8u * H), lane_ld(crow0 + (long)t * H, u0), lane_ld(crow0 + (long)max(t - 1, 0) * H, u0));
+      float dh = gates_sum(lstm_fp32_product<KS>(wv, dp)), da, db;
       if (SEQ || t == T - 1) dh += dh_own;
-      const float *gr = grow0 + (long)t * G;
-      cell(t, dh, factors(t, lane_ld(gr, col0), lane_ld(gr, col0 + 8u * H), lane_ld(crow0 + (long)t * H, u0), lane_ld(crow0 + (long)max(t - 1, 0) * H, u0)),
-           col0, da, db);
+      cell(t, dh, f, col0, da, db);
       if (unit_ok) {
-        float *o = df + ((n + 1) & 1) * 2 * G + p * H + u;
-        o[0] = da; o[2 * H] = db;
+        float *o = df + ((n + 1) & 1) * 8 * KP + p * KP + u;
+        o[0] = da; o[2 * KP] = db;
       }
       __syncthreads();
     }
     return;
   }
   f16x4 w[2][2 * KS];
-  float un[4];
+  f32x4 un;
   {
     const uint32_t ex = sf_exponent(__float_as_uint(most));
-    const float sc = sf_scale(ex), back = sf_unscale(ex);
-    un[0] = quad_bcast<0>(back); un[1] = quad_bcast<1>(back); un[2] = quad_bcast<2>(back); un[3] = quad_bcast<3>(back);
+    const float sc = sf_scale(ex), back = sf_unscale(ex), piece = p ? 1.f / 2048.f : 1.f;
+    un[0] = quad_bcast<0>(back) * piece; un[1] = quad_bcast<1>(back) * piece; un[2] = quad_bcast<2>(back) * piece; un[3] = quad_bcast<3>(back) * piece;
 #pragma unroll
     for (int i = 0; i < 2 * KS; ++i) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float v = 4 * i + j < H && row < H ? wv[4 * i + j] * sc : 0.f;
+        const float v = wv[4 * i + j] * sc;
         const _Float16 hi = (_Float16)v;
         w[0][i][j] = hi;
-        w[1][i][j] = (_Float16)(v - (float)hi);
+        w[1][i][j] = (_Float16)((v - (float)hi) * 2048.f);
       }
     }
   }
@@ -620,16 +659,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       acc[0] = __builtin_amdgcn_mfma_f32_4x4x4f16(w[0][2 * i + 1], d1, acc[0], 0, 0, 0);
       acc[1] = __builtin_amdgcn_mfma_f32_4x4x4f16(w[1][2 * i + 1], d1, acc[1], 0, 0, 0);
     }
-    float s[4];
+    f32x4 s;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) s[r] = (acc[0][r] + acc[1][r]) * un[r];
-    // the four gates' sums: the halves of a row of sixteen lanes exchange two units each, then its quads one
-    const bool hi = lane & 8, odd = lane & 4;
-    const float r0 = (hi ? s[2] : s[0]) + row_swap8(hi ? s[0] : s[2]);
-    const float r1 = (hi ? s[3] : s[1]) + row_swap8(hi ? s[1] : s[3]);
-    float dh = (odd ? r1 : r0) + quad_mirror(half_mirror(odd ? r0 : r1));
+    for (int r = 0; r < 4; ++r) s[r] = fmaf(acc[1][r], 1.f / 2048.f, acc[0][r]) * un[r];
+    float dh = gates_sum(s);
     dh += quad_xor1(dh); // the other piece
-    dh *= __uint_as_float(((e ? used[1] : used[0]) - 8u) << 23);
+    dh *= __uint_as_float(((e ? used[1] : used[0]) - 11u) << 23);
     if (SEQ || t == T - 1) dh += dh_own;
     float da, db;
     cell(t, dh, f, colx, da, db);
@@ -642,18 +677,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if ((lane & 13) == 0) atomicMax(&mine[e], __float_as_uint(m)); // (lanes 0 and 2 of a row: the examples)
     if (tid < 2) top[(n + 1) % 3][tid] = 0;
     auto put = [&](uint32_t ee) {
-      const float sc = __uint_as_float((262u - ee) << 23); // 2^8 over the power of two
+      const float sc = __uint_as_float((265u - ee) << 23); // 2^11 over the power of two
       _Float16 *o = dout + (p * 4 + 2 * e) * KP + u;       // [gate][example, piece][unit]
       const float ya = da * sc, yb = db * sc;
       const _Float16 ha = (_Float16)ya, hb = (_Float16)yb;
-      o[0] = ha; o[KP] = (_Float16)(ya - (float)ha);
-      o[8 * KP] = hb; o[9 * KP] = (_Float16)(yb - (float)hb);
+      o[0] = ha; o[KP] = (_Float16)((ya - (float)ha) * 2048.f);
+      o[8 * KP] = hb; o[9 * KP] = (_Float16)((yb - (float)hb) * 2048.f);
     };
     if (unit_ok) put(e ? guess[1] : guess[0]);
     __syncthreads();
     const uint32_t x0 = exponent(mine[0]), x1 = exponent(mine[1]);
     const int off0 = (int)x0 - (int)guess[0], off1 = (int)x1 - (int)guess[1];
-    const bool again0 = off0 > 6 || off0 < -8, again1 = off1 > 6 || off1 < -8; // too large, or small enough to lose bits
+    const bool again0 = off0 > 3 || off0 < -3, again1 = off1 > 3 || off1 < -3; // too large, or small enough to lose bits
     if (again0 || again1) { // (an example's scales never depend on the other one)
       if (unit_ok && (e ? again1 : again0)) put(e ? x1 : x0);
       if (again0) guess[0] = x0;

@@ -231,3 +231,32 @@ def test_lstm_weights_of_very_different_sizes(hidden, power, where, out):
     assert np.isfinite(norms0).all() and np.allclose(norms, norms0, rtol=4e-6), np.abs(norms / norms0 - 1).max()
     _by_tensor(m, clipped, parts[0][2] + parts[1][2], 4e-6, "clipped")
     _by_tensor(m, plain, parts[0][3] + parts[1][3], 4e-6, "plain")
+
+
+@pytest.mark.parametrize("out", ["last", "seq"])
+@pytest.mark.parametrize("hidden", [48, 64, 100, 128])
+@pytest.mark.parametrize("power,between", [(12, 2.0 ** -25), (18, 2.0 ** -25), (23, 2.0 ** -25), (30, 0.0)])
+def test_lstm_gate_gradients_of_very_different_sizes(hidden, power, between, out):
+    """Half of the units count 2^power less and hardly look at the other half's gates: their part of the gradient comes from themselves.
+    Two examples per workgroup against one, which is fp32 throughout."""
+    layers = [W.embedding(40, 9), (W.lstm_last if out == "last" else W.lstm_seq)(9, hidden)]
+    m = W.model(W.token_input(12), layers + ([W.seq_mean()] if out == "seq" else []) + [W.dense(hidden, 3)], 3)
+    rng = np.random.default_rng(hidden + power)
+    x, y = W.make_inputs(m, 258, rng, zipf_exponent=0.8)
+    theta = W.init_params(m, rng, bias_scale=0.3) * np.float32(2)
+    at = {(li, name): slice(off, off + int(np.prod(shape))) for li, name, shape, off in W.param_tensors(m)}
+    last = max(li for li, _ in at)
+    half = np.arange(hidden) < hidden // 2  # the units that count
+    gates = np.tile(half, 4)
+    w = theta[at[1, "W_hh"]].reshape(hidden, 4 * hidden)
+    w[np.ix_(~half, gates)] = np.sign(w[np.ix_(~half, gates)]) * np.abs(w).max() * np.float32(between)
+    theta[at[last, "W"]].reshape(hidden, 3)[~half] *= np.float32(2.0 ** -power)
+    _, norms, clipped, plain = _both_gradients(m, theta, x, y, 258)
+    parts = [_both_gradients(m, theta, x[i:i + 129], y[i:i + 129], 129) for i in (0, 129)]
+    assert np.allclose(norms, np.concatenate([p[1] for p in parts]), rtol=4e-6)
+    for got, ref, label in ((clipped, parts[0][2] + parts[1][2], "clipped"), (plain, parts[0][3] + parts[1][3], "plain")):
+        _by_tensor(m, got, ref, 4e-6, label)
+        for name in ("W_ih", "W_hh", "b"):
+            a, b = (v[at[1, name]].reshape(-1, 4 * hidden)[:, ~gates] for v in (got, ref))
+            # (rounding of sums in two orders, 4e-7 at most where all gradients are of one size, over twelve steps)
+            assert np.linalg.norm(a - b) <= 4e-6 * np.linalg.norm(b), (label, name, np.linalg.norm(a - b) / np.linalg.norm(b))
