@@ -258,5 +258,5 @@ def test_lstm_gate_gradients_of_very_different_sizes(hidden, power, between, out
         _by_tensor(m, got, ref, 4e-6, label)
         for name in ("W_ih", "W_hh", "b"):
             a, b = (v[at[1, name]].reshape(-1, 4 * hidden)[:, ~gates] for v in (got, ref))
-            # (rounding of sums in two orders, 4e-7 at most where all gradients are of one size, over twelve steps)
+            # the two routes' rounding: 3.1e-7 at most at 2^12, 9.2e-7 at 2^23; about four times that
             assert np.linalg.norm(a - b) <= 4e-6 * np.linalg.norm(b), (label, name, np.linalg.norm(a - b) / np.linalg.norm(b))
