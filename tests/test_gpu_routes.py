@@ -398,7 +398,8 @@ def test_embedding_rows_of_each_width_below_a_hidden_layer(dim, seq, vocab):
     _check_all_regimes(m, x, y, theta, f"embedding {vocab}x{dim} T{seq} below a hidden layer", stepper=DpStep(m, 9))
 
 
-# Large batches take the convolutions on the fp16 units; the routes go by the largest batch, so a few examples reach them.
+# Large batches take the convolutions on the fp16 units; the routes go by the largest batch, so a few examples reach them, but for
+# layers whose weights can be resident, which go by the batch.
 @pytest.mark.parametrize("cin,widths,plane,act,pool,max_batch,batch,routes", [
     (32, (48, 33), (32, 32), "tanh", "max", 65, 3, ["f16 -", "f16+maxpool f16"]),   # two blocks of output channels; bands of one image
     (36, (33, 100), (8, 32), "relu", "avg", 257, 3, ["f16 -", "f16+avgpool f16"]),  # ragged chunks of sixteen; one image per two waves, an odd image over
@@ -411,7 +412,13 @@ def test_embedding_rows_of_each_width_below_a_hidden_layer(dim, seq, vocab):
     (56, (256, 64), (4, 4), "tanh", "max", 4097, 19, ["f16 -", "f16+maxpool f16"]),
     (35, (260, 34), (8, 4), "relu", "avg", 2049, 9, ["f16 -", "f16+avgpool f16"]),
     (32, (48, 36), (64, 32), "relu", "avg", 33, 1, ["f16 -", "f16+avgpool f16"]),
-    (32, (32, 64), (32, 32), "tanh", "max", 33, 3, ["f16 -", "f16+maxpool split"]),  # one block; three pieces stay three
+    (32, (32, 64), (32, 32), "tanh", "max", 65, 65, ["f16 -", "f16+maxpool split"]), # one block; three pieces stay three; the smallest batch that is not left to resident weights
+    (32, (32, 64), (32, 32), "tanh", "max", 65, 64, ["f16 -", "f16+maxpool split"]), # the largest that is
+    (32, (32, 64), (32, 32), "tanh", "max", 64, 3, ["mf32 -", "f16+maxpool split"]),
+    (32, (48, 33), (32, 32), "tanh", "max", 65, 33, ["f16 -", "f16+maxpool f16"]),
+    (40, (32, 64, 32), (16, 16), "relu", "avg", 140, 129, ["split -", "f16 split", "split+avgpool f16"]),  # 32 -> 64 each way, above the line and on it
+    (40, (32, 64, 32), (16, 16), "relu", "avg", 140, 128, ["split -", "f16 split", "split+avgpool f16"]),
+    (40, (32, 64, 32), (16, 16), "relu", "avg", 128, 5, ["split -", "mf32 split", "split+avgpool mf32"]),
     (64, (128, 128), (8, 8), "relu", "avg", 513, 3, ["f16 -", "f16+avgpool f16"]),   # one tile over the line, and on it
     (64, (128, 128), (8, 8), "relu", "avg", 512, 3, ["mf64 -", "mf64+avgpool mf64"]),
 ])
